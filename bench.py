@@ -67,10 +67,13 @@ FAMILY_VECTOR_BYTES = {
     "msd": 160,          # two chains as moment_pair + two accumulators read + write
     "evolve_pair": 160,  # two chains as moment_pair + two accumulators read + write
 }
+# the same for one launch of a march, which takes several steps: per chain two elements read
+# and two written, and the accumulators once
+FAMILY_MARCH_BYTES = {"moment_sym": 64, "moment_pair": 128, "evolve": 96, "msd": 192, "evolve_pair": 192}
 FAMILY_KERNEL = {"moment": "k_moment_step", "moment_sym": "k_moment_step_sym",
                  "moment_pair": "k_moment_step_pair", "evolve": "k_evolve_term", "msd": "k_msd_term",
                  "evolve_pair": "k_evolve_pair_term"}
-KERNEL_SOURCES = ("device_common.h", "internal.h", "kernels.hip")   # what the step kernels are built from
+KERNEL_SOURCES = ("device_common.h", "internal.h", "kernels.hip", "march.h", "march_core.h", "lattice.cpp")   # what the step kernels are built from
 
 
 def log(msg):
@@ -92,33 +95,22 @@ def family_bytes(info, B, family="moment"):
         per_entry = 2
     else:
         per_entry = 4 + {0: 0, 1: 8, 2: 16}[mode] + (8 if family == "msd" else 0)
-    if box_used(info, B, family):
-        per_entry = 0          # the box stencil reads no neighbour indices
+    if march_used(info, family):   # no indices; one launch is several steps
+        per_entry = {0: 0, 1: 8, 2: 16, 3: 2}[mode]
+        return int(info.entries) * per_entry + n * 8 + n * FAMILY_MARCH_BYTES[family] * B
     return int(info.entries) * per_entry + n * 8 + n * FAMILY_VECTOR_BYTES[family] * B
 
 
-def box_used(info, B, family):
-    """Whether the family runs a periodic-box stencil kernel: the Hermitian moment step with
-    variant bit 26 (a handle whose matrix is a periodic box, or whose segments are all
-    periodic squares: the sheet form), the MSD term with bit 27 (a periodic box with uniform
-    x steps); blocks of B >= 2."""
-    if B < 2 or (int(info.box[0]) <= 0 and int(info.sheets) == 0):
-        return False
+def march_used(info, family):
+    """Whether the family runs as a lattice march, several steps per launch (variant bit 26, set
+    where the handle's lattice has one; the MSD term with bit 27 too)."""
     v = int(info.kernel_variant)
-    if family == "moment_sym":
-        return (v >> 26) & 1 == 1
-    if int(info.box[0]) <= 0:
-        return False
-    if family == "msd":
-        return (v >> 27) & 1 == 1 and int(info.box_msd) == 1
-    return False
+    return bool((v >> 26) & 1) and family in FAMILY_MARCH_BYTES and (family != "msd" or bool((v >> 27) & 1))
 
 
 def kernel_name(info, B, family):
-    """The kernel the family runs on this handle: the general one, or its box or sheet form."""
-    if not box_used(info, B, family):
-        return FAMILY_KERNEL[family]
-    return FAMILY_KERNEL[family] + ("_box" if int(info.box[0]) > 0 else "_sheet")
+    """The kernel the family runs on this handle: the general one, or the march."""
+    return "k_march (%s)" % family if march_used(info, family) else FAMILY_KERNEL[family]
 
 
 SERIES_FAMILIES = ("evolve", "msd", "evolve_pair")
@@ -126,7 +118,7 @@ SERIES_FAMILIES = ("evolve", "msd", "evolve_pair")
 
 def family_config(v, family):
     """What the variant code v sets for one kernel family: (non-temporal loads, banded order,
-    pencil order, cap on resident workgroups per CU).  Bit 0 non-temporal loads (bit 7 flips it
+    pencil order, cap on resident workgroups per CU, lattice march).  Bit 0 non-temporal loads (bit 7 flips it
     for the evolution and MSD families), bit 1 banded order, bit 6 pencil order, bits 2-5 the
     per-CU cap (0 = none) unless the family has its own (3 bits per family from bit 8: 0 = the
     per-CU cap, 1 + c = cap c)."""
@@ -139,8 +131,10 @@ def family_config(v, family):
     c = (v >> (8 + 3 * K_FAMILIES.index(family))) & 7
     if c:
         cap = c - 1
-    box = (v >> 26) & 1 if family == "moment_sym" else ((v >> 27) & 1 if family == "msd" else 0)
-    return nt, banded, banded & ((v >> 6) & 1), cap, box
+    march = (v >> 26) & 1 if family in FAMILY_MARCH_BYTES else 0
+    if family == "msd":
+        march &= (v >> 27) & 1
+    return nt, banded, banded & ((v >> 6) & 1), cap, march
 
 
 def variant_text(v, family=None):
@@ -148,9 +142,9 @@ def variant_text(v, family=None):
     if family is None:
         nt, banded, pencil, cap = v & 1, (v >> 1) & 1, ((v >> 1) & (v >> 6)) & 1, (v >> 2) & 15
     else:
-        nt, banded, pencil, cap, box = family_config(v, family)
-        if box:
-            return "code %d: stencil form, %s" % (v, "%d workgroups/CU" % cap if cap else "full occupancy")
+        nt, banded, pencil, cap, march = family_config(v, family)
+        if march:
+            return "code %d: lattice march" % v
     order = "pencil" if pencil else ("banded" if banded else "plain")
     return "code %d: %s loads, %s row order, %s" % (v, "non-temporal" if nt else "plain", order,
                                                    "%d workgroups/CU" % cap if cap else "full occupancy")

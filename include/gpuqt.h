@@ -149,15 +149,12 @@ typedef struct {
                                 of per-entry hopping gradients */
   int32_t pencil_mask;       /* bit log2(B) set: block width B has a pencil row order */
   int32_t box[3];            /* (Lx, Ly, Lz) when H is a periodic simple cubic box in natural
-                                order with one uniform hopping (see gpuqt_autotune, bit 26),
-                                else 0 */
+                                order with one uniform hopping, else 0 */
   int32_t box_msd;           /* 1: on that box the position differences are +-dx for the x
-                                neighbours and 0 for the others, so the MSD term can run as a
-                                box stencil too (bit 27) */
+                                neighbours and 0 for the others */
   int32_t sheets;            /* 1: every segment is a periodic Lx x Ly square in natural order
                                 (rows off_s + x + Lx y, each with its four periodic neighbours,
-                                Lx, Ly >= 3, Lx Ly <= 2^24) with one uniform hopping, so the
-                                Hermitian step can run as a sheet stencil (bit 26) */
+                                Lx, Ly >= 3, Lx Ly <= 2^24) with one uniform hopping */
 } gpuqt_h_info_t;
 
 /* Describe the layout.  energy_max (may be NULL) receives [n_segments] DeltaE;
@@ -178,7 +175,10 @@ enum {
 /* Bytes of device workspace `op` needs for B columns, M moments and Np
  * Chebyshev terms per time step.  Np = 0 reserves room for up to 8192 terms
  * (enough for DeltaE*|dt| up to about 7000).  M is ignored by the EVOLVE
- * operations, Np by MOMENTS and MOMENTS_BACKWARD. */
+ * operations, Np by MOMENTS and MOMENTS_BACKWARD.  On a lattice with marches (gpuqt_autotune,
+ * bit 26) the size of EVOLVE, EVOLVE_COMMUTATOR, VAC and MSD includes room for them (4, 8, 10
+ * and 10 vectors instead of 2, 5, 9 and 9) up to 32 GiB; a call given less, but the general
+ * kernels' share, runs those. */
 gpuqt_status gpuqt_workspace_size(gpuqt_h h, int32_t op, int32_t B, int32_t M, int32_t Np,
                                   size_t *bytes);
 
@@ -408,20 +408,16 @@ gpuqt_status gpuqt_vac_backward_tape_workspace_size(gpuqt_h h, int32_t B, int32_
  * streamed data at this B, and for B >= 2 with two bands per period for
  * periods of 1024 rows or more: workgroups then sweep bands of W rows of the
  * period one period after another, so rows D apart are visited W rows apart);
- * bit 26: on a periodic simple cubic box (one segment, rows x + Lx (y + Ly z), each
- * with its six periodic neighbours, one uniform hopping; gpuqt_h_info_t.box), the Hermitian
- * moment step of blocks of B >= 2 vectors as a box stencil: a workgroup marches through
- * a column of the box, keeps each lane's elements of three consecutive planes in
- * registers and the current plane's tile in LDS, so x is read about once per step instead
- * of once per neighbour and no neighbour indices are read (timed against the best other
- * variant, kept when faster); on segments that are all periodic squares
- * (gpuqt_h_info_t.sheets) bit 26 selects the two-dimensional form: a workgroup marches
- * along y through a strip of 256 / B cells of one segment, rows y - 1, y, y + 1 in
- * registers and row y in LDS; bit 27: the fused MSD term likewise (both chains staged,
- * where the position differences are +-dx on the x neighbours and 0 on the others,
- * gpuqt_h_info_t.box_msd), timed against the MSD family's best and kept when faster;
- * both box kernels are timed uncapped and at caps 1..6 and keep the fastest as their
- * family's own cap;
+ * bit 26: on a lattice with a fixed neighbour pattern (a periodic simple cubic box with one
+ * hopping; segments that are all periodic squares; segments that are all periodic brick-wall
+ * honeycombs, rows x + Lx y with the neighbours x +- 1 and one of y +- 1, Lx and Ly even),
+ * natural order, the marches: several recurrence steps per launch in one sweep along the
+ * slowest direction, the intermediate steps held on chip, for the moments of phiL = phiR
+ * and the VAC, MSD and evolution series; blocks of vectors are then advanced as separate
+ * vectors.  Built handles of such a lattice start with bits 26 and 27 set; the autotuner
+ * times the Hermitian step's march against the best general variant and keeps the faster;
+ * bit 27: the march of the fused MSD term (where the position differences are +-dx on the
+ * x neighbours and 0 on the others);
  * bit 6 (with bit 1): the pencil order instead (built for segments with a row
  * period of at least 128 rows: the four wavefronts of a workgroup take the
  * same rows of four consecutive periods at once, so a row's neighbours one
@@ -443,8 +439,7 @@ gpuqt_status gpuqt_vac_backward_tape_workspace_size(gpuqt_h h, int32_t B, int32_
  *        Hermitian step only.
  *   times_us : NULL or HOST [7], microseconds per step of load/order variants 0..3, of
  *              the pencil order with plain (4) and non-temporal (5) loads, each at its best
- *              cap, and of the periodic-box stencil (6, at the chosen cap); 0 for what this
- *              handle and B do not have.
+ *              cap, and of the lattice march (6); 0 for what this handle and B do not have.
  * Not safe while other calls on the handle are in flight.
  */
 gpuqt_status gpuqt_autotune(gpuqt_h h, int32_t B, void *ws, size_t ws_bytes, void *stream,
@@ -457,9 +452,9 @@ gpuqt_status gpuqt_autotune(gpuqt_h h, int32_t B, void *ws, size_t ws_bytes, voi
  * cap c of 0..6), so a code read from gpuqt_h_info after gpuqt_autotune reproduces the tuned
  * configuration.  The banded and pencil bits only take effect for block widths that have
  * such an order (gpuqt_h_info_t.banded_mask, pencil_mask); a pencil bit for a width without
- * a pencil order falls back to the banded order.  Bit 26 (the box stencil of the Hermitian
- * step) takes effect on a periodic box (gpuqt_h_info_t.box) for blocks of B >= 2, bit 27
- * (that of the MSD term) where gpuqt_h_info_t.box_msd is also set.
+ * a pencil order falls back to the banded order.  Bits 26 and 27 (the marches) take effect on
+ * the lattices gpuqt_autotune describes; without bit 26 the general kernels run, whatever
+ * the lattice.
  * GPUQT_ERR_ARG for a negative code, a per-CU cap above 8, bit 6 without bit 1 or bits set
  * above bit 27. */
 gpuqt_status gpuqt_set_variant(gpuqt_h h, int32_t variant);

@@ -804,8 +804,8 @@ def gpuqt_autotune(H: Hamiltonian, B: int = 1, ws=None, stream=None):
     """Time the kernel variants (plain / non-temporal loads, plain / banded / pencil row order,
     each uncapped and at per-CU workgroup caps below its occupancy limit), keep the fastest;
     returns us per moment step of load variants 0..3, of the pencil order with plain and
-    non-temporal loads (entries 4, 5) at their best cap, and of the periodic-box stencil
-    (entry 6, at the chosen cap; blocks of B >= 2 on a periodic box), 0 where a variant does
+    non-temporal loads (entries 4, 5) at their best cap, and of the lattice march
+    (entry 6), 0 where a variant does
     not exist.
     H.info.kernel_variant: bits 0-1 the load variant, bits 2-5 the cap (0: none), bit 6 the
     pencil order, from bit 8 the two-chain moment, MSD and two-vector evolution families'
@@ -823,8 +823,8 @@ def gpuqt_set_variant(H: Hamiltonian, variant: int):
     """Pin the kernel variant code (bit 0: non-temporal streams, bit 1: banded row order,
     bits 2-5: resident workgroups per CU at most, 0 = no cap; bit 6 (with bit 1): the pencil
     order instead of the banded one; bit 7: the evolution and MSD terms on the other load
-    variant; bit 26: the periodic-box Hermitian step (blocks of B >= 2), bit 27: the
-    periodic-box MSD term; from bit 8, 3 bits per kernel
+    variant; bit 26: the lattice marches, bit 27: the march of the
+    MSD term; from bit 8, 3 bits per kernel
     family: 0 = that cap, 1 + c = the family's own cap c).  H.info.kernel_variant after
     gpuqt_autotune is such a code."""
     _check(lib().gpuqt_set_variant(H.handle, int(variant)), "gpuqt_set_variant")

@@ -13,7 +13,10 @@ CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libgpuqt.so")
 BUILD_DIR = os.path.join(ROOT, "_build")
 
-SOURCES = ["kernels.hip", "kernels_adjoint.hip", "api.cpp", "layout.cpp", "io.cpp", "tune.cpp", "noalloc.hip"]
+SOURCES = ["kernels.hip", "kernels_adjoint.hip", "api.cpp", "layout.cpp", "io.cpp", "tune.cpp", "noalloc.hip",
+           "lattice.cpp", "march.hip", "march_square_uniform.hip", "march_square_real.hip", "march_square_complex.hip", "march_square_dict.hip",
+           "march_brick_uniform.hip", "march_brick_real.hip", "march_brick_complex.hip", "march_brick_dict.hip",
+           "march_box_uniform.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I", os.path.join(ROOT, "include")]
@@ -43,7 +46,7 @@ def build(verbose: bool = False) -> str:
         obj = os.path.join(BUILD_DIR, os.path.splitext(src)[0] + ".o")
         objs.append(obj)
         cmds.append([hipcc, *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj])
-    with concurrent.futures.ThreadPoolExecutor(max_workers=len(cmds)) as ex:
+    with concurrent.futures.ThreadPoolExecutor(max_workers=min(len(cmds), os.cpu_count() or 8)) as ex:
         for lines in ex.map(_run, cmds):
             if verbose:
                 print("\n".join(lines))

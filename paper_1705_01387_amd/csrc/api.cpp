@@ -85,6 +85,32 @@ int op_vectors(int op) {
   }
 }
 
+// Vectors an operation needs to run as marches (four chain buffers a chain, the running
+// sums and the states), and whether the handle's marches cover the operation.
+int march_vectors(int op) {
+  switch (op) {
+    case GPUQT_OP_MOMENTS: return 4;
+    case GPUQT_OP_EVOLVE: return 4;
+    case GPUQT_OP_EVOLVE_COMMUTATOR: return 8;
+    case GPUQT_OP_VAC: return 10;
+    case GPUQT_OP_MSD: return 10;
+    default: return 0;
+  }
+}
+bool march_covers(const Handle* h, int op, int B) {
+  switch (op) {
+    case GPUQT_OP_MOMENTS: return h->march_on(MF_SYM, B);
+    case GPUQT_OP_EVOLVE: return h->march_on(MF_EVO, B);
+    case GPUQT_OP_EVOLVE_COMMUTATOR: return h->march_on(MF_MSD, B);
+    case GPUQT_OP_VAC: return h->march_on(MF_PAIR, B) && h->march_on(MF_EVO2, B);
+    case GPUQT_OP_MSD: return h->march_on(MF_MSD, B) && h->march_on(MF_SYM, B);
+    default: return false;
+  }
+}
+// Workspaces grow for the marches up to this size; beyond it the general kernels keep
+// the smaller one, so that the largest systems a device holds still fit.
+constexpr size_t kMarchWsMax = size_t(32) << 30;
+
 gpuqt_status check_device(const Handle* h) {
   int dev = -1;
   HIP_TRY(hipGetDevice(&dev));
@@ -363,6 +389,177 @@ gpuqt_status run_evolve_pair(const Handle* h, int B, double dt, int Np, const do
     cb = ob;
   }
   return GPUQT_OK;
+}
+
+// ---------------------------------------------------------------------------
+// marches (march.h): vectors are planar, column c of a block at c * n
+// ---------------------------------------------------------------------------
+
+// Buffers a march may write.
+struct BufPool {
+  std::vector<double2*> free;
+  double2* take() {
+    double2* p = free.back();
+    free.pop_back();
+    return p;
+  }
+  void give(const double2* p) { free.push_back(const_cast<double2*>(p)); }
+};
+
+// The sums of a series: tables of one time step and where they are kept.
+struct MarchSums {
+  double2* acc[2] = {nullptr, nullptr};     // updated by every launch
+  double2* last[2] = {nullptr, nullptr};    // written by the last launch (taken from the pool when NULL and
+                                            // keep is unset; else acc)
+  bool keep = true;
+  const double* J = nullptr;
+  int ldJ = 0;
+  double sgn = 1.0;
+};
+
+int timing_family(int mf) {
+  switch (mf) {
+    case MF_SYM: return GPUQT_K_MOMENT_SYM;
+    case MF_PAIR: return GPUQT_K_MOMENT_PAIR;
+    case MF_EVO: return GPUQT_K_EVOLVE;
+    case MF_EVO2: return GPUQT_K_EVOLVE_PAIR;
+    default: return GPUQT_K_MSD;
+  }
+}
+
+// Steps 1 .. K of a family from xa (and xb; NULL with MF_MSD: chain b starts from zero),
+// T a launch, chain elements in buffers of the pool (4 per chain).  late: buffers that
+// become free once the first launch has read its inputs.  dots go to part, sums to su.
+gpuqt_status run_march(const Handle* h, int B, int fam, int K, const double2* xa, const double2* xb, BufPool* pool,
+                       const std::vector<const double2*>& late, double2* part, MarchSums* su, hipStream_t s,
+                       double2* const* keep = nullptr) {
+  // keep: every chain vector to its own buffer (rows of B columns), a_k to keep[k-1], b_k to keep[K+k-1]
+  const Handle::MarchDev& m = h->march[fam][Handle::log2B(B)];
+  const MarchMat A = h->march_mat(fam, B);
+  const int NC = (fam == MF_SYM || fam == MF_EVO) ? 1 : 2;
+  const int launches = (K + m.T - 1) / m.T;
+  TimeScope ts(h, s, timing_family(fam), launches);
+  MarchIO io;
+  std::memset(&io, 0, sizeof(io));
+  io.zero_b = NC == 2 && !xb;
+  io.x[0] = xa;
+  io.x[1] = NC == 2 ? (xb ? xb : xa) : nullptr;
+  io.k_end = K;
+  io.part = part;
+  if (su) {
+    io.J = su->J;
+    io.ldJ = su->ldJ;
+    io.sgn = su->sgn;
+  }
+  for (int q = 0; q < launches; ++q) {
+    const bool last = q + 1 == launches;
+    io.first = q == 0;
+    io.k0 = 1 + q * m.T;
+    io.keep = keep ? 1 : 0;
+    for (int c = 0; c < NC && keep; ++c) {
+      for (int t = 0; t < m.T; ++t) io.keepv[c][t] = io.k0 + t <= K ? keep[c * K + io.k0 + t - 1] : nullptr;
+      io.o1[c] = io.keepv[c][m.T - 2];
+      io.o2[c] = io.keepv[c][m.T - 1];
+    }
+    for (int c = 0; c < NC && !keep; ++c) {
+      io.o1[c] = last ? nullptr : pool->take();
+      io.o2[c] = last ? nullptr : pool->take();
+    }
+    for (int c = 0; c < NC && su; ++c) {
+      io.acc_in[c] = su->acc[c];
+      if (last && !su->keep) su->last[c] = pool->take();
+      io.acc_out[c] = last && !su->keep ? su->last[c] : su->acc[c];
+    }
+    HIP_TRY(launch_march(h->lat.pattern, h->hop_mode, fam, m.lanes, A, io, s));
+    if (q == 0) {
+      for (const double2* p : late) pool->give(p);
+    } else if (!keep) {
+      for (int c = 0; c < NC; ++c) {
+        pool->give(io.x[c]);
+        pool->give(io.w[c]);
+      }
+    }
+    for (int c = 0; c < NC; ++c) {
+      io.w[c] = io.o1[c];
+      io.x[c] = io.o2[c];
+    }
+  }
+  return GPUQT_OK;
+}
+
+// Moments of the Hermitian set phi ([n][B], or planar) into mu (complex) or mu_re, by the march
+// when the handle has it and `buf` holds four vectors, else by the general step with buf[0], buf[1].
+gpuqt_status run_moment_set(const Handle* h, int B, const double2* phi, bool planar, int M, double2* part,
+                            double2* const* buf, int nbuf, double2* mu, double* mu_re, hipStream_t s) {
+  gpuqt_status st;
+  if (nbuf >= 4 && h->march_on(MF_SYM, B)) {
+    const double2* x = phi;
+    BufPool pool;
+    std::vector<const double2*> late;
+    for (int i = 0; i < 4; ++i) pool.free.push_back(buf[i]);
+    if (!planar && B > 1) {   // the planar copy is one of the buffers the second launch writes
+      double2* p = pool.take();
+      HIP_TRY(launch_to_planar(h->n, B, phi, p, s));
+      x = p;
+      late.push_back(p);
+    }
+    if ((st = run_march(h, B, MF_SYM, pair_steps(M), x, nullptr, &pool, late, part, nullptr, s))) return st;
+    const Handle::MarchDev& m = h->march[MF_SYM][Handle::log2B(B)];
+    HIP_TRY(launch_reduce_moments(part, M, m.items, B, h->n_seg, m.item0, 1, mu, mu_re, s));
+    return GPUQT_OK;
+  }
+  if ((st = run_moments(h, B, phi, phi, M, part, buf[0], buf[1], s, true))) return st;
+  HIP_TRY(launch_reduce_moments(part, M, h->G_of(B, FAM_SYM), B, h->n_seg, h->blk0_of(B, FAM_SYM), 1, mu, mu_re, s));
+  return GPUQT_OK;
+}
+
+// out = J_0 in (in NULL: zero) on planar vectors
+gpuqt_status march_scale(const Handle* h, int B, const double2* in, double2* out, const double* J, int ldJ,
+                         hipStream_t s) {
+  const DevMat D = h->view(1);
+  for (int c = 0; c < B; ++c)
+    HIP_TRY(launch_scale(D, 1, in ? in + (int64_t)c * h->n : nullptr, out + (int64_t)c * h->n, J, ldJ, s));
+  return GPUQT_OK;
+}
+
+// V in on planar vectors
+gpuqt_status march_velocity(const Handle* h, int B, const double2* in, double2* out, hipStream_t s) {
+  const DevMat D = h->view(1);
+  for (int c = 0; c < B; ++c)
+    HIP_TRY(launch_commutator(D, h->hop_mode, 1, GPUQT_VELOCITY, in + (int64_t)c * h->n, out + (int64_t)c * h->n, s));
+  return GPUQT_OK;
+}
+
+// One time step of planar chains: out_a = U(dt) a, and (fam MF_EVO2) out_b = U(dt) b or (MF_MSD)
+// out_b = [X, U(dt)] a + U(dt) b, b NULL for zero.  The pool holds 4 buffers per chain, of which
+// `late` may come back after the first launch.  move: the sums end in buffers taken from the
+// pool instead (su.last), out_a and out_b being scratch until then.
+gpuqt_status march_evolve(const Handle* h, int B, int fam, double dt, int Np, const double2* a, const double2* b,
+                          double2* out_a, double2* out_b, BufPool* pool, const std::vector<const double2*>& late,
+                          double* Jtab, bool move, MarchSums* su, hipStream_t s, double2* const* keep = nullptr) {
+  HIP_TRY(launch_bessel_table(h->d_seg_dE, h->n_seg, std::fabs(dt), Np, Np, Jtab, s));
+  su->acc[0] = out_a;
+  su->acc[1] = out_b;
+  su->keep = !move;
+  su->J = Jtab;
+  su->ldJ = Np;
+  su->sgn = dt >= 0 ? 1.0 : -1.0;
+  if (Np == 1) {
+    gpuqt_status st;
+    if (keep) {   // rows of B columns
+      HIP_TRY(launch_scale(h->view(B), B, a, out_a, Jtab, Np, s));
+      HIP_TRY(launch_scale(h->view(B), B, b, out_b, Jtab, Np, s));
+      return GPUQT_OK;
+    }
+    if (move) {
+      su->last[0] = pool->take();
+      su->last[1] = fam == MF_EVO ? nullptr : pool->take();
+    }
+    if ((st = march_scale(h, B, a, move ? su->last[0] : out_a, Jtab, Np, s))) return st;
+    if (fam != MF_EVO) return march_scale(h, B, b, move ? su->last[1] : out_b, Jtab, Np, s);
+    return GPUQT_OK;
+  }
+  return run_march(h, B, fam, Np - 1, a, b, pool, late, nullptr, su, s, keep);
 }
 
 // Source of the adjoint recurrence: real loss weights w[seg][b][n] on Re mu_n,
@@ -683,16 +880,14 @@ gpuqt_status gpuqt_build_h(const gpuqt_h_desc* desc, void* stream, gpuqt_h* out)
   up((void**)&h->d_seg_hop, L.seg_hop.data(), L.seg_hop.size() * 8);
   up((void**)&h->d_seg_hop0, L.seg_hop.data(), L.seg_hop.size() * 8);
   h->max_nn_in = desc->max_nn;
-  if (L.hop_mode == HOP_UNIFORM && L.n_seg == 1 && L.uniform_width == 6 && detect_box(desc, h->box))
-    h->box_msd_ok = box_dx_uniform(L, h->box, &h->box_dx) ? 1 : 0;
+  if (L.hop_mode == HOP_UNIFORM && L.n_seg == 1 && L.uniform_width == 6) (void)detect_box(desc, h->box);
   // plans for fewer resident workgroups per CU, and each hot family's occupancy
   h->d_plans[kPerCU - 1] = h->d_plan;
   h->d_blk0s[kPerCU - 1] = h->d_seg_blk0;
   h->Gs[kPerCU - 1] = h->G;
   std::vector<std::vector<BlkPlan>> plans(kPerCU);   // alive until the stream is synchronised
   std::vector<std::vector<int32_t>> blk0s(kPerCU);
-  std::vector<int32_t> sheet_host, sheet_zc, sheet_blk0;   // alive until the stream is synchronised
-  std::vector<int64_t> sheet_off;
+  std::vector<char> march_host;   // alive until the stream is synchronised
   for (int p = 1; p < kPerCU; ++p) {
     plan_blocks(L.seg_off, cus, p, &plans[p - 1], &blk0s[p - 1]);
     h->Gs[p - 1] = (int32_t)plans[p - 1].size();
@@ -706,31 +901,47 @@ gpuqt_status gpuqt_build_h(const gpuqt_h_desc* desc, void* stream, gpuqt_h* out)
         for (int v = 0; v < 2; ++v)
           h->occ[f][lb][v] = (int8_t)std::min(kPerCU, kernel_occupancy(f, D0, h->hop_mode, 1 << lb, v));
   }
-  // segments that are all periodic squares with one uniform hopping: the sheet kernel's
-  // (Lx, Ly) and first row per segment, and per plan and block width its own split of the
-  // plan's workgroups over the segments (by work, not rows) and rows per work item
-  if (L.hop_mode == HOP_UNIFORM && h->box[0] == 0 && detect_sheets(desc, L.seg_off, &sheet_host)) {
-    const int ns = L.n_seg;
-    sheet_off.assign(L.seg_off.begin(), L.seg_off.end() - 1);
-    sheet_zc.assign((size_t)kPerCU * kNumB * ns, 1);
-    sheet_blk0.assign((size_t)kPerCU * kNumB * (ns + 1), 0);
-    std::vector<int32_t> len(ns), b0, zc;
-    std::vector<int64_t> cols(ns);
-    for (int sg = 0; sg < ns; ++sg) len[sg] = sheet_host[2 * sg + 1];
-    for (int p = 0; p < kPerCU; ++p) {
-      for (int lb = 1; lb < kNumB; ++lb) {   // blocks of B >= 2
-        const int tx = (kSheetCells * kBlock) >> lb;   // cells per strip (kSheetCells per lane)
-        for (int sg = 0; sg < ns; ++sg) cols[sg] = (sheet_host[2 * sg] + tx - 1) / tx;
-        sheet_split(cols, len, h->Gs[p], &b0, &zc);
-        std::copy(zc.begin(), zc.end(), sheet_zc.begin() + ((size_t)p * kNumB + lb) * ns);
-        std::copy(b0.begin(), b0.end(), sheet_blk0.begin() + ((size_t)p * kNumB + lb) * (ns + 1));
+  // the lattice of the march kernels and, per family and block width, their tiles: all
+  // tables in one allocation
+  std::vector<int32_t> sheets;
+  if (h->box[0] == 0 && L.uniform_width == 4) (void)detect_sheets(desc, L.seg_off, &sheets);
+  h->sheet_ok = !sheets.empty() && L.hop_mode == HOP_UNIFORM ? 1 : 0;
+  if (detect_lattice(desc, L, h->box, sheets, &h->lat)) {
+    h->box_msd_ok = h->lat.pattern == MARCH_BOX ? h->lat.dx_ok : 0;
+    std::vector<size_t> at[2];
+    for (int f = 0; f < kMarchFamilies; ++f) {
+      const MarchShape sh = march_shape(h->lat.pattern, h->hop_mode, f);
+      for (int lb = 0; lb < kNumB; ++lb) {
+        MarchPlan mp;
+        size_t o[2] = {0, 0};
+        if (sh.T > 0 && plan_march(h->lat, L.seg_off, sh.T, 1 << lb, h->G, cus, sh.lanes, sh.max_tile_x, &mp)) {
+          Handle::MarchDev& md = h->march[f][lb];
+          md.T = mp.T;
+          md.lanes = mp.lanes;
+          md.items = mp.items;
+          auto put = [&](const void* src, size_t bytes) {
+            const size_t off = round_up(march_host.size(), 16);
+            march_host.resize(off + bytes);
+            std::memcpy(march_host.data() + off, src, bytes);
+            return off;
+          };
+          o[0] = put(mp.segs.data(), mp.segs.size() * sizeof(MarchSeg));
+          o[1] = put(mp.item0.data(), mp.item0.size() * 4);
+        }
+        at[0].push_back(o[0]);
+        at[1].push_back(o[1]);
       }
     }
-    up((void**)&h->d_sheet, sheet_host.data(), sheet_host.size() * 4);
-    up((void**)&h->d_sheet_off, sheet_off.data(), sheet_off.size() * 8);
-    up((void**)&h->d_sheet_zc, sheet_zc.data(), sheet_zc.size() * 4);
-    up((void**)&h->d_sheet_blk0, sheet_blk0.data(), sheet_blk0.size() * 4);
-    h->sheet_ok = ok ? 1 : 0;
+    up((void**)&h->d_march, march_host.data(), march_host.size());
+    if (h->lat.dx_ok) up((void**)&h->d_dxcol, h->lat.dxcol.data(), h->lat.dxcol.size() * 8);
+    if (!h->d_march) h->lat.pattern = MARCH_NONE;
+    for (int f = 0; f < kMarchFamilies && h->d_march; ++f)
+      for (int lb = 0; lb < kNumB; ++lb) {
+        h->march[f][lb].segs = reinterpret_cast<const MarchSeg*>(h->d_march + at[0][f * kNumB + lb]);
+        h->march[f][lb].item0 = reinterpret_cast<const int32_t*>(h->d_march + at[1][f * kNumB + lb]);
+      }
+    h->use_box = 1;
+    h->use_box_msd = h->lat.dx_ok;
   }
   std::vector<double> zeros_g(h->G, 0.0);
   up((void**)&h->d_bound, zeros_g.data(), zeros_g.size() * 8);
@@ -800,8 +1011,7 @@ void gpuqt_destroy_h(gpuqt_h hh) {
   if (!h) return;
   void* ptrs[] = {h->d_slice_ptr, h->d_col, h->d_hop, h->d_dx, h->d_diag, h->d_cls,
                   h->d_plan, h->d_seg_blk0, h->d_seg_dE, h->d_seg_hop, h->d_seg_hop0, h->d_hop0, h->d_bound,
-                  h->d_hidx, h->d_htab, h->d_htab0, h->d_dxtab, h->d_offtab, h->d_sheet, h->d_sheet_zc,
-                  h->d_sheet_off, h->d_sheet_blk0};
+                  h->d_hidx, h->d_htab, h->d_htab0, h->d_dxtab, h->d_offtab, h->d_march, h->d_dxcol};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   for (int32_t* p : h->d_units)
@@ -949,6 +1159,10 @@ gpuqt_status gpuqt_workspace_size(gpuqt_h hh, int32_t op, int32_t B, int32_t M, 
     return GPUQT_OK;
   }
   *bytes = ws_layout(h, nv, B, rows, ldJ).total;
+  if (march_covers(h, op, B) && march_vectors(op) > nv) {
+    const size_t m = ws_layout(h, march_vectors(op), B, rows, ldJ).total;
+    if (m <= kMarchWsMax) *bytes = m;
+  }
   return GPUQT_OK;
 }
 
@@ -968,17 +1182,15 @@ gpuqt_status gpuqt_moments(gpuqt_h hh, int32_t B, const double* phiL, const doub
   if ((st = check_device(h))) return st;
   hipStream_t s = static_cast<hipStream_t>(stream);
   char* base = static_cast<char*>(ws);
-  double2* A = reinterpret_cast<double2*>(base);
-  double2* Bf = reinterpret_cast<double2*>(base + W.vec_bytes);
+  double2* v[4];
+  for (int i = 0; i < 4; ++i) v[i] = reinterpret_cast<double2*>(base + i * W.vec_bytes);
   double2* part = reinterpret_cast<double2*>(base + W.off_part);
-  const bool sym = phiL == phiR;   // Hermitian set: product identities, half the steps
-  if ((st = run_moments(h, B, reinterpret_cast<const double2*>(phiL),
-                        reinterpret_cast<const double2*>(phiR), M, part, A, Bf, s, sym,
-                        sym ? nullptr : reinterpret_cast<double2*>(base + 2 * W.vec_bytes),
-                        sym ? nullptr : reinterpret_cast<double2*>(base + 3 * W.vec_bytes))))
+  const double2* L = reinterpret_cast<const double2*>(phiL);
+  if (phiL == phiR)   // Hermitian set: product identities, half the steps
+    return run_moment_set(h, B, L, false, M, part, v, 4, reinterpret_cast<double2*>(mu), nullptr, s);
+  if ((st = run_moments(h, B, L, reinterpret_cast<const double2*>(phiR), M, part, v[0], v[1], s, false, v[2], v[3])))
     return st;
-  const int fam = sym ? FAM_SYM : FAM_PAIR;
-  HIP_TRY(launch_reduce_moments(part, M, h->G_of(B, fam), B, h->n_seg, h->blk0_of(B, fam), 1,   // raw dots
+  HIP_TRY(launch_reduce_moments(part, M, h->G_of(B, FAM_PAIR), B, h->n_seg, h->blk0_of(B, FAM_PAIR), 1,   // raw dots
                                 reinterpret_cast<double2*>(mu), nullptr, s));
   return GPUQT_OK;
 }
@@ -1036,6 +1248,39 @@ gpuqt_status gpuqt_evolve(gpuqt_h hh, int32_t B, double dt, int32_t Np, const do
   if ((st = check_device(h))) return st;
   char* base = static_cast<char*>(ws);
   auto V = [&](int i) { return reinterpret_cast<double2*>(base + W.vec_bytes * i); };
+  const double2* in = reinterpret_cast<const double2*>(psi_in);
+  const double2* cin = reinterpret_cast<const double2*>(chi_in);
+  double2* out = reinterpret_cast<double2*>(psi_out);
+  double2* cout = reinterpret_cast<double2*>(chi_out);
+  const WsLayout WM = ws_layout(h, march_vectors(op), B, 0, np);
+  if (march_covers(h, op, B) && ws_bytes >= WM.total) {
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    BufPool pool;
+    for (int i = 0; i < march_vectors(op); ++i) pool.free.push_back(reinterpret_cast<double2*>(base + i * WM.vec_bytes));
+    double* J = reinterpret_cast<double*>(base + WM.off_J);
+    std::vector<const double2*> late;
+    // a block's inputs are made planar in buffers the second launch writes, its sums run
+    // planar in the outputs and end in free buffers, from which they go back to [n][B]
+    auto planar = [&](const double2* v, const double2** p) -> gpuqt_status {
+      *p = v;
+      if (B == 1 || !v) return GPUQT_OK;
+      double2* q = pool.take();
+      HIP_TRY(launch_to_planar(h->n, B, v, q, s));
+      late.push_back(q);
+      *p = q;
+      return GPUQT_OK;
+    };
+    const double2 *pa = nullptr, *pb = nullptr;
+    if ((st = planar(in, &pa)) || (st = planar(cin, &pb))) return st;
+    MarchSums su;
+    if ((st = march_evolve(h, B, chi_out ? MF_MSD : MF_EVO, dt, np, pa, pb, out, cout, &pool, late, J, B > 1, &su, s)))
+      return st;
+    if (B > 1) {
+      HIP_TRY(launch_from_planar(h->n, B, su.last[0], out, s));
+      if (cout) HIP_TRY(launch_from_planar(h->n, B, su.last[1], cout, s));
+    }
+    return GPUQT_OK;
+  }
   double* J = reinterpret_cast<double*>(base + W.off_J);
   return run_evolve(h, B, dt, np, reinterpret_cast<const double2*>(psi_in),
                     reinterpret_cast<double2*>(psi_out), reinterpret_cast<const double2*>(chi_in),
@@ -1131,6 +1376,56 @@ static gpuqt_status vac_tape_check(const Handle* h, int B, int n_t, int M, int P
   return GPUQT_OK;
 }
 
+// gpuqt_vac by the marches: every vector planar, ten buffers.  Between rows psi_L and psi_R
+// are alive (psi_L of row 0 may be the caller's phi); a row's moments start from V psi_L, which
+// the second launch may overwrite, and psi_R, which it may not; the evolution to the next
+// row may overwrite both states once its first launch has read them.
+static gpuqt_status vac_march(const Handle* h, int32_t B, const double2* phi, int32_t n_t, const double* dt, int32_t M,
+                              int32_t Np, double* out, char* base, const WsLayout& W, hipStream_t s) {
+  gpuqt_status st;
+  BufPool pool;
+  for (int i = 0; i < march_vectors(GPUQT_OP_VAC); ++i)
+    pool.free.push_back(reinterpret_cast<double2*>(base + i * W.vec_bytes));
+  double2* part = reinterpret_cast<double2*>(base + W.off_part);
+  double* J = reinterpret_cast<double*>(base + W.off_J);
+  const Handle::MarchDev& mp = h->march[MF_PAIR][Handle::log2B(B)];
+  const double2* psiL = phi;
+  bool own_L = false;   // psi_L is a buffer of the pool
+  if (B > 1) {
+    double2* p = pool.take();
+    HIP_TRY(launch_to_planar(h->n, B, phi, p, s));
+    psiL = p;
+    own_L = true;
+  }
+  double2* psiR = pool.take();
+  if ((st = march_velocity(h, B, psiL, psiR, s))) return st;
+  const int64_t row = (int64_t)h->n_seg * B * M;
+  for (int k = 0; k < n_t; ++k) {
+    {
+      double2* phiL = pool.take();
+      if ((st = march_velocity(h, B, psiL, phiL, s))) return st;
+      BufPool q = pool;   // every buffer is free again once the row is done
+      if ((st = run_march(h, B, MF_PAIR, pair_steps(M), phiL, psiR, &q, {phiL}, part, nullptr, s))) return st;
+      HIP_TRY(launch_reduce_moments(part, M, mp.items, B, h->n_seg, mp.item0, 1, nullptr, out + row * k, s));
+      pool.give(phiL);
+    }
+    if (k + 1 < n_t) {
+      const int np = terms_for(h, dt[k], Np);
+      double2 *Ln = pool.take(), *Rn = pool.take();
+      std::vector<const double2*> late = {psiR};
+      if (own_L) late.push_back(psiL);
+      BufPool q = pool;
+      MarchSums su;
+      if ((st = march_evolve(h, B, MF_EVO2, -dt[k], np, psiL, psiR, Ln, Rn, &q, late, J, false, &su, s))) return st;
+      for (const double2* p : late) pool.give(p);
+      psiL = Ln;
+      psiR = Rn;
+      own_L = true;
+    }
+  }
+  return GPUQT_OK;
+}
+
 static gpuqt_status vac_impl(const Handle* h, int32_t B, const double* phi, int32_t n_t, const double* dt, int32_t M,
                       int32_t Np, double* out, void* ws, size_t ws_bytes, void* tape, size_t tape_bytes,
                       void* stream) {
@@ -1149,6 +1444,10 @@ static gpuqt_status vac_impl(const Handle* h, int32_t B, const double* phi, int3
   auto V = [&](int i) { return reinterpret_cast<double2*>(base + W.vec_bytes * i); };
   double2* part = reinterpret_cast<double2*>(base + W.off_part);
   double* J = reinterpret_cast<double*>(base + W.off_J);
+  const WsLayout WM = ws_layout(h, march_vectors(GPUQT_OP_VAC), B, moment_rows(M), np);
+  const bool marched = march_covers(h, GPUQT_OP_VAC, B) && ws_bytes >= WM.total;
+  if (marched && !tape)
+    return vac_march(h, B, reinterpret_cast<const double2*>(phi), n_t, dt, M, Np, out, base, WM, s);
   const DevMat D = h->view(B);
   // psi_L = phi (input, read only), psi_R = V phi
   const double2* psiL = reinterpret_cast<const double2*>(phi);
@@ -1163,21 +1462,33 @@ static gpuqt_status vac_impl(const Handle* h, int32_t B, const double* phi, int3
     HIP_TRY(launch_commutator(D, h->hop_mode, B, GPUQT_VELOCITY, psiL, phiL, s));
     if (tape) {
       const std::vector<double2*> keep = T.chains(k);
-      if ((st = run_moments(h, B, phiL, psiR, M, part, nullptr, nullptr, s, false, nullptr, nullptr,
-                            keep.data())))
+      if (marched) {   // the same marches as gpuqt_vac, with every step stored
+        const Handle::MarchDev& mp = h->march[MF_PAIR][Handle::log2B(B)];
+        if ((st = run_march(h, B, MF_PAIR, pair_steps(M), phiL, psiR, nullptr, {}, part, nullptr, s, keep.data())))
+          return st;
+        HIP_TRY(launch_reduce_moments(part, M, mp.items, B, h->n_seg, mp.item0, 1, nullptr, out + row * k, s));
+      } else if ((st = run_moments(h, B, phiL, psiR, M, part, nullptr, nullptr, s, false, nullptr, nullptr,
+                                   keep.data()))) {
         return st;
+      }
     } else if ((st = run_moments(h, B, phiL, psiR, M, part, V(5), V(6), s, false, V(7), V(8)))) {
       return st;
     }
-    HIP_TRY(launch_reduce_moments(part, M, h->G_of(B, FAM_PAIR), B, h->n_seg, h->blk0_of(B, FAM_PAIR), 1,
-                                  nullptr, out + row * k, s));
+    if (!marched)
+      HIP_TRY(launch_reduce_moments(part, M, h->G_of(B, FAM_PAIR), B, h->n_seg, h->blk0_of(B, FAM_PAIR), 1,
+                                    nullptr, out + row * k, s));
     if (k + 1 < n_t) {
       const int np_k = terms_for(h, dt[k], Np);
       double2* Ln = tape ? T.psiL(k + 1) : (psiL == Lbuf[0]) ? Lbuf[1] : Lbuf[0];
       double2* Rn = tape ? T.psiR(k + 1) : Rbuf[ri ^ 1];
       // both states advance with the same U(-dt): one two-chain series
       const std::vector<double2*> ev = tape ? T.evolution(k, np_k) : std::vector<double2*>();
-      if ((st = run_evolve_pair(h, B, -dt[k], np_k, psiL, Ln, psiR, Rn, V(5), V(6), V(7), V(8), J, s,
+      if (marched) {
+        MarchSums su;
+        if ((st = march_evolve(h, B, MF_EVO2, -dt[k], np_k, psiL, psiR, Ln, Rn, nullptr, {}, J, false, &su, s,
+                               ev.data())))
+          return st;
+      } else if ((st = run_evolve_pair(h, B, -dt[k], np_k, psiL, Ln, psiR, Rn, V(5), V(6), V(7), V(8), J, s,
                                 tape ? ev.data() : nullptr)))
         return st;
       psiL = Ln;
@@ -1230,6 +1541,42 @@ gpuqt_status gpuqt_msd(gpuqt_h hh, int32_t B, const double* phi, int32_t n_t, co
   auto V = [&](int i) { return reinterpret_cast<double2*>(base + W.vec_bytes * i); };
   double2* part = reinterpret_cast<double2*>(base + W.off_part);
   double* J = reinterpret_cast<double*>(base + W.off_J);
+  const WsLayout WM = ws_layout(h, march_vectors(GPUQT_OP_MSD), B, moment_rows(M), np);
+  if (march_covers(h, GPUQT_OP_MSD, B) && ws_bytes >= WM.total) {
+    // by the marches: every vector planar; psi of row 0 may be the caller's phi, chi is
+    // zero there, and both may be overwritten once a step's first launch has read them
+    BufPool pool;
+    for (int i = 0; i < march_vectors(GPUQT_OP_MSD); ++i)
+      pool.free.push_back(reinterpret_cast<double2*>(base + i * WM.vec_bytes));
+    double2* part = reinterpret_cast<double2*>(base + WM.off_part);
+    double* J = reinterpret_cast<double*>(base + WM.off_J);
+    const double2 *psi = reinterpret_cast<const double2*>(phi), *chi = nullptr;
+    bool own = false;
+    if (B > 1) {
+      double2* p = pool.take();
+      HIP_TRY(launch_to_planar(h->n, B, psi, p, s));
+      psi = p;
+      own = true;
+    }
+    for (int k = 0; k < n_t; ++k) {
+      double2 *Pn = pool.take(), *Cn = pool.take();
+      std::vector<const double2*> late;
+      if (own) late.push_back(psi);
+      if (chi) late.push_back(chi);
+      BufPool q = pool;   // every buffer is free again once the step is done
+      MarchSums su;
+      if ((st = march_evolve(h, B, MF_MSD, dt[k], terms_for(h, dt[k], Np), psi, chi, Pn, Cn, &q, late, J, false, &su, s)))
+        return st;
+      for (const double2* p : late) pool.give(p);
+      psi = Pn;
+      chi = Cn;
+      own = true;
+      if ((st = run_moment_set(h, B, chi, true, M, part, pool.free.data(), (int)pool.free.size(), nullptr,
+                               out + (int64_t)h->n_seg * B * M * k, s)))
+        return st;
+    }
+    return GPUQT_OK;
+  }
   double2* Pbuf[2] = {V(0), V(1)};
   double2* Cbuf[2] = {V(2), V(3)};
   const double2* psi = reinterpret_cast<const double2*>(phi);
@@ -1242,9 +1589,8 @@ gpuqt_status gpuqt_msd(gpuqt_h hh, int32_t B, const double* phi, int32_t n_t, co
     double2* Cn = Cbuf[pi];
     if ((st = run_evolve(h, B, dt[k], np_k, psi, Pn, chi, Cn, V(4), V(5), V(6), V(7), V(8), J, s)))
       return st;
-    if ((st = run_moments(h, B, Cn, Cn, M, part, V(4), V(5), s, true))) return st;
-    HIP_TRY(launch_reduce_moments(part, M, h->G_of(B, FAM_SYM), B, h->n_seg, h->blk0_of(B, FAM_SYM), 1,
-                                  nullptr, out + row * k, s));
+    double2* const four[4] = {V(4), V(5), V(6), V(7)};
+    if ((st = run_moment_set(h, B, Cn, false, M, part, four, 4, nullptr, out + row * k, s))) return st;
     psi = Pn;
     chi = Cn;
     pi ^= 1;
@@ -1657,36 +2003,35 @@ gpuqt_status gpuqt_autotune(gpuqt_h hh, int32_t B, void* ws, size_t ws_bytes, vo
   h->banded = (best_v >> 1) & 1;
   h->pencil = (best_v >> 2) & 1;
   h->per_cu_cap = best_cap;
-  // on a periodic box (or segments that are all periodic squares: the sheet form), the
-  // stencil kernel of the Hermitian step, uncapped and at
-  // caps 1..6 (its loads run a plane ahead, so a few workgroups per CU fill HBM, and
-  // fewer concurrent streams use the DRAM pages and the L2 better); when it beats the
-  // best general variant it is kept, with its cap as the Hermitian family's own
-  if (!st && (h->box[0] > 0 || h->sheet_ok) && B >= 2 && h->hop_mode == HOP_UNIFORM) {
+  // on a lattice with a march, the Hermitian step's march (per step; the last launch may
+  // compute a few steps more than the moments need); kept when it beats the best general
+  // variant, and when the workspace has no room to time it
+  const WsLayout WF = ws_layout(h, kTuneVectors, B, kSteps + 1, kTuneNp);
+  const int K = pair_steps(kSteps + 1);
+  if (!st && h->lat.pattern != MARCH_NONE) {
     h->use_box = 1;
-    float bbest = 0.0f;
-    int bcap = 0;
-    for (int cap : {0, 1, 2, 3, 4, 5, 6}) {
-      h->fam_cap[FAM_SYM] = (int8_t)cap;
+    const int T = h->march[MF_SYM][lb].T;
+    if (T > 0 && ws_bytes >= WF.total) {
+      double2* v[4];
+      for (int i = 0; i < 4; ++i) v[i] = reinterpret_cast<double2*>(base + (i + 1) * WF.vec_bytes);
+      double2* partF = reinterpret_cast<double2*>(base + WF.off_part);
       float mb = 0.0f;
-      if ((st = time_run([&] { return run_moments(h, B, phi, phi, kSteps + 1, part, A, Bf, s, true); }, &mb)))
-        break;
-      if (bbest == 0.0f || mb < bbest) {
-        bbest = mb;
-        bcap = cap;
-      }
-    }
-    if (times_us && !st) times_us[kTuneTimes - 1] = 1e3 * bbest / (kSteps / 2);
-    if (!st && bbest < best) {
-      h->fam_cap[FAM_SYM] = (int8_t)bcap;
-    } else {
-      h->use_box = 0;
-      h->fam_cap[FAM_SYM] = -1;
+      st = time_run(
+          [&]() -> gpuqt_status {
+            BufPool pool;
+            for (double2* p : v) pool.free.push_back(p);
+            return run_march(h, B, MF_SYM, K, phi, nullptr, &pool, {}, partF, nullptr, s);
+          },
+          &mb);
+      const double per = (double)mb / ((K + T - 1) / T * T);
+      if (times_us && !st) times_us[kTuneTimes - 1] = 1e3 * per;
+      if (st || per >= (double)best / K) h->use_box = 0;
     }
   }
+  const int march_sym = h->use_box;
+  h->use_box = 0;   // the general kernels' caps below
   // with room for their vectors, each of the two-chain moment, two-vector
   // evolution and MSD families also gets its own cap at this load variant
-  const WsLayout WF = ws_layout(h, kTuneVectors, B, kSteps + 1, kTuneNp);
   if (!st && ws_bytes >= WF.total) {
     double2* v[kTuneVectors];
     for (int i = 0; i < kTuneVectors; ++i) v[i] = reinterpret_cast<double2*>(base + i * WF.vec_bytes);
@@ -1724,14 +2069,13 @@ gpuqt_status gpuqt_autotune(gpuqt_h hh, int32_t B, void* ws, size_t ws_bytes, vo
     st = tune_family(FAM_PAIR, &t_pair);
     // the series families (two-vector evolution and MSD terms) with the handle's
     // load variant and with the other one; the pair of caps of the faster total stays
-    float tot[2] = {0.0f, 0.0f}, tmsd[2] = {0.0f, 0.0f};
+    float tot[2] = {0.0f, 0.0f};
     int8_t cap_ev[2] = {-1, -1}, cap_msd[2] = {-1, -1};
     for (int flip = 0; flip < 2 && !st; ++flip) {
       h->series_nt_flip = flip;
       float te = 0.0f, tm = 0.0f;
       if ((st = tune_family(FAM_EVOLVE_PAIR, &te)) || (st = tune_family(FAM_MSD, &tm))) break;
       tot[flip] = te + tm;
-      tmsd[flip] = tm;
       cap_ev[flip] = h->fam_cap[FAM_EVOLVE_PAIR];
       cap_msd[flip] = h->fam_cap[FAM_MSD];
     }
@@ -1740,35 +2084,15 @@ gpuqt_status gpuqt_autotune(gpuqt_h hh, int32_t B, void* ws, size_t ws_bytes, vo
       h->series_nt_flip = fl;
       h->fam_cap[FAM_EVOLVE_PAIR] = cap_ev[fl];
       h->fam_cap[FAM_MSD] = cap_msd[fl];
-      // on a periodic box with uniform x steps, the MSD term's box stencil kernel,
-      // uncapped and at caps 1..6, kept (with its cap) when faster
-      if (h->box_msd_ok && B >= 2 && h->hop_mode == HOP_UNIFORM) {
-        h->use_box_msd = 1;
-        float bbest = 0.0f;
-        int bcap = 0;
-        for (int cap : {0, 1, 2, 3, 4, 5, 6}) {
-          h->fam_cap[FAM_MSD] = (int8_t)cap;
-          float mb = 0.0f;
-          if ((st = time_run([&] { return run_family(FAM_MSD); }, &mb))) break;
-          if (bbest == 0.0f || mb < bbest) {
-            bbest = mb;
-            bcap = cap;
-          }
-        }
-        if (!st && bbest < tmsd[fl]) {
-          h->fam_cap[FAM_MSD] = (int8_t)bcap;
-        } else {
-          h->use_box_msd = 0;
-          h->fam_cap[FAM_MSD] = cap_msd[fl];
-        }
-      }
     }
   }
+  h->use_box = march_sym;
+  h->use_box_msd = march_sym ? h->lat.dx_ok : 0;
   if (st) {
     for (int f = 0; f < kFamilies; ++f) h->fam_cap[f] = -1;
     h->series_nt_flip = 0;
-    h->use_box = 0;
-    h->use_box_msd = 0;
+    h->use_box = h->lat.pattern != MARCH_NONE;
+    h->use_box_msd = h->lat.dx_ok;
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
@@ -1839,7 +2163,7 @@ gpuqt_status gpuqt_set_variant(gpuqt_h hh, int32_t variant) {
     return fail(GPUQT_ERR_ARG,
                 "variant must be bits 0-1 load variant, bits 2-5 a per-CU cap of 0..8, bit 6 the pencil "
                 "order (with bit 1), bit 7 the series families' load flip, 3 bits per kernel family "
-                "from bit 8, bit 26 the periodic-box Hermitian step and bit 27 the periodic-box MSD term");
+                "from bit 8, bit 26 the lattice marches and bit 27 the MSD term's march");
   h->nt = variant & 1;
   h->banded = (variant >> 1) & 1;
   h->pencil = (variant >> 6) & 1;

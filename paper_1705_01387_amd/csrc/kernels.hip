@@ -137,386 +137,6 @@ __global__ __launch_bounds__(kBlock) void k_moment_step_sym(DevMat A, StepIO io,
 }
 
 // ---------------------------------------------------------------------------
-// The Hermitian moment step of k_moment_step_sym on a periodic box (every row
-// x + Lx (y + Ly z) with the six neighbours one step away in x, y and z, one
-// uniform hopping; detect_box), for blocks of B >= 2 vectors.  The gathers of
-// the general kernel fetch every element of x through the L1 five times per
-// step (as the row's own element and as the neighbour one line and one plane
-// away on either side).  Here a workgroup owns a TX x TY column of the box and
-// a run of zc planes and marches through them: each lane keeps its elements of
-// planes z - 1, z and z + 1 in registers (the z neighbours), plane z of the
-// tile and its one-row halo go to LDS (the x and y neighbours), so x is read
-// about (1 + halo) times instead of five, and the neighbour indices are not
-// read at all.  Everything plane z + 1 needs (x of plane z + 2, the halo of
-// z + 1, w and the diagonal) is loaded while plane z is computed; one barrier
-// per plane (double-buffered LDS).  Addresses are a plane base, uniform over
-// the workgroup, plus a 32-bit byte offset per lane that is fixed for the run
-// (a plane of the block must span less than 4 GiB; box_fits).  Positions of a
-// tile past the box edge hold the wrapped rows (so the edge rows' periodic
-// neighbours are in place) and produce no output.  Work items (column, run of
-// planes) go round the G workgroups, each writing one partial like the
-// general kernel; the column index runs fastest, so the workgroups of one XCD
-// (consecutive logical blocks) hold a band of neighbouring columns at the same
-// run and march through z together, and the halo rows they read from each
-// other are hits in that XCD's L2.
-// ---------------------------------------------------------------------------
-
-// Which elements of a TX x TY box tile (plus its one-cell halo without the
-// corners) this thread handles, their LDS slots, and per work item their byte
-// offsets inside a plane of a block of B vectors and of the diagonal.
-template <int B, int TX, int TY>
-struct BoxTile {
-  static constexpr int PX = TX + 2, PY = TY + 2, PE = PX * PY * B;   // staged elements per plane
-  static constexpr int OE = TX * TY * B;                              // own elements per plane
-  static_assert(OE % kBlock == 0, "a tile plane must give every thread the same count");
-  static constexpr int OPT = OE / kBlock;
-  static constexpr int HE = (2 * TX + 2 * TY) * B;                    // halo elements
-  static constexpr int HPT = (HE + kBlock - 1) / kBlock;
-  // hval: the lane's halo element exists (HE is not always a multiple of kBlock); the
-  // other lanes load the element of lane e mod HE instead and do not stage it, so that
-  // every lane issues the same loads (a load under a lane test would make the compiler
-  // wait for all loads in flight, prefetches included, where the branches join)
-  int oslot[OPT], olx[OPT], oly[OPT], hslot[HPT], hpx[HPT], hpy[HPT];
-  bool hval[HPT], oval[OPT];
-  uint32_t oo[OPT], od[OPT], ho[HPT];   // own element, own diagonal, halo element
-
-  __device__ __forceinline__ explicit BoxTile(int b) {
-#pragma unroll
-    for (int i = 0; i < OPT; ++i) {
-      const int p = (threadIdx.x + i * kBlock) / B;
-      olx[i] = p % TX;
-      oly[i] = p / TX;
-      oslot[i] = ((oly[i] + 1) * PX + olx[i] + 1) * B + b;
-    }
-#pragma unroll
-    for (int j = 0; j < HPT; ++j) {
-      const int e = threadIdx.x + j * kBlock;
-      const int q = (e % HE) / B;
-      hval[j] = e < HE;
-      int px = 0, py = 0;
-      if (q < TX) {
-        px = q + 1;
-      } else if (q < 2 * TX) {
-        px = q - TX + 1;
-        py = PY - 1;
-      } else if (q < 2 * TX + TY) {
-        py = q - 2 * TX + 1;
-      } else {
-        px = PX - 1;
-        py = q - 2 * TX - TY + 1;
-      }
-      hpx[j] = px;
-      hpy[j] = py;
-      hslot[j] = (py * PX + px) * B + b;
-    }
-  }
-
-  // the tile whose first cell is (x0, y0)
-  __device__ __forceinline__ void place(int x0, int y0, int Lx, int Ly, int b) {
-    auto wrap = [](int v, int L) { return ((v % L) + L) % L; };
-#pragma unroll
-    for (int i = 0; i < OPT; ++i) {
-      const int X = x0 + olx[i], Y = y0 + oly[i];
-      oval[i] = X < Lx && Y < Ly;
-      const uint32_t row = (uint32_t)wrap(Y, Ly) * (uint32_t)Lx + (uint32_t)wrap(X, Lx);
-      oo[i] = (row * B + b) * (uint32_t)sizeof(double2);
-      od[i] = row * (uint32_t)sizeof(double);
-    }
-#pragma unroll
-    for (int j = 0; j < HPT; ++j) {
-      const uint32_t row = (uint32_t)wrap(y0 + hpy[j] - 1, Ly) * (uint32_t)Lx + (uint32_t)wrap(x0 + hpx[j] - 1, Lx);
-      ho[j] = (row * B + b) * (uint32_t)sizeof(double2);
-    }
-  }
-};
-
-// The streams a box kernel reads or writes once per step (everything but the
-// staged chains) carry the non-temporal hint, so that they do not push the
-// staged planes, which neighbouring tiles read again as halo, out of the L2
-// (cubic 200^3: the B = 4 Hermitian step 318 -> 308 us, the MSD term
-// 1080 -> 1036 us, B = 16 1288 -> 1217 us).
-constexpr bool kBoxNtLoad = true, kBoxNtStore = true;
-
-template <bool NT = false>
-__device__ __forceinline__ double2 box_ld(const char* base, uint32_t off) {
-  return ld2<NT>(reinterpret_cast<const double2*>(base + off));
-}
-__device__ __forceinline__ void box_st(char* base, uint32_t off, double2 v) {
-  if constexpr (kBoxNtStore) {
-    const d2v t = {v.x, v.y};
-    __builtin_nontemporal_store(t, reinterpret_cast<d2v*>(base + off));
-  } else {
-    *reinterpret_cast<double2*>(base + off) = v;
-  }
-}
-__device__ __forceinline__ double box_ldd(const char* base, uint32_t off) {
-  if constexpr (kBoxNtLoad) return __builtin_nontemporal_load(reinterpret_cast<const double*>(base + off));
-  return *reinterpret_cast<const double*>(base + off);
-}
-
-template <int B, int TX, int TY, bool FIRST>
-__global__ __launch_bounds__(kBlock) void k_moment_step_sym_box(DevMat A, StepIO io, int zc,
-                                                                double2* __restrict__ part_a,
-                                                                double2* __restrict__ part_b,
-                                                                double2* __restrict__ part_c) {
-  using T = BoxTile<B, TX, TY>;
-  constexpr int OPT = T::OPT, HPT = T::HPT, PX = T::PX;
-  __shared__ double2 lds[2][T::PE];
-  const int lb = logical_block(A.G);
-  const int Lx = A.box[0], Ly = A.box[1], Lz = A.box[2];
-  const int txn = (Lx + TX - 1) / TX, tyn = (Ly + TY - 1) / TY, zn = (Lz + zc - 1) / zc;
-  const int64_t cols = (int64_t)txn * tyn, items = cols * zn;
-  const double hu = A.seg_hop[0];
-  const int b = threadIdx.x & (B - 1);
-  const char* xs = reinterpret_cast<const char*>(io.x);
-  const char* ws = reinterpret_cast<const char*>(io.w);   // not read on the first step
-  char* os = reinterpret_cast<char*>(io.out);
-  const char* ds = reinterpret_cast<const char*>(A.diag);
-  const int64_t vplane = (int64_t)Lx * Ly * B * (int64_t)sizeof(double2);
-  const int64_t dplane = (int64_t)Lx * Ly * (int64_t)sizeof(double);
-  auto zw = [Lz](int z) { return z < 0 ? z + Lz : (z >= Lz ? z - Lz : z); };   // z in [-1, Lz + 1]
-  T t(b);
-  // first: a = <v0|v0>, b = <v0|v1>, c = <v1|v1>;  else: a = <vk|vk-1>, c = <vk|vk>
-  double ar = 0.0, ai = 0.0, br = 0.0, bi = 0.0, cr = 0.0, ci = 0.0;
-  for (int64_t it = lb; it < items; it += A.G) {
-    const int tz = (int)(it / cols);
-    const int64_t txy = it % cols;
-    const int z0 = tz * zc, z1 = min(z0 + zc, Lz);
-    t.place((int)(txy % txn) * TX, (int)(txy / txn) * TY, Lx, Ly, b);
-    // x of planes z - 1, z, z + 1 and the one loaded for z + 2 rotate through x0..x3; w,
-    // the diagonal and the halo of planes z and z + 1 through (w0, w1), (d0, d1), (h0, h1).
-    // The loop below is unrolled four planes deep so that the rotation is a renaming: a
-    // register copy of a load in flight would wait for it.
-    double2 x0[OPT], x1[OPT], x2[OPT], x3[OPT], w0[OPT], w1[OPT], h0[HPT], h1[HPT];
-    double d0[OPT], d1[OPT];
-    {
-      const char* xa = xs + zw(z0 - 1) * vplane;
-      const char* xb = xs + z0 * vplane;
-      const char* xd = xs + zw(z0 + 1) * vplane;
-#pragma unroll
-      for (int i = 0; i < OPT; ++i) {
-        x0[i] = box_ld(xa, t.oo[i]);
-        x1[i] = box_ld(xb, t.oo[i]);
-        x2[i] = box_ld(xd, t.oo[i]);
-        w0[i] = FIRST ? make_double2(0.0, 0.0) : box_ld<kBoxNtLoad>(ws + z0 * vplane, t.oo[i]);
-        d0[i] = box_ldd(ds + z0 * dplane, t.od[i]);
-      }
-#pragma unroll
-      for (int j = 0; j < HPT; ++j) h0[j] = box_ld(xb, t.ho[j]);
-    }
-    // plane z, staged in LDS buffer BF: first the loads for plane z + 1 (on the last plane
-    // of the run they read the planes after it, wrapped into the box, and go unused: the
-    // same loads on every plane keep the wait for plane z's operands from waiting for
-    // these too), then the stencil
-    auto plane = [&](int z, auto BF, double2(&xm)[OPT], double2(&xc)[OPT], double2(&xp)[OPT],
-                     double2(&xq)[OPT], double2(&wc)[OPT], double2(&wn)[OPT], double(&dc)[OPT],
-                     double(&dn)[OPT], double2(&hc)[HPT], double2(&hn)[HPT]) {
-      constexpr int bf = decltype(BF)::value;
-      const int z1n = zw(z + 1);
-      const char* xq_ = xs + zw(z + 2) * vplane;
-      const char* xn_ = xs + z1n * vplane;
-#pragma unroll
-      for (int i = 0; i < OPT; ++i) {
-        xq[i] = box_ld(xq_, t.oo[i]);
-        if (!FIRST) wn[i] = box_ld<kBoxNtLoad>(ws + z1n * vplane, t.oo[i]);
-        dn[i] = box_ldd(ds + z1n * dplane, t.od[i]);
-      }
-#pragma unroll
-      for (int j = 0; j < HPT; ++j) hn[j] = box_ld(xn_, t.ho[j]);
-#pragma unroll
-      for (int i = 0; i < OPT; ++i) lds[bf][t.oslot[i]] = xc[i];
-#pragma unroll
-      for (int j = 0; j < HPT; ++j)
-        if (t.hval[j]) lds[bf][t.hslot[j]] = hc[j];
-      __syncthreads();
-      char* oz = os + z * vplane;
-#pragma unroll
-      for (int i = 0; i < OPT; ++i) {
-        if (t.oval[i]) {
-          const int c = t.oslot[i];
-          double2 sn = cadd(lds[bf][c + B], lds[bf][c - B]);
-          sn = cadd(sn, lds[bf][c + PX * B]);
-          sn = cadd(sn, lds[bf][c - PX * B]);
-          sn = cadd(sn, xp[i]);
-          sn = cadd(sn, xm[i]);
-          const double2 xr = xc[i];
-          const double2 h = make_double2(fma(dc[i], xr.x, hu * sn.x), fma(dc[i], xr.y, hu * sn.y));
-          const double2 y = FIRST ? h : twice_minus(h, wc[i]);
-          box_st(oz, t.oo[i], y);
-          if (FIRST) {
-            cdot_acc(ar, ai, xr, xr);
-            cdot_acc(br, bi, xr, y);
-          } else {
-            cdot_acc(ar, ai, y, xr);
-          }
-          cdot_acc(cr, ci, y, y);
-        }
-      }
-    };
-    using S0 = std::integral_constant<int, 0>;
-    using S1 = std::integral_constant<int, 1>;
-    for (int z = z0; z < z1; z += 4) {
-      plane(z, S0{}, x0, x1, x2, x3, w0, w1, d0, d1, h0, h1);
-      if (z + 1 >= z1) break;
-      plane(z + 1, S1{}, x1, x2, x3, x0, w1, w0, d1, d0, h1, h0);
-      if (z + 2 >= z1) break;
-      plane(z + 2, S0{}, x2, x3, x0, x1, w0, w1, d0, d1, h0, h1);
-      if (z + 3 >= z1) break;
-      plane(z + 3, S1{}, x3, x0, x1, x2, w1, w0, d1, d0, h1, h0);
-    }
-    __syncthreads();   // the next item stages into buffer 0 again
-  }
-  block_reduce_store<B>(ar, ai, part_a + (int64_t)lb * B);
-  __syncthreads();
-  block_reduce_store<B>(cr, ci, part_c + (int64_t)lb * B);
-  if (FIRST) {
-    __syncthreads();
-    block_reduce_store<B>(br, bi, part_b + (int64_t)lb * B);
-  }
-}
-
-// ---------------------------------------------------------------------------
-// The Hermitian step of k_moment_step_sym on segments that are each a periodic
-// Lx x Ly square (rows off_s + x + Lx y, four neighbours, one uniform hopping per
-// segment; detect_sheets), for blocks of B >= 2 vectors: the two-dimensional form
-// of k_moment_step_sym_box.  A workgroup holds a strip of TX = 256 / B cells of one
-// row (a lane per cell and vector) and marches along y: rows y - 1, y and y + 1 of
-// the strip stay in registers (the y neighbours), row y and its two halo cells go
-// to LDS (the x neighbours).  The workgroups of segment s (sheet_blk0: the plan's
-// workgroups split over the segments by their work, so that the segments finish
-// together) take its work items (strip, run of sheet_zc rows), strip index
-// fastest, so the workgroups of
-// one XCD hold neighbouring strips of the same rows.  Loads for row y + 1 are
-// issued unconditionally while row y is computed and the march is unrolled four
-// rows deep, as in the box kernel.
-// ---------------------------------------------------------------------------
-template <int B, int OPT, bool FIRST>
-__global__ __launch_bounds__(kBlock) void k_moment_step_sym_sheet(DevMat A, StepIO io,
-                                                                  double2* __restrict__ part_a,
-                                                                  double2* __restrict__ part_b,
-                                                                  double2* __restrict__ part_c) {
-  constexpr int TL = kBlock / B;               // cells per lane row of the strip
-  constexpr int TX = OPT * TL, PX = TX + 2;    // cells per strip: OPT per lane
-  __shared__ double2 lds[2][PX * B];
-  const int lb = logical_block(A.G);
-  // this workgroup's segment in the kernel's own split (sheet_blk0: by work, not rows)
-  int sg = 0;
-  for (int hi = A.sheet_nseg - 1; sg < hi;) {
-    const int mid = (sg + hi + 1) >> 1;
-    if (A.sheet_blk0[mid] <= lb) sg = mid;
-    else hi = mid - 1;
-  }
-  const int Lx = A.sheet[2 * sg], Ly = A.sheet[2 * sg + 1];
-  const int zc = A.sheet_zc[sg];
-  const int w0 = A.sheet_blk0[sg], nw = A.sheet_blk0[sg + 1] - w0;
-  const int64_t off = A.sheet_off[sg];
-  const int cols = (Lx + TX - 1) / TX, zn = (Ly + zc - 1) / zc;
-  const int64_t items = (int64_t)cols * zn;
-  const double hu = A.seg_hop[sg];
-  const int b = threadIdx.x & (B - 1);
-  const int cx = threadIdx.x / B;                       // first cell of this lane in the strip
-  const char* xs = reinterpret_cast<const char*>(io.x + off * B);
-  const char* ws = reinterpret_cast<const char*>((FIRST ? io.x : io.w) + off * B);   // not read when FIRST
-  char* os = reinterpret_cast<char*>(io.out + off * B);
-  const char* ds = reinterpret_cast<const char*>(A.diag + off);
-  const int64_t vrow = (int64_t)Lx * B * (int64_t)sizeof(double2), drow = (int64_t)Lx * (int64_t)sizeof(double);
-  auto zw = [Ly](int y) { return y < 0 ? y + Ly : (y >= Ly ? y - Ly : y); };   // y in [-1, Ly + 1]
-  auto wrap = [](int v, int L) { return ((v % L) + L) % L; };
-  // halo: lanes 0 .. B - 1 stage the cell left of the strip, B .. 2B - 1 the one right of
-  // it; the other lanes load lane (threadIdx.x mod 2B)'s element and do not stage it
-  const bool hval = threadIdx.x < 2 * B;
-  const bool hright = (threadIdx.x % (2 * B)) >= B;
-  const int hslot = (hright ? PX - 1 : 0) * B + b;
-  double ar = 0.0, ai = 0.0, br = 0.0, bi = 0.0, cr = 0.0, ci = 0.0;
-  for (int64_t it = lb - w0; it < items; it += nw) {
-    const int tz = (int)(it / cols), strip = (int)(it % cols);
-    const int x0 = strip * TX;
-    const int y0 = tz * zc, y1 = min(y0 + zc, Ly);
-    bool oval[OPT];
-    uint32_t oo[OPT], od[OPT];
-#pragma unroll
-    for (int i = 0; i < OPT; ++i) {
-      const int X = x0 + cx + i * TL;
-      oval[i] = X < Lx;
-      const uint32_t xo = (uint32_t)wrap(X, Lx);
-      oo[i] = (xo * B + b) * (uint32_t)sizeof(double2);
-      od[i] = xo * (uint32_t)sizeof(double);
-    }
-    const uint32_t ho = ((uint32_t)wrap(hright ? x0 + TX : x0 - 1, Lx) * B + b) * (uint32_t)sizeof(double2);
-    // x of rows y - 1, y, y + 1 and the one loaded for y + 2 rotate through q0..q3; w, the
-    // diagonal and the halo of rows y and y + 1 through pairs (unrolled four rows deep)
-    double2 q0[OPT], q1[OPT], q2[OPT], q3[OPT], wa[OPT], wb[OPT], h0, h1;
-    double d0[OPT], d1[OPT];
-#pragma unroll
-    for (int i = 0; i < OPT; ++i) {
-      q0[i] = box_ld(xs + zw(y0 - 1) * vrow, oo[i]);
-      q1[i] = box_ld(xs + y0 * vrow, oo[i]);
-      q2[i] = box_ld(xs + zw(y0 + 1) * vrow, oo[i]);
-      wa[i] = FIRST ? make_double2(0.0, 0.0) : box_ld<kBoxNtLoad>(ws + y0 * vrow, oo[i]);
-      wb[i] = make_double2(0.0, 0.0);
-      d0[i] = box_ldd(ds + y0 * drow, od[i]);
-    }
-    h0 = box_ld(xs + y0 * vrow, ho);
-    auto row = [&](int y, auto BF, double2(&xm)[OPT], double2(&xc)[OPT], double2(&xp)[OPT], double2(&xq)[OPT],
-                   double2(&wc)[OPT], double2(&wn)[OPT], double(&dc)[OPT], double(&dn)[OPT], double2& hc,
-                   double2& hn) {
-      constexpr int bf = decltype(BF)::value;
-      const int y1n = zw(y + 1);
-#pragma unroll
-      for (int i = 0; i < OPT; ++i) {
-        xq[i] = box_ld(xs + zw(y + 2) * vrow, oo[i]);
-        if (!FIRST) wn[i] = box_ld<kBoxNtLoad>(ws + y1n * vrow, oo[i]);
-        dn[i] = box_ldd(ds + y1n * drow, od[i]);
-      }
-      hn = box_ld(xs + y1n * vrow, ho);
-#pragma unroll
-      for (int i = 0; i < OPT; ++i) lds[bf][(cx + i * TL + 1) * B + b] = xc[i];
-      if (hval) lds[bf][hslot] = hc;
-      __syncthreads();
-#pragma unroll
-      for (int i = 0; i < OPT; ++i) {
-        if (oval[i]) {
-          const int c = (cx + i * TL + 1) * B + b;
-          double2 sn = cadd(lds[bf][c + B], lds[bf][c - B]);
-          sn = cadd(sn, xp[i]);
-          sn = cadd(sn, xm[i]);
-          const double2 xr = xc[i];
-          const double2 h = make_double2(fma(dc[i], xr.x, hu * sn.x), fma(dc[i], xr.y, hu * sn.y));
-          const double2 yv = FIRST ? h : twice_minus(h, wc[i]);
-          box_st(os + y * vrow, oo[i], yv);
-          if (FIRST) {
-            cdot_acc(ar, ai, xr, xr);
-            cdot_acc(br, bi, xr, yv);
-          } else {
-            cdot_acc(ar, ai, yv, xr);
-          }
-          cdot_acc(cr, ci, yv, yv);
-        }
-      }
-    };
-    using S0 = std::integral_constant<int, 0>;
-    using S1 = std::integral_constant<int, 1>;
-    for (int y = y0; y < y1; y += 4) {
-      row(y, S0{}, q0, q1, q2, q3, wa, wb, d0, d1, h0, h1);
-      if (y + 1 >= y1) break;
-      row(y + 1, S1{}, q1, q2, q3, q0, wb, wa, d1, d0, h1, h0);
-      if (y + 2 >= y1) break;
-      row(y + 2, S0{}, q2, q3, q0, q1, wa, wb, d0, d1, h0, h1);
-      if (y + 3 >= y1) break;
-      row(y + 3, S1{}, q3, q0, q1, q2, wb, wa, d1, d0, h1, h0);
-    }
-    __syncthreads();   // the next item stages into buffer 0 again
-  }
-  block_reduce_store<B>(ar, ai, part_a + (int64_t)lb * B);
-  __syncthreads();
-  block_reduce_store<B>(cr, ci, part_c + (int64_t)lb * B);
-  if (FIRST) {
-    __syncthreads();
-    block_reduce_store<B>(br, bi, part_b + (int64_t)lb * B);
-  }
-}
-
-// ---------------------------------------------------------------------------
 // Moment step for <a|T_n|b> with a != b: both chains a_k = T_k a, b_k = T_k b
 // advance in one launch (one matrix read, the two gathers share the indices)
 // and the identities give
@@ -988,214 +608,9 @@ hipError_t launch_evolve_term(const DevMat& A, int hop_mode, int B, const StepIO
   });
 }
 
-namespace {
-
-// The fused MSD term of k_msd_term on a periodic box whose position differences are
-// +-box_dx on the x neighbours and 0 on the others, as the box stencil of
-// k_moment_step_sym_box with both chains staged: [X,H~] a at a row is
-// -box_dx hu (a_{x+1} - a_{x-1}).  Work items, tiles, addressing and the one-plane
-// lookahead as there; no partial sums.
-template <int B, int TX, int TY, bool FIRST>
-__global__ __launch_bounds__(kBlock) void k_msd_term_box(DevMat A, ChainIO io, double2* acc_a, double2* acc_b,
-                                                         const double* __restrict__ Jtab, int ldJ, int m,
-                                                         double2 ph_m, double2 ph_0, int zc) {
-  using T = BoxTile<B, TX, TY>;
-  constexpr int OPT = T::OPT, HPT = T::HPT, PX = T::PX;
-  __shared__ double2 lda[2][T::PE], ldb[2][T::PE];
-  const int lb = logical_block(A.G);
-  const int Lx = A.box[0], Ly = A.box[1], Lz = A.box[2];
-  const int txn = (Lx + TX - 1) / TX, tyn = (Ly + TY - 1) / TY, zn = (Lz + zc - 1) / zc;
-  const int64_t cols = (int64_t)txn * tyn, items = cols * zn;
-  const double hu = A.seg_hop[0];
-  const double hdx = hu * A.box_dx;
-  const double2 cm = cscale(Jtab[m], ph_m);
-  const double2 c0 = cscale(Jtab[0], ph_0);
-  const int b = threadIdx.x & (B - 1);
-  const char* xas = reinterpret_cast<const char*>(io.xa);
-  const char* xbs = reinterpret_cast<const char*>(io.xb);
-  // read only after the first step: the previous chain elements and the running sums
-  // (acc is read and then overwritten element by element, so it is not restrict)
-  const char* was = reinterpret_cast<const char*>(io.wa);
-  const char* wbs = reinterpret_cast<const char*>(io.wb);
-  const char* sas = reinterpret_cast<const char*>(acc_a);
-  const char* sbs = reinterpret_cast<const char*>(acc_b);
-  char* oas = reinterpret_cast<char*>(io.oa);
-  char* obs = reinterpret_cast<char*>(io.ob);
-  char* aas = reinterpret_cast<char*>(acc_a);
-  char* abs_ = reinterpret_cast<char*>(acc_b);
-  const char* ds = reinterpret_cast<const char*>(A.diag);
-  const int64_t vplane = (int64_t)Lx * Ly * B * (int64_t)sizeof(double2);
-  const int64_t dplane = (int64_t)Lx * Ly * (int64_t)sizeof(double);
-  auto zw = [Lz](int z) { return z < 0 ? z + Lz : (z >= Lz ? z - Lz : z); };   // z in [-1, Lz + 1]
-  T t(b);
-  for (int64_t it = lb; it < items; it += A.G) {
-    const int tz = (int)(it / cols);
-    const int64_t txy = it % cols;
-    const int z0 = tz * zc, z1 = min(z0 + zc, Lz);
-    t.place((int)(txy % txn) * TX, (int)(txy / txn) * TY, Lx, Ly, b);
-    // chains a and b of planes z - 1, z, z + 1 and the ones loaded for z + 2 rotate through
-    // a0..a3 and b0..b3; the previous chain elements, the running sums, the diagonal and the
-    // halos of planes z and z + 1 through pairs; unrolled four planes deep as in
-    // k_moment_step_sym_box, so that the rotation is a renaming
-    double2 a0[OPT], a1[OPT], a2[OPT], a3[OPT], b0[OPT], b1[OPT], b2[OPT], b3[OPT];
-    double2 wa0[OPT], wa1[OPT], wb0[OPT], wb1[OPT], sa0[OPT], sa1[OPT], sb0[OPT], sb1[OPT];
-    double d0[OPT], d1[OPT];
-    double2 ha0[HPT], ha1[HPT], hb0[HPT], hb1[HPT];
-    // the once-read operands of plane z (only the diagonal on the first step)
-    auto ld_prev = [&](int z, double2(&wa)[OPT], double2(&wb)[OPT], double2(&sa)[OPT], double2(&sb)[OPT],
-                       double(&d)[OPT]) {
-      const int64_t v = z * vplane;
-#pragma unroll
-      for (int i = 0; i < OPT; ++i) {
-        if (!FIRST) {
-          wa[i] = box_ld<kBoxNtLoad>(was + v, t.oo[i]);
-          wb[i] = box_ld<kBoxNtLoad>(wbs + v, t.oo[i]);
-          sa[i] = box_ld<kBoxNtLoad>(sas + v, t.oo[i]);
-          sb[i] = box_ld<kBoxNtLoad>(sbs + v, t.oo[i]);
-        }
-        d[i] = box_ldd(ds + z * dplane, t.od[i]);
-      }
-    };
-    {
-      const int64_t vm = zw(z0 - 1) * vplane, v0 = z0 * vplane, vp = zw(z0 + 1) * vplane;
-#pragma unroll
-      for (int i = 0; i < OPT; ++i) {
-        wa0[i] = wb0[i] = sa0[i] = sb0[i] = make_double2(0.0, 0.0);
-        wa1[i] = wb1[i] = sa1[i] = sb1[i] = make_double2(0.0, 0.0);
-        a0[i] = box_ld(xas + vm, t.oo[i]);
-        a1[i] = box_ld(xas + v0, t.oo[i]);
-        a2[i] = box_ld(xas + vp, t.oo[i]);
-        b0[i] = box_ld(xbs + vm, t.oo[i]);
-        b1[i] = box_ld(xbs + v0, t.oo[i]);
-        b2[i] = box_ld(xbs + vp, t.oo[i]);
-      }
-      ld_prev(z0, wa0, wb0, sa0, sb0, d0);
-#pragma unroll
-      for (int j = 0; j < HPT; ++j) {
-        ha0[j] = box_ld(xas + v0, t.ho[j]);
-        hb0[j] = box_ld(xbs + v0, t.ho[j]);
-      }
-    }
-    // plane z in LDS buffer BF: the loads for plane z + 1 (unconditional, as in
-    // k_moment_step_sym_box), then the stencil on both chains
-    auto plane = [&](int z, auto BF, double2(&am)[OPT], double2(&ac)[OPT], double2(&ap)[OPT], double2(&aq)[OPT],
-                     double2(&bm)[OPT], double2(&bc)[OPT], double2(&bp)[OPT], double2(&bq)[OPT],
-                     double2(&wac)[OPT], double2(&wan)[OPT], double2(&wbc)[OPT], double2(&wbn)[OPT],
-                     double2(&sac)[OPT], double2(&san)[OPT], double2(&sbc)[OPT], double2(&sbn)[OPT],
-                     double(&dc)[OPT], double(&dn)[OPT], double2(&hac)[HPT], double2(&han)[HPT],
-                     double2(&hbc)[HPT], double2(&hbn)[HPT]) {
-      constexpr int bf = decltype(BF)::value;
-      {
-        const int z1n = zw(z + 1);
-        const int64_t vq = zw(z + 2) * vplane, vn = z1n * vplane;
-#pragma unroll
-        for (int i = 0; i < OPT; ++i) {
-          aq[i] = box_ld(xas + vq, t.oo[i]);
-          bq[i] = box_ld(xbs + vq, t.oo[i]);
-        }
-        ld_prev(z1n, wan, wbn, san, sbn, dn);
-#pragma unroll
-        for (int j = 0; j < HPT; ++j) {
-          han[j] = box_ld(xas + vn, t.ho[j]);
-          hbn[j] = box_ld(xbs + vn, t.ho[j]);
-        }
-      }
-#pragma unroll
-      for (int i = 0; i < OPT; ++i) {
-        lda[bf][t.oslot[i]] = ac[i];
-        ldb[bf][t.oslot[i]] = bc[i];
-      }
-#pragma unroll
-      for (int j = 0; j < HPT; ++j)
-        if (t.hval[j]) {
-          lda[bf][t.hslot[j]] = hac[j];
-          ldb[bf][t.hslot[j]] = hbc[j];
-        }
-      __syncthreads();
-      const int64_t vz = z * vplane;
-#pragma unroll
-      for (int i = 0; i < OPT; ++i) {
-        if (t.oval[i]) {
-          const int c = t.oslot[i];
-          const double2 axp = lda[bf][c + B], axm = lda[bf][c - B];
-          double2 na = cadd(axp, axm);
-          na = cadd(na, lda[bf][c + PX * B]);
-          na = cadd(na, lda[bf][c - PX * B]);
-          na = cadd(na, ap[i]);
-          na = cadd(na, am[i]);
-          double2 nb = cadd(ldb[bf][c + B], ldb[bf][c - B]);
-          nb = cadd(nb, ldb[bf][c + PX * B]);
-          nb = cadd(nb, ldb[bf][c - PX * B]);
-          nb = cadd(nb, bp[i]);
-          nb = cadd(nb, bm[i]);
-          const double dg = dc[i];
-          const double2 ha = make_double2(fma(dg, ac[i].x, hu * na.x), fma(dg, ac[i].y, hu * na.y));
-          const double2 hb = make_double2(fma(dg, bc[i].x, hu * nb.x), fma(dg, bc[i].y, hu * nb.y));
-          // [X,H~] a + H~ b, [X,H~]_rj = -dx_rj H~_rj
-          const double2 g = make_double2(hb.x - hdx * (axp.x - axm.x), hb.y - hdx * (axp.y - axm.y));
-          if (FIRST) {
-            box_st(oas + vz, t.oo[i], ha);
-            box_st(obs + vz, t.oo[i], g);
-            box_st(aas + vz, t.oo[i], cadd(cmul(c0, ac[i]), cmul(cm, ha)));
-            box_st(abs_ + vz, t.oo[i], cadd(cmul(c0, bc[i]), cmul(cm, g)));
-          } else {
-            const double2 ya = twice_minus(ha, wac[i]);
-            const double2 yb = twice_minus(g, wbc[i]);
-            box_st(oas + vz, t.oo[i], ya);
-            box_st(obs + vz, t.oo[i], yb);
-            box_st(aas + vz, t.oo[i], cadd(sac[i], cmul(cm, ya)));
-            box_st(abs_ + vz, t.oo[i], cadd(sbc[i], cmul(cm, yb)));
-          }
-        }
-      }
-    };
-    using S0 = std::integral_constant<int, 0>;
-    using S1 = std::integral_constant<int, 1>;
-    for (int z = z0; z < z1; z += 4) {
-      plane(z, S0{}, a0, a1, a2, a3, b0, b1, b2, b3, wa0, wa1, wb0, wb1, sa0, sa1, sb0, sb1, d0, d1, ha0, ha1,
-            hb0, hb1);
-      if (z + 1 >= z1) break;
-      plane(z + 1, S1{}, a1, a2, a3, a0, b1, b2, b3, b0, wa1, wa0, wb1, wb0, sa1, sa0, sb1, sb0, d1, d0, ha1,
-            ha0, hb1, hb0);
-      if (z + 2 >= z1) break;
-      plane(z + 2, S0{}, a2, a3, a0, a1, b2, b3, b0, b1, wa0, wa1, wb0, wb1, sa0, sa1, sb0, sb1, d0, d1, ha0,
-            ha1, hb0, hb1);
-      if (z + 3 >= z1) break;
-      plane(z + 3, S1{}, a3, a0, a1, a2, b3, b0, b1, b2, wa1, wa0, wb1, wb0, sa1, sa0, sb1, sb0, d1, d0, ha1,
-            ha0, hb1, hb0);
-    }
-    __syncthreads();   // the next item stages into buffer 0 again
-  }
-}
-
-}  // namespace
-
-// Planes per work item of the box kernels on tiles of tx x ty (stencil_run over the G
-// workgroups).
-static int box_run(const DevMat& A, int tx, int ty) {
-  const int64_t cols = (int64_t)((A.box[0] + tx - 1) / tx) * ((A.box[1] + ty - 1) / ty);
-  return stencil_run(cols, A.box[2], A.G);
-}
-
 hipError_t launch_msd_term(const DevMat& A, int hop_mode, int B, const ChainIO& io, double2* acc_a,
                            double2* acc_b, const double* Jtab, int ldJ, int m, double2 phase_m,
                            double2 phase_0, hipStream_t s) {
-  if (A.use_box_msd && A.box[0] > 0 && hop_mode == HOP_UNIFORM && B >= 2) {
-    // tiles: 16 x 8 (B = 2), 8 x 8 (4), 8 x 4 (8), 4 x 4 (16): two staged chains fit the LDS
-    const int zc = box_run(A, B == 2 ? 16 : (B == 16 ? 4 : 8), B >= 8 ? 4 : 8);
-    auto go = [&](auto Fc) {
-      constexpr bool F = decltype(Fc)::value;
-      const dim3 g(A.G);
-      switch (B) {
-        case 2: k_msd_term_box<2, 16, 8, F><<<g, kBlock, 0, s>>>(A, io, acc_a, acc_b, Jtab, ldJ, m, phase_m, phase_0, zc); break;
-        case 4: k_msd_term_box<4, 8, 8, F><<<g, kBlock, 0, s>>>(A, io, acc_a, acc_b, Jtab, ldJ, m, phase_m, phase_0, zc); break;
-        case 8: k_msd_term_box<8, 8, 4, F><<<g, kBlock, 0, s>>>(A, io, acc_a, acc_b, Jtab, ldJ, m, phase_m, phase_0, zc); break;
-        default: k_msd_term_box<16, 4, 4, F><<<g, kBlock, 0, s>>>(A, io, acc_a, acc_b, Jtab, ldJ, m, phase_m, phase_0, zc); break;
-      }
-    };
-    if (io.first) go(std::true_type{}); else go(std::false_type{});
-    return hipGetLastError();
-  }
   return dispatch_sparse(A, hop_mode, B, A.nt, [&](auto Bc, auto Hc, auto Kc, auto NTc) {
     k_msd_term<decltype(Bc)::value, decltype(Hc)::value, decltype(Kc)::value, decltype(NTc)::value>
         <<<dim3(A.G), kBlock, 0, s>>>(A, io, acc_a, acc_b, Jtab, ldJ, m, phase_m, phase_0);
@@ -1257,35 +672,6 @@ hipError_t launch_moment_step_pair(const DevMat& A, int hop_mode, int B, const C
 
 hipError_t launch_moment_step_sym(const DevMat& A, int hop_mode, int B, const StepIO& io,
                                   double2* part_a, double2* part_b, double2* part_c, hipStream_t s) {
-  if (A.use_sheet && A.sheet && A.sheet_zc && A.sheet_blk0 && hop_mode == HOP_UNIFORM && B >= 2) {
-    auto go = [&](auto Fc) {
-      constexpr bool F = decltype(Fc)::value;
-      const dim3 g(A.G);
-      switch (B) {
-        case 2: k_moment_step_sym_sheet<2, kSheetCells, F><<<g, kBlock, 0, s>>>(A, io, part_a, part_b, part_c); break;
-        case 4: k_moment_step_sym_sheet<4, kSheetCells, F><<<g, kBlock, 0, s>>>(A, io, part_a, part_b, part_c); break;
-        case 8: k_moment_step_sym_sheet<8, kSheetCells, F><<<g, kBlock, 0, s>>>(A, io, part_a, part_b, part_c); break;
-        default: k_moment_step_sym_sheet<16, kSheetCells, F><<<g, kBlock, 0, s>>>(A, io, part_a, part_b, part_c); break;
-      }
-    };
-    if (io.first) go(std::true_type{}); else go(std::false_type{});
-    return hipGetLastError();
-  }
-  if (A.use_box && A.box[0] > 0 && hop_mode == HOP_UNIFORM && B >= 2) {
-    const int zc = box_run(A, B == 2 ? 16 : 8, 8);   // the tiles of the instances below
-    auto go = [&](auto Fc) {
-      constexpr bool F = decltype(Fc)::value;
-      const dim3 g(A.G);
-      switch (B) {
-        case 2: k_moment_step_sym_box<2, 16, 8, F><<<g, kBlock, 0, s>>>(A, io, zc, part_a, part_b, part_c); break;
-        case 4: k_moment_step_sym_box<4, 8, 8, F><<<g, kBlock, 0, s>>>(A, io, zc, part_a, part_b, part_c); break;
-        case 8: k_moment_step_sym_box<8, 8, 8, F><<<g, kBlock, 0, s>>>(A, io, zc, part_a, part_b, part_c); break;
-        default: k_moment_step_sym_box<16, 8, 8, F><<<g, kBlock, 0, s>>>(A, io, zc, part_a, part_b, part_c); break;
-      }
-    };
-    if (io.first) go(std::true_type{}); else go(std::false_type{});
-    return hipGetLastError();
-  }
   return dispatch_sparse(A, hop_mode, B, A.nt, [&](auto Bc, auto Hc, auto Kc, auto NTc) {
     k_moment_step_sym<decltype(Bc)::value, decltype(Hc)::value, decltype(Kc)::value,
                       decltype(NTc)::value><<<dim3(A.G), kBlock, 0, s>>>(A, io, part_a, part_b, part_c);

@@ -1,0 +1,239 @@
+// Lattices of the march kernels (march.h): recognising them in a descriptor and
+// cutting them into the tiles of a launch.  Host code only.
+#include <algorithm>
+#include <cmath>
+
+#include "internal.h"
+#include "march.h"
+
+namespace gpuqt {
+
+namespace {
+
+// The dims of a segment of n rows that is a BRICK lattice, from row 0's neighbours
+// (1, Lx - 1 and Lx or (Ly - 1) Lx); every row must have its three neighbours in the
+// slots of row 0.  slot = stored slots of (+x, -x, vertical).
+bool brick_dims(const gpuqt_h_desc* d, int64_t off, int64_t n, int32_t dims[3], int32_t slot[3], int32_t* parity) {
+  const int64_t k = d->max_nn;
+  const int32_t* r0 = d->nbr + off * k;
+  for (int cand = 0; cand < 3; ++cand) {
+    const int64_t Lx = (int64_t)r0[cand] - off + 1;   // candidate: the -x neighbour of (0, 0) is Lx - 1
+    if (Lx < 4 || Lx % 2 || n % Lx || Lx > (1 << 24)) continue;
+    const int64_t Ly = n / Lx;
+    if (Ly < 4 || Ly % 2 || Ly > INT32_MAX) continue;
+    for (int par = 0; par < 2; ++par) {
+      int32_t s[3] = {-1, cand, -1};
+      for (int j = 0; j < 3; ++j) {
+        const int64_t c = r0[j] - off;
+        if (j == cand) continue;
+        if (c == 1 && s[0] < 0) s[0] = j;
+        else if (c == (par == 0 ? Lx : (Ly - 1) * Lx)) s[2] = j;
+      }
+      if (s[0] < 0 || s[2] < 0) continue;
+      bool ok = true;
+      for (int64_t y = 0; y < Ly && ok; ++y) {
+        const int64_t up = off + (y + 1 == Ly ? 0 : y + 1) * Lx, dn = off + (y == 0 ? Ly - 1 : y - 1) * Lx;
+        const int64_t row = off + y * Lx;
+        for (int64_t x = 0; x < Lx; ++x) {
+          const int32_t* c = d->nbr + (row + x) * k;
+          if (d->nn[row + x] != 3 || c[s[0]] != row + (x + 1 == Lx ? 0 : x + 1) ||
+              c[s[1]] != row + (x == 0 ? Lx - 1 : x - 1) || c[s[2]] != (((x + y + par) & 1) == 0 ? up : dn) + x) {
+            ok = false;
+            break;
+          }
+        }
+      }
+      if (!ok) continue;
+      dims[0] = (int32_t)Lx;
+      dims[1] = 1;
+      dims[2] = (int32_t)Ly;
+      std::copy(s, s + 3, slot);
+      *parity = par;
+      return true;
+    }
+  }
+  return false;
+}
+
+}  // namespace
+
+bool detect_lattice(const gpuqt_h_desc* d, const HostLayout& L, const int32_t box[3],
+                    const std::vector<int32_t>& sheets, MarchLattice* M) {
+  *M = MarchLattice();
+  const int n_seg = L.n_seg;
+  if (box[0] > 0) {
+    M->pattern = MARCH_BOX;
+    M->dims = {box[0], box[1], box[2]};
+  } else if (!sheets.empty()) {
+    M->pattern = MARCH_SQUARE;
+    for (int s = 0; s < n_seg; ++s) M->dims.insert(M->dims.end(), {sheets[2 * s], 1, sheets[2 * s + 1]});
+  } else if (L.uniform_width == 3 && d->nn && d->nbr) {
+    for (int s = 0; s < n_seg; ++s) {
+      int32_t dims[3], slot[3], par = 0;
+      if (!brick_dims(d, L.seg_off[s], L.seg_off[s + 1] - L.seg_off[s], dims, slot, &par)) return false;
+      if (s > 0 && (par != M->parity || !std::equal(slot, slot + 3, M->slot))) return false;
+      M->parity = par;
+      std::copy(slot, slot + 3, M->slot);
+      M->dims.insert(M->dims.end(), dims, dims + 3);
+    }
+    M->pattern = MARCH_BRICK;
+  } else {
+    return false;
+  }
+  // rows (planes) of blocks of 16 vectors are addressed with 32-bit byte offsets
+  for (int s = 0; s < n_seg; ++s)
+    if ((int64_t)M->dims[3 * s] * M->dims[3 * s + 1] >= (int64_t(1) << 24)) {
+      M->pattern = MARCH_NONE;
+      return false;
+    }
+  // one pass over the rows: the stored slot of each square neighbour (needed where every
+  // entry has its own hopping: it must be the same on every row) and the position steps
+  const bool square = M->pattern == MARCH_SQUARE;
+  const bool slots = square && L.hop_mode != HOP_UNIFORM;
+  const int K = L.uniform_width, S = L.S;
+  bool dx_ok = true;
+  size_t col0 = 0;
+  for (int s = 0; s < n_seg; ++s) {
+    const int64_t Lx = M->dims[3 * s], Ly = M->dims[3 * s + 1], Lm = M->dims[3 * s + 2];
+    const int64_t off = L.seg_off[s];
+    M->dxcol.resize(col0 + Lx, 0.0);
+    double* dxc = M->dxcol.data() + col0;
+    col0 += Lx;
+    for (int64_t z = 0; z < Ly * Lm; ++z) {
+      const int64_t row = off + z * Lx;
+      const int64_t up = off + (z + 1 == Lm ? 0 : z + 1) * Lx, dn = off + (z == 0 ? Lm - 1 : z - 1) * Lx;
+      for (int64_t x = 0; x < Lx; ++x) {
+        const int64_t r = row + x, e0 = (r / S) * ((int64_t)K * S) + r % S;
+        const int64_t xp = row + (x + 1 == Lx ? 0 : x + 1), xm = row + (x == 0 ? Lx - 1 : x - 1);
+        for (int j = 0; j < K; ++j) {
+          const int64_t e = e0 + (int64_t)j * S, c = L.col[e];
+          if (slots) {
+            const int64_t want[4] = {xp, xm, up + x, dn + x};
+            int q = 0;
+            while (q < 4 && want[q] != c) ++q;
+            if (q == 4) {
+              M->pattern = MARCH_NONE;
+              return false;
+            }
+            if (s == 0 && z == 0 && x == 0) M->slot[q] = j;
+            if (M->slot[q] != j) {
+              M->pattern = MARCH_NONE;
+              return false;
+            }
+          }
+          if (!dx_ok) continue;
+          const double v = L.hop_mode == HOP_DICT ? L.dxtab[L.hidx[e]] : L.dx[e];
+          if (c == xp) {
+            if (z == 0) dxc[x] = v;
+            dx_ok = dx_ok && v == dxc[x];
+          } else if (c != xm) {
+            dx_ok = dx_ok && v == 0.0;
+          } else if (z > 0) {   // (row 0's +x differences are known by now)
+            dx_ok = dx_ok && v == -dxc[x == 0 ? Lx - 1 : x - 1];
+          }
+        }
+      }
+    }
+  }
+  if (M->pattern == MARCH_BOX)   // one value in the whole box
+    for (double v : M->dxcol) dx_ok = dx_ok && v == M->dxcol[0];
+  M->dx = M->dxcol[0];
+  M->dx_ok = dx_ok ? 1 : 0;
+  return true;
+}
+
+// The tiles and runs with the least estimated time: an iteration (one row or plane of
+// a workgroup) costs its wavefronts' share of a CU's issue slots, a CU runs
+// ceil(workgroups / CUs) workgroups one iteration after another's, and a run of zc rows
+// takes zc + 2 T iterations.  Measured on 2000^2 rows with T = 8: within 10 % of the times
+// of 16 to 125 rows per run; on 200^3 likewise.
+bool plan_march(const MarchLattice& M, const std::vector<int64_t>& seg_off, int T, int B, int max_items, int cus,
+                const std::vector<int>& lane_choices, int max_tile_x, MarchPlan* out) {
+  const int n_seg = (int)seg_off.size() - 1;
+  const bool box = M.pattern == MARCH_BOX;
+  double best = 0.0;
+  out->T = 0;
+  auto ceil_div = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+  // tiles of one segment: as equal as the counts allow
+  auto consider = [&](int lanes, const std::vector<MarchSeg>& tiles, int zmax) {
+    int64_t last = -1;
+    for (int64_t nz = 1; nz <= zmax; nz = nz < 64 ? nz + 1 : nz + nz / 16) {
+      const int64_t zt = ceil_div(zmax, nz);
+      if (zt == last) continue;
+      last = zt;
+      int64_t items = 0;
+      int zc = 0;
+      for (const MarchSeg& t : tiles) {
+        const int64_t runs = ceil_div(t.Lm, std::min<int64_t>(zt, t.Lm));
+        const int64_t z = ceil_div(t.Lm, runs);
+        items += (int64_t)t.nx * t.ny * ceil_div(t.Lm, z);
+        zc = std::max(zc, (int)z);
+      }
+      if (items > max_items) break;
+      const double waves = (double)ceil_div(items * B, cus) * lanes / 256.0;
+      const double t = (ceil_div(zc + 2 * T, 3) * 3) * std::max(waves, 0.75);
+      if (best == 0.0 || t < best) {
+        best = t;
+        out->T = T;
+        out->lanes = lanes;
+        out->items = (int32_t)items;
+        out->segs = tiles;
+        int32_t first = 0;
+        out->item0.assign(1, 0);
+        for (MarchSeg& q : out->segs) {
+          const int64_t runs = ceil_div(q.Lm, std::min<int64_t>(zt, q.Lm));
+          q.zc = (int32_t)ceil_div(q.Lm, runs);
+          q.item0 = first;
+          first += (int32_t)(q.nx * q.ny * ceil_div(q.Lm, q.zc));
+          out->item0.push_back(first);
+        }
+      }
+    }
+  };
+  for (int lanes : lane_choices) {
+    int zmax = 0;
+    std::vector<MarchSeg> tiles(n_seg);
+    for (int s = 0; s < n_seg; ++s) {
+      MarchSeg& t = tiles[s];
+      t = MarchSeg();
+      t.off = seg_off[s];
+      t.Lx = M.dims[3 * s];
+      t.Ly = M.dims[3 * s + 1];
+      t.Lm = M.dims[3 * s + 2];
+      t.ny = t.ty = t.uy = 1;
+      t.dx0 = s == 0 ? 0 : tiles[s - 1].dx0 + tiles[s - 1].Lx;
+      zmax = std::max(zmax, t.Lm);
+      if (!box) {
+        const int u = lanes - 2 * T;
+        t.nx = (int32_t)ceil_div(t.Lx, u);
+        t.ux = (int32_t)ceil_div(t.Lx, t.nx);
+        t.nx = (int32_t)ceil_div(t.Lx, t.ux);
+        t.tx = t.ux + 2 * T;
+      }
+    }
+    if (!box) {
+      consider(lanes, tiles, zmax);
+      continue;
+    }
+    // a box: every split of the plane whose tile (with its margins) has at most `lanes` cells
+    MarchSeg& t = tiles[0];
+    for (int nx = 1; nx <= t.Lx; ++nx) {
+      const int ux = (int)ceil_div(t.Lx, nx);
+      if (ux + 2 * T > max_tile_x) continue;
+      const int uy_max = lanes / (ux + 2 * T) - 2 * T;
+      if (uy_max < 1) continue;
+      const int ny = (int)ceil_div(t.Ly, uy_max), uy = (int)ceil_div(t.Ly, ny);
+      t.ux = ux;
+      t.uy = uy;
+      t.nx = (int32_t)ceil_div(t.Lx, ux);
+      t.ny = (int32_t)ceil_div(t.Ly, uy);
+      t.tx = ux + 2 * T;
+      t.ty = uy + 2 * T;
+      consider(lanes, tiles, zmax);
+      if (ux <= 4) break;
+    }
+  }
+  return out->T > 0;
+}
+
+}  // namespace gpuqt

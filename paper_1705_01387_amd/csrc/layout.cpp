@@ -588,71 +588,6 @@ bool detect_sheets(const gpuqt_h_desc* d, const std::vector<int64_t>& seg_off, s
   return true;
 }
 
-int stencil_run(int64_t cols, int len, int64_t workers) {
-  workers = std::max<int64_t>(workers, 1);
-  int best_z = len;
-  int64_t best = -1;
-  for (int runs = 1; runs <= len; ++runs) {
-    const int z = (len + runs - 1) / runs;
-    if (runs > 1 && z < 16) break;
-    const int64_t rounds = (cols * ((len + z - 1) / z) + workers - 1) / workers;
-    const int64_t cost = rounds * (z + 2);
-    if (best < 0 || cost < best) {
-      best = cost;
-      best_z = z;
-    }
-  }
-  return std::max(best_z, 1);
-}
-
-void sheet_split(const std::vector<int64_t>& cols, const std::vector<int32_t>& len, int64_t G,
-                 std::vector<int32_t>* blk0, std::vector<int32_t>* zc) {
-  const int n = (int)cols.size();
-  auto cost = [&](int s, int64_t g) -> int64_t {
-    const int z = stencil_run(cols[s], len[s], g);
-    const int64_t rounds = (cols[s] * ((len[s] + z - 1) / z) + g - 1) / g;
-    return rounds * (z + 2);
-  };
-  // least workgroups that keep segment s within T (G + 1: none do); cost falls with g
-  auto need = [&](int s, int64_t T) -> int64_t {
-    if (cost(s, G) > T) return G + 1;
-    int64_t lo = 1, hi = G;
-    while (lo < hi) {
-      const int64_t mid = (lo + hi) / 2;
-      if (cost(s, mid) <= T) hi = mid;
-      else lo = mid + 1;
-    }
-    return lo;
-  };
-  auto fits = [&](int64_t T) {
-    int64_t tot = 0;
-    for (int s = 0; s < n && tot <= G; ++s) tot += need(s, T);
-    return tot <= G;
-  };
-  int64_t lo = 1, hi = 1;
-  for (int s = 0; s < n; ++s) hi = std::max(hi, cost(s, 1));
-  while (lo < hi) {
-    const int64_t mid = (lo + hi) / 2;
-    if (fits(mid)) hi = mid;
-    else lo = mid + 1;
-  }
-  std::vector<int64_t> g(n);
-  int64_t used = 0;
-  int big = 0;
-  for (int s = 0; s < n; ++s) {
-    g[s] = std::max<int64_t>(1, need(s, lo));
-    used += g[s];
-    if (cols[s] * len[s] > cols[big] * len[big]) big = s;
-  }
-  g[big] += G - used;
-  blk0->assign(n + 1, 0);
-  zc->assign(n, 1);
-  for (int s = 0; s < n; ++s) {
-    (*blk0)[s + 1] = (*blk0)[s] + (int32_t)g[s];
-    (*zc)[s] = stencil_run(cols[s], len[s], g[s]);
-  }
-}
-
 bool detect_box(const gpuqt_h_desc* d, int32_t box[3]) {
   box[0] = box[1] = box[2] = 0;
   if (!d || d->n < 27 || d->max_nn < 6 || (d->n_segments > 1) || !d->nn || !d->nbr) return false;
@@ -688,44 +623,6 @@ bool detect_box(const gpuqt_h_desc* d, int32_t box[3]) {
   box[0] = (int32_t)Lx;
   box[1] = (int32_t)Ly;
   box[2] = (int32_t)Lz;
-  return true;
-}
-
-bool box_dx_uniform(const HostLayout& L, const int32_t box[3], double* dx) {
-  const int64_t Lx = box[0], Ly = box[1], LxLy = (int64_t)box[0] * box[1];
-  if (Lx <= 0 || L.uniform_width != 6 || L.dx.empty() || L.col.empty()) return false;
-  const int S = L.S;
-  double delta = 0.0;
-  bool have = false;
-  for (int64_t r = 0; r < L.n; ++r) {
-    const int64_t x = r % Lx, yz = r / Lx;
-    const int64_t xp = (x + 1) % Lx + Lx * yz, xm = (x + Lx - 1) % Lx + Lx * yz;
-    const int64_t base = (r / S) * (int64_t)(6 * S) + (r % S);
-    for (int j = 0; j < 6; ++j) {
-      const int64_t e = base + (int64_t)j * S;
-      const int64_t c = L.col[e];
-      const double d = L.dx[e];
-      if (c == xp) {
-        if (!have) {
-          delta = d;
-          have = true;
-        }
-        if (d != delta) return false;
-      } else if (c == xm) {
-        if (!have) {
-          delta = -d;
-          have = true;
-        }
-        if (d != -delta) return false;
-      } else if (d != 0.0) {
-        return false;
-      }
-    }
-  }
-  (void)Ly;
-  (void)LxLy;
-  if (!have) return false;
-  *dx = delta;
   return true;
 }
 

@@ -43,7 +43,9 @@ gpuqt_status tune_key(const Handle* h, int B, std::string* key) {
   std::ostringstream o;
   o << arch << " n" << (int)std::floor(std::log2((double)std::max<int64_t>(h->n, 1))) << " K" << h->uniform_width
     << " w" << h->max_width << " S" << h->S << " h" << h->hop_mode << " s" << h->n_seg << " p"
-    << (period > 0 ? (int)std::floor(std::log2((double)period)) : -1) << " m" << mask << " B" << B;
+    << (period > 0 ? (int)std::floor(std::log2((double)period)) : -1) << " m" << mask;
+  if (h->lat.pattern != MARCH_NONE) o << " l" << h->lat.pattern;   // its codes choose marches too
+  o << " B" << B;
   *key = o.str();
   return GPUQT_OK;
 }

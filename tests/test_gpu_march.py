@@ -1,0 +1,152 @@
+"""The lattice marches (several recurrence steps per launch) against the oracle and against the
+general kernels on the same handle (variant bit 26 off), at widths on both sides of a tile's
+edge, runs of one row and of many, every hopping storage and block width.  Bar: normwise
+1e-10, as for every kernel: the forms differ in rounding only, a few ulps a step."""
+import numpy as np
+import pytest
+
+import oracle as O
+import paper_1705_01387_amd as P
+from paper_1705_01387_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-10
+MARCH = 3 << 26
+
+
+def say(*a):
+    print(*a, flush=True)
+
+
+def dev(a):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda")
+
+
+def host(t):
+    return t.detach().cpu().numpy()
+
+
+def err(got, ref):
+    return float(np.max(np.abs(np.asarray(got) - np.asarray(ref))) / max(np.max(np.abs(ref)), 1e-300))
+
+
+def sheet(Lx, Ly, seed, **kw):
+    return I.square(Lx, Ly, W=2.0, seed=seed, **kw)
+
+
+# name: (model, build options, march expected).  Tiles own 64 - 2 T or 128 - 2 T cells of a row (T = 8: 48 and
+# 112) or, in a box, tiles of at most 1024 cells with margins of T.
+CASES = {
+    "square48x40": lambda: (sheet(48, 40, 1), {}, True),
+    "square49x3": lambda: (sheet(49, 3, 2), {}, True),
+    "square3x50": lambda: (sheet(3, 50, 3), {}, True),
+    "square113x17": lambda: (sheet(113, 17, 4), {}, True),
+    "square_real_table": lambda: (sheet(40, 22, 5, t1=-0.7), {}, True),
+    "square_real_entries": lambda: (I.bond_disorder(sheet(37, 19, 6), 0.2, 7), dict(no_dictionary=True), True),
+    "square_complex_table": lambda: (I.bond_disorder(sheet(61, 9, 8), 0.2, 9, max_phase=0.5), {}, True),
+    "square_complex_entries": lambda: (I.bond_disorder(sheet(57, 23, 10), 0.2, 11, max_phase=0.5),
+                                       dict(no_dictionary=True, slice_height=32), True),
+    "brick_uniform": lambda: (I.honeycomb(29, 20, W=2.0, seed=12), {}, True),
+    "brick_flux_table": lambda: (I.honeycomb(27, 18, flux=1 / 243, W=2.0, seed=13), {}, True),
+    "brick_complex_entries": lambda: (I.honeycomb(24, 50, flux=1 / 600, W=2.0, seed=14), dict(no_dictionary=True), True),
+    "brick_real_entries": lambda: (I.bond_disorder(I.honeycomb(20, 12, W=1.0, seed=15), 0.3, 16),
+                                   dict(no_dictionary=True), True),
+    "box26x27x9": lambda: (I.box(26, 27, 9, W=3.0, seed=17), {}, True),
+    "box3x4x30": lambda: (I.box(3, 4, 30, W=3.0, seed=18, slot_seed=19), {}, True),
+    "box45x11x5": lambda: (I.box(45, 11, 5, W=3.0, seed=20), {}, True),
+    # no march: open in x, next-nearest neighbours, a chain
+    "open": lambda: (sheet(30, 20, 21, periodic_x=False), {}, False),
+    "nnn": lambda: (sheet(30, 20, 22, t2=-0.2), {}, False),
+    "chain": lambda: (I.chain(500, W=1.0, seed=23), {}, False),
+}
+
+
+def build(name):
+    m, opt, march = CASES[name]()
+    Hs, V, XH = O.operators(m.nn, m.nbr, m.hop, m.onsite, m.x, m.length_x)
+    dE = 1.01 * O.gershgorin_bound(Hs)
+    H = P.gpuqt_build_h_from_model(m, energy_max=dE, **opt)
+    assert (H.info.kernel_variant & MARCH == MARCH) == march, name
+    return m, H, Hs, V, XH, dE
+
+
+@pytest.mark.parametrize("B", [1, 2, 16])
+@pytest.mark.parametrize("name", list(CASES))
+def test_march_matches_oracle_and_general(gpu, name, B):
+    """Moment sets at every remainder of steps per launch, VAC and MSD rows (a step with fewer
+    terms than a launch takes and one with many), evolution with and without chi."""
+    say(f"case: march {name} B={B}")
+    m, H, Hs, V, XH, dE = build(name)
+    phi, chi = I.random_phase(m.n, B, 30), I.random_phase(m.n, B, 31)
+    d, dc = dev(phi), dev(chi)
+    dts = [0.02, 1.3]
+    both = []
+    for code in (H.info.kernel_variant, H.info.kernel_variant & ~MARCH):
+        P.gpuqt_set_variant(H, code)
+        both.append(dict(
+            **{f"mu{M}": host(P.gpuqt_moments(H, d, d, M))[0] for M in (1, 2, 3, 8, 17, 18, 21, 64)},
+            vac=host(P.gpuqt_vac(H, d, dts, 24)), msd=host(P.gpuqt_msd(H, d, dts, 24)),
+            one=host(P.gpuqt_evolve(H, d, -0.9)), np1=host(P.gpuqt_evolve(H, d, 0.9, Np=1)),
+            zero=host(P.gpuqt_evolve(H, d, 0.9, with_commutator=True)[1]),
+            chi=host(P.gpuqt_evolve(H, d, 0.9, chi=dc, with_commutator=True)[1])))
+    for k in both[0]:
+        assert err(both[0][k], both[1][k]) < TOL, k
+    got = both[0]
+    for M in (1, 2, 3, 8, 17, 18, 21, 64):
+        assert err(got[f"mu{M}"], O.chebyshev_moments(Hs / dE, phi, phi, M).T) < TOL, M
+    for k in range(2):
+        assert err(got["vac"][k, 0], O.vac_moments(Hs, V, phi, dts, dE, 24)[k].T) < TOL, k
+        assert err(got["msd"][k, 0], O.msd_moments(Hs, XH, phi, dts, dE, 24)[k].T) < TOL, k
+    assert err(got["one"], O.evolve(Hs / dE, phi, -0.9, dE)) < TOL
+    assert err(got["zero"], O.commutator_evolve(Hs / dE, XH / dE, phi, 0.9, dE)) < TOL
+
+
+@pytest.mark.parametrize("B", [1, 4])
+def test_march_segments(gpu, B):
+    """Uneven segments of squares (each with its own DeltaE) and of brick lattices in one launch."""
+    say(f"case: march segments B={B}")
+    sets = [[sheet(37, 5, 40), sheet(130, 21, 41), sheet(3, 3, 42), sheet(50, 64, 43)],
+            [I.honeycomb(10, 8, flux=1 / 40, W=1.0, seed=44), I.honeycomb(31, 14, flux=1 / 217, W=1.0, seed=45)]]
+    for mods in sets:
+        cat = I.concat_segments(mods)
+        offs = np.cumsum([0] + [mm.n for mm in mods])
+        ops = [O.operators(mm.nn, mm.nbr, mm.hop, mm.onsite, mm.x, mm.length_x) for mm in mods]
+        dEs = [1.01 * O.gershgorin_bound(o[0]) for o in ops]
+        H = P.gpuqt_build_h(cat.nn, cat.nbr, cat.hop, cat.onsite, cat.x, 0.0, cat.volume, 0.0, seg_offsets=offs,
+                            seg_energy_max=dEs, seg_length_x=[mm.length_x for mm in mods])
+        assert H.info.kernel_variant & MARCH == MARCH
+        phi = np.concatenate([I.random_phase(mm.n, B, 50 + s) for s, mm in enumerate(mods)], axis=0)
+        mu = host(P.gpuqt_moments(H, dev(phi), dev(phi), 50))
+        vac, msd = host(P.gpuqt_vac(H, dev(phi), [0.6, 0.6], 20)), host(P.gpuqt_msd(H, dev(phi), [0.6], 20))
+        for s, (Hs, V, XH) in enumerate(ops):
+            ph = phi[offs[s]:offs[s + 1]]
+            assert err(mu[s], O.chebyshev_moments(Hs / dEs[s], ph, ph, 50).T) < TOL, s
+            assert err(vac[1, s], O.vac_moments(Hs, V, ph, [0.6, 0.6], dEs[s], 20)[1].T) < TOL, s
+            assert err(msd[0, s], O.msd_moments(Hs, XH, ph, [0.6], dEs[s], 20)[0].T) < TOL, s
+
+
+def test_march_falls_back(gpu):
+    """Slots that differ from row to row with per-entry hoppings, positions that are no lattice's
+    (no MSD march) and a workspace of the general kernels' size: right results all the same."""
+    import torch
+    say("case: march fallbacks")
+    m = I.bond_disorder(sheet(30, 18, 60), 0.2, 61, max_phase=0.4)
+    order = np.argsort(np.random.default_rng(62).random((m.n, 4)), axis=1)
+    m.nbr, m.hop = np.take_along_axis(m.nbr, order, 1), np.take_along_axis(m.hop, order, 1)
+    H = P.gpuqt_build_h_from_model(m, no_dictionary=True)
+    assert H.info.kernel_variant & MARCH == 0
+    m = sheet(40, 30, 63)
+    m.x = m.x + 0.01 * np.random.default_rng(64).random(m.n)
+    Hs, V, XH = O.operators(m.nn, m.nbr, m.hop, m.onsite, m.x, m.length_x)
+    H = P.gpuqt_build_h_from_model(m)
+    assert H.info.kernel_variant & MARCH == 1 << 26
+    dE, phi = float(H.energy_max[0]), I.random_phase(m.n, 2, 65)
+    assert err(host(P.gpuqt_msd(H, dev(phi), [0.7], 20))[0, 0], O.msd_moments(Hs, XH, phi, [0.7], dE, 20)[0].T) < TOL
+    assert err(host(P.gpuqt_vac(H, dev(phi), [0.7, 0.7], 20))[1, 0],
+               O.vac_moments(Hs, V, phi, [0.7, 0.7], dE, 20)[1].T) < TOL
+    full = P.gpuqt_workspace_size(H, P.OP_VAC, 2, 20, 40)
+    small = full - -(-m.n * 2 * 16 // 256) * 256       # one vector less
+    ws = torch.empty(small, dtype=torch.uint8, device="cuda")
+    assert err(host(P.gpuqt_vac(H, dev(phi), [0.7, 0.7], 20, Np=40, ws=ws))[1, 0],
+               O.vac_moments(Hs, V, phi, [0.7, 0.7], dE, 20)[1].T) < TOL
