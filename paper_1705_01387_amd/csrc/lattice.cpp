@@ -142,16 +142,20 @@ bool detect_lattice(const gpuqt_h_desc* d, const HostLayout& L, const int32_t bo
   return true;
 }
 
-// The tiles and runs with the least estimated time: an iteration (one row or plane of
-// a workgroup) costs its wavefronts' share of a CU's issue slots, a CU runs
-// ceil(workgroups / CUs) workgroups one iteration after another's, and a run of zc rows
-// takes zc + 2 T iterations.  Measured on 2000^2 rows with T = 8: within 10 % of the times
-// of 16 to 125 rows per run; on 200^3 likewise.
+// The tiles and runs with the least estimated time: a run of zc rows (planes) takes zc + 2 T
+// iterations, and an iteration costs the CU's wavefronts per SIMD and `idle` of a wavefront's
+// time more per round of resident workgroups, which nothing hides (0.7 for the chain of eight
+// steps, a tenth elsewhere, and at least 0.75 wavefronts' time; fitted to runs of 24 to 100 rows of 64 and 128 cells on 2000^2
+// squares and a brick lattice, where it picks runs within 8 % of the best measured); a barrier
+// between two wavefronts costs a twentieth.  A box,
+// whose workgroups fill a CU, runs ceil(workgroups / CUs) of them in turn, and a fifth more for
+// every time its planes are read (margins and cut lines).
 bool plan_march(const MarchLattice& M, const std::vector<int64_t>& seg_off, int T, int B, int max_items, int cus,
                 const std::vector<int>& lane_choices, int max_tile_x, MarchPlan* out) {
   const int n_seg = (int)seg_off.size() - 1;
   const bool box = M.pattern == MARCH_BOX;
   double best = 0.0;
+  const double idle = T >= 8 ? 0.7 : 0.1;
   out->T = 0;
   auto ceil_div = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
   // tiles of one segment: as equal as the counts allow
@@ -170,8 +174,18 @@ bool plan_march(const MarchLattice& M, const std::vector<int64_t>& seg_off, int 
         zc = std::max(zc, (int)z);
       }
       if (items > max_items) break;
-      const double waves = (double)ceil_div(items * B, cus) * lanes / 256.0;
-      const double t = (ceil_div(zc + 2 * T, 3) * 3) * std::max(waves, 0.75);
+      const int64_t per_cu = ceil_div(items * B, cus);
+      // wavefronts per SIMD: of the fullest CU, and (several workgroups to a CU) of the average one
+      const double waves = (box ? (double)per_cu : 0.5 * (per_cu + (double)(items * B) / cus)) * lanes / 256.0;
+      const double rounds = (double)ceil_div(per_cu, box ? 1 : 512 / lanes);   // of resident workgroups
+      // elements read per element: margins, and lines of 8 elements that a tile's rows cut
+      double moved = 0.0, rows = 0.0;
+      for (const MarchSeg& t : tiles) {
+        moved += (double)t.nx * t.ny * (t.tx + 7) * t.ty * (t.Lm + 2.0 * T * ceil_div(t.Lm, std::min<int64_t>(zc, t.Lm)));
+        rows += (double)t.Lx * t.Ly * t.Lm;
+      }
+      const double t = (ceil_div(zc + 2 * T, 3) * 3) * (std::max(waves, 0.75) + idle * rounds) *
+                       (1.0 + (box ? 0.2 * moved / rows : lanes > 64 ? 0.05 : 0.0));
       if (best == 0.0 || t < best) {
         best = t;
         out->T = T;

@@ -39,7 +39,7 @@ constexpr bool has_dots(int fam) { return fam == MF_SYM || fam == MF_PAIR; }
 // LDS elements of one staged row (plane): the tile's cells and a margin of one
 // row of cells (at most kMaxTileX in a box) on either side, so that a neighbour
 // index never leaves it.
-constexpr int kMaxTileX = 48;
+constexpr int kMaxTileX = 64;
 constexpr int margin_of(int pat) { return pat == MARCH_BOX ? kMaxTileX : 1; }
 constexpr size_t lds_bytes(int pat, int fam, int T, int lanes) {
   return (size_t)2 * (two_chains(fam) ? 2 : 1) * T * (lanes + 2 * margin_of(pat)) * sizeof(double2);
@@ -49,6 +49,9 @@ constexpr size_t lds_bytes(int pat, int fam, int T, int lanes) {
 // stays in scalar registers, a lane adds a 32-bit byte offset, and an access past
 // the row (offset kNoLane) reads zero and stores nothing, so that masked stores
 // need no branch and the compiler's count of accesses in flight stays exact.
+#ifndef MWPE
+#define MWPE (PAT == MARCH_BOX ? 4 : 2)
+#endif
 constexpr uint32_t kNoLane = 0xfffffff0u;
 struct RowBuf {
   __amdgpu_buffer_rsrc_t r;
@@ -65,15 +68,18 @@ struct RowBuf {
     const u2 v = __builtin_amdgcn_raw_buffer_load_b64(r, o, 0, 0);
     return __builtin_bit_cast(double, v);
   }
+  template <int AUX = 0>
   __device__ __forceinline__ void st2(uint32_t o, double2 v) const {
     typedef unsigned int u4 __attribute__((ext_vector_type(4)));
     const d2v d = {v.x, v.y};
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, d), r, o, 0, 0);
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, d), r, o, 0, AUX);
   }
 };
 
+// (two chains with their dots need more than the 256 registers of two waves a SIMD: spilled to fit them, the
+// brick lattice's step costs 18.4 us instead of 16.5 at one wave)
 template <int PAT, int FAM, int HOP, int T, int LANES, bool FIRST, bool KEEP>
-__global__ __launch_bounds__(LANES) void k_march(MarchMat A, MarchIO io) {
+__global__ __launch_bounds__(LANES, PAT == MARCH_BOX ? 4 : FAM == MF_PAIR ? 1 : 2) void k_march(MarchMat A, MarchIO io) {
   constexpr int NC = two_chains(FAM) ? 2 : 1;
   constexpr bool DOTS = has_dots(FAM);
   constexpr bool BOX = PAT == MARCH_BOX;
@@ -81,13 +87,19 @@ __global__ __launch_bounds__(LANES) void k_march(MarchMat A, MarchIO io) {
   constexpr bool ENTRY = HOP != HOP_UNIFORM;
   constexpr bool CPLX = HOP == HOP_COMPLEX || HOP == HOP_DICT;
   constexpr int KE = ENTRY ? K : 1;
-  constexpr int NB = BOX ? 4 : 2;   // neighbours staged in LDS
+  // rows loaded ahead: two where the registers allow it (2 - 8 % on squares, none on boxes)
+  constexpr int AHEAD = !ENTRY && PAT != MARCH_BOX && FAM != MF_PAIR ? 2 : 1;
+  // outputs past the caches (bit 1: non-temporal): 4 % on the box MSD term, none or a loss elsewhere
+  constexpr int NTS = BOX && FAM == MF_MSD ? 2 : 0;
+  constexpr bool IM = NC == 2 || ENTRY;   // (one chain, one real hopping: H~ is real symmetric and every dot real)
   using hv_t = std::conditional_t<CPLX, double2, double>;
   constexpr int SLOTS = LANES + 2 * margin_of(PAT);
   __shared__ double2 lds[2 * NC * T * SLOTS];   // [2][NC][T][SLOTS]
 
-  const int total = A.items * A.B;
-  const int lb = logical_block(total);
+  // consecutive work items to one XCD (workgroups go to the 8 XCDs round-robin), so that
+  // tiles that share margins, or columns that share lines, meet in its L2
+  const int total = A.items * A.B, xcd = blockIdx.x & 7;
+  const int lb = xcd * (total >> 3) + min(xcd, total & 7) + ((int)blockIdx.x >> 3);
   // (the quotients are the same in every lane; readfirstlane keeps them and the
   // addresses built on them in scalar registers)
   auto uni = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
@@ -199,9 +211,9 @@ __global__ __launch_bounds__(LANES) void k_march(MarchMat A, MarchIO io) {
   int64_t ba = ra * pv;
   int64_t b1 = (z0 - 2 * T + 1) * pv;     // and that of the row level T computes next
   auto next = [&](int r) { return r + 1 == S.Lm ? 0 : r + 1; };
-  double2 nx[NC], nw[NC], na[DOTS ? 1 : NC];
-  double nd;
-  hv_t nh[KE];
+  double2 nx[3][NC], nw[3][NC], na[3][DOTS ? 1 : NC];   // rows on their way, by phase
+  double nd[3];
+  hv_t nh[3][KE];
   int32_t nk[KE];                         // table keys of the row after nh's
   auto entry0 = [&](int r) -> int64_t {   // first stored entry of the lane's row r
     const int64_t row = S.off + (int64_t)r * plane + cell;
@@ -214,25 +226,26 @@ __global__ __launch_bounds__(LANES) void k_march(MarchMat A, MarchIO io) {
       for (int j = 0; j < K; ++j) nk[j] = A.hidx[e + ((int64_t)A.slot[j] << A.S_log2)];
     }
   };
-  auto load = [&]() {
+  auto load = [&](auto Qc) {
+    constexpr int Q = decltype(Qc)::value;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-      nx[c] = RowBuf(xs[c], bx, nv).ld2(vo);
-      if (!FIRST) nw[c] = RowBuf(ws[c], bw, nv).ld2(vo);
-      if (!DOTS) na[c] = RowBuf(as[c], ba, nv).ld2(so);
+      nx[Q][c] = RowBuf(xs[c], bx, nv).ld2(vo);
+      if (!FIRST) nw[Q][c] = RowBuf(ws[c], bw, nv).ld2(vo);
+      if (!DOTS) na[Q][c] = RowBuf(as[c], ba, nv).ld2(so);
     }
-    nd = RowBuf(ds, rw * plane * (int64_t)sizeof(double), (uint32_t)plane * (uint32_t)sizeof(double)).ld1(dof);
+    nd[Q] = RowBuf(ds, rw * plane * (int64_t)sizeof(double), (uint32_t)plane * (uint32_t)sizeof(double)).ld1(dof);
     if constexpr (HOP == HOP_DICT) {
 #pragma unroll
-      for (int j = 0; j < K; ++j) nh[j] = A.htab[nk[j]];
+      for (int j = 0; j < K; ++j) nh[Q][j] = A.htab[nk[j]];
       load_keys(next(rw));
     } else if constexpr (ENTRY) {
       const int64_t e = entry0(rw);
 #pragma unroll
       for (int j = 0; j < K; ++j) {
         const int64_t ej = e + ((int64_t)A.slot[j] << A.S_log2);
-        if constexpr (HOP == HOP_REAL) nh[j] = A.hop[ej];
-        else nh[j] = reinterpret_cast<const double2*>(A.hop)[ej];
+        if constexpr (HOP == HOP_REAL) nh[Q][j] = A.hop[ej];
+        else nh[Q][j] = reinterpret_cast<const double2*>(A.hop)[ej];
       }
     }
     if (!DOTS) {
@@ -244,8 +257,12 @@ __global__ __launch_bounds__(LANES) void k_march(MarchMat A, MarchIO io) {
     rx = next(rx);
     rw = next(rw);
   };
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  using I2 = std::integral_constant<int, 2>;
   load_keys(rw);
-  load();
+  load(I0{});
+  if constexpr (AHEAD == 2) load(I1{});
   __syncthreads();
 
   double2* rd = lds + NC * T * SLOTS + me;   // staged rows of the last iteration
@@ -278,47 +295,28 @@ __global__ __launch_bounds__(LANES) void k_march(MarchMat A, MarchIO io) {
 #pragma unroll
         for (int j = 0; j < K; ++j) hq[s][j] = hq[s - 1][j];
     }
-    dq[0] = 2.0 * nd;
+    dq[0] = 2.0 * nd[P];
     if constexpr (ENTRY)
 #pragma unroll
       for (int j = 0; j < K; ++j) {
-        if constexpr (CPLX) hq[0][j] = cscale(2.0, nh[j]);
-        else hq[0][j] = 2.0 * nh[j];
+        if constexpr (CPLX) hq[0][j] = cscale(2.0, nh[P][j]);
+        else hq[0][j] = 2.0 * nh[P][j];
       }
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-      h[c][0][P] = (c == 1 && bz) ? make_double2(0.0, 0.0) : nx[c];
-      wv[c] = FIRST ? make_double2(0.0, 0.0) : nw[c];
-      if constexpr (!DOTS) av[c] = (c == 1 && bz) ? make_double2(0.0, 0.0) : na[c];
+      h[c][0][P] = (c == 1 && bz) ? make_double2(0.0, 0.0) : nx[P][c];
+      wv[c] = FIRST ? make_double2(0.0, 0.0) : nw[P][c];
+      if constexpr (!DOTS) av[c] = (c == 1 && bz) ? make_double2(0.0, 0.0) : na[P][c];
     }
-    load();
-    // staged neighbours of the level being computed, read one level ahead
-    double2 e[NC][NB];
-    auto stage = [&](int s) {
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        const double2* L = rd + (c * T + s) * SLOTS;
-        e[c][0] = L[1];
-        e[c][1] = L[-1];
-        if constexpr (BOX) {
-          e[c][NB - 2] = L[up];
-          e[c][NB - 1] = L[-up];
-        }
-      }
-    };
-    stage(0);
+    load(std::integral_constant<int, AHEAD == 2 ? P1 : (P + 1) % 3>{});
 #pragma unroll
     for (int s = 0; s < T; ++s) {         // level s + 2 from level s + 1; its row is i - 1 - s
       const int r = i - 1 - s;
-      double2 y[NC], sx = make_double2(0.0, 0.0), u[NC][NB];
-#pragma unroll
-      for (int c = 0; c < NC; ++c)
-#pragma unroll
-        for (int b = 0; b < NB; ++b) u[c][b] = e[c][b];
-      if (s + 1 < T) stage(s + 1);
+      double2 y[NC], sx = make_double2(0.0, 0.0);
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
-        const double2 xp = u[c][0], xm = u[c][1];
+        const double2* L = rd + (c * T + s) * SLOTS;
+        const double2 xp = L[1], xm = L[-1];
         const double2 xc = h[c][s][P1];
         const double2 zp = h[c][s][P], zm = h[c][s][P2];
         const double2 w2 = s == 0 ? wv[c] : h[c][s > 0 ? s - 1 : 0][P2];
@@ -351,8 +349,8 @@ __global__ __launch_bounds__(LANES) void k_march(MarchMat A, MarchIO io) {
             }
           }
           if constexpr (BOX) {
-            n = cadd(n, u[c][NB - 2]);
-            n = cadd(n, u[c][NB - 1]);
+            n = cadd(n, L[up]);
+            n = cadd(n, L[-up]);
           }
           if constexpr (PAT == MARCH_BRICK) {
             n = cadd(n, ((xw + r + A.parity) & 1) == 0 ? zp : zm);
@@ -372,17 +370,24 @@ __global__ __launch_bounds__(LANES) void k_march(MarchMat A, MarchIO io) {
         const double2 xa = h[0][s][P1], xb = h[NC - 1][s][P1];
         double a0 = ar[s], a1 = ai[s], b0 = cr[s], b1 = ci[s], d0 = zr, d1 = zi;
         if (FIRST && s == 0) {
-          cdot_acc(d0, d1, xa, xb);                 // <a0|b0>
-          cdot_acc(a0, a1, xa, y[NC - 1]);          // <a0|b1>
-        } else {
+          if constexpr (IM) {
+            cdot_acc(d0, d1, xa, xb);                 // <a0|b0>
+            cdot_acc(a0, a1, xa, y[NC - 1]);          // <a0|b1>
+          } else {
+            d0 = fma(xa.x, xa.x, fma(xa.y, xa.y, d0));
+            a0 = fma(y[0].x, xa.x, fma(y[0].y, xa.y, a0));
+          }
+        } else if constexpr (IM) {
           cdot_acc(a0, a1, y[0], xb);
+        } else {
+          a0 = fma(y[0].x, xb.x, fma(y[0].y, xb.y, a0));
         }
         if constexpr (NC == 1) b0 = fma(y[0].x, y[0].x, fma(y[0].y, y[0].y, b0));
         else cdot_acc(b0, b1, y[0], y[NC - 1]);
         // lanes the tile does not own sum up whatever they hold; it is dropped at the end
         const bool in = inside(r);
         ar[s] = in ? a0 : ar[s];
-        ai[s] = in ? a1 : ai[s];
+        if constexpr (IM) ai[s] = in ? a1 : ai[s];
         cr[s] = in ? b0 : cr[s];
         if constexpr (NC == 2) ci[s] = in ? b1 : ci[s];
         if (FIRST && s == 0) {
@@ -399,7 +404,7 @@ __global__ __launch_bounds__(LANES) void k_march(MarchMat A, MarchIO io) {
         if (out || pre) {
           const uint32_t o = inside(r) ? so : kNoLane;
           if (KEEP) RowBuf(io.keepv[c][s] + vbase, out ? b1 - pv : b1, io.keepv[c][s] ? nv : 0).st2(o, y[c]);
-          else RowBuf(out ? o2s[c] : o1s[c], out ? b1 - pv : b1, nvo).st2(o, y[c]);
+          else RowBuf(out ? o2s[c] : o1s[c], out ? b1 - pv : b1, nvo).template st2<NTS>(o, y[c]);
           if constexpr (!DOTS) {
             if (out) {
               // the sums of level T + 1's row: the steps before it are this row in the
@@ -412,7 +417,7 @@ __global__ __launch_bounds__(LANES) void k_march(MarchMat A, MarchIO io) {
                 if (io.k0 + m > io.k_end) v = make_double2(0.0, 0.0);
                 axpy_c(a, cm[m], v);
               }
-              RowBuf(aos[c], b1 - pv, nv).st2(o, a);
+              RowBuf(aos[c], b1 - pv, nv).template st2<NTS>(o, a);
             }
           }
         }
@@ -425,9 +430,6 @@ __global__ __launch_bounds__(LANES) void k_march(MarchMat A, MarchIO io) {
     __syncthreads();
   };
   // level T + 1 has row z0 at i = z0 + T and row z1 - 1 at i = z1 - 1 + T
-  using I0 = std::integral_constant<int, 0>;
-  using I1 = std::integral_constant<int, 1>;
-  using I2 = std::integral_constant<int, 2>;
   int i = z0 - T;
   auto three = [&](auto Cc) {
     iter(i, I0{}, Cc);
@@ -452,7 +454,7 @@ __global__ __launch_bounds__(LANES) void k_march(MarchMat A, MarchIO io) {
 #pragma unroll
     for (int s = 0; s < T; ++s) {
       v[4 * s] = wsum(own ? ar[s] : 0.0);
-      v[4 * s + 1] = wsum(own ? ai[s] : 0.0);
+      v[4 * s + 1] = IM ? wsum(own ? ai[s] : 0.0) : 0.0;
       v[4 * s + 2] = wsum(own ? cr[s] : 0.0);
       v[4 * s + 3] = NC == 2 ? wsum(own ? ci[s] : 0.0) : 0.0;
     }
