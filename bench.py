@@ -73,7 +73,7 @@ FAMILY_MARCH_BYTES = {"moment_sym": 64, "moment_pair": 128, "evolve": 96, "msd":
 FAMILY_KERNEL = {"moment": "k_moment_step", "moment_sym": "k_moment_step_sym",
                  "moment_pair": "k_moment_step_pair", "evolve": "k_evolve_term", "msd": "k_msd_term",
                  "evolve_pair": "k_evolve_pair_term"}
-KERNEL_SOURCES = ("device_common.h", "internal.h", "kernels.hip", "march.h", "march_core.h", "lattice.cpp")   # what the step kernels are built from
+KERNEL_SOURCES = ("device_common.h", "internal.h", "kernels.hip", "march.h", "march_core.h", "patch_core.h", "lattice.cpp")   # what the step kernels are built from
 
 
 def log(msg):

@@ -410,9 +410,10 @@ gpuqt_status gpuqt_vac_backward_tape_workspace_size(gpuqt_h h, int32_t B, int32_
  * period one period after another, so rows D apart are visited W rows apart);
  * bit 26: on a lattice with a fixed neighbour pattern (a periodic simple cubic box with one
  * hopping; segments that are all periodic squares; segments that are all periodic brick-wall
- * honeycombs, rows x + Lx y with the neighbours x +- 1 and one of y +- 1, Lx and Ly even),
- * natural order, the marches: several recurrence steps per launch in one sweep along the
- * slowest direction, the intermediate steps held on chip, for the moments of phiL = phiR
+ * honeycombs, rows x + Lx y with the neighbours x +- 1 and one of y +- 1, Lx and Ly even;
+ * segments that are all rings with the neighbours x +- 1), natural order, the marches:
+ * several recurrence steps per launch in one sweep along the slowest direction (rings and
+ * small lattices: in patches held whole), the intermediate steps held on chip, for the moments of phiL = phiR
  * and the VAC, MSD and evolution series; blocks of vectors are then advanced as separate
  * vectors.  Built handles of such a lattice start with bits 26 and 27 set; the autotuner
  * times the Hermitian step's march against the best general variant and keeps the faster;

@@ -16,7 +16,10 @@ BUILD_DIR = os.path.join(ROOT, "_build")
 SOURCES = ["kernels.hip", "kernels_adjoint.hip", "api.cpp", "layout.cpp", "io.cpp", "tune.cpp", "noalloc.hip",
            "lattice.cpp", "march.hip", "march_square_uniform.hip", "march_square_real.hip", "march_square_complex.hip", "march_square_dict.hip",
            "march_brick_uniform.hip", "march_brick_real.hip", "march_brick_complex.hip", "march_brick_dict.hip",
-           "march_box_uniform.hip"]
+           "march_box_uniform.hip",
+           "patch_square_uniform.hip", "patch_square_real.hip", "patch_square_complex.hip", "patch_square_dict.hip",
+           "patch_brick_uniform.hip", "patch_brick_real.hip", "patch_brick_complex.hip", "patch_brick_dict.hip",
+           "patch_chain.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I", os.path.join(ROOT, "include")]

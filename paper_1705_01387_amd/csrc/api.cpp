@@ -455,6 +455,7 @@ gpuqt_status run_march(const Handle* h, int B, int fam, int K, const double2* xa
     const bool last = q + 1 == launches;
     io.first = q == 0;
     io.k0 = 1 + q * m.T;
+    io.steps = last ? (K - q * m.T + kPatchUnroll - 1) / kPatchUnroll * kPatchUnroll : m.T;
     io.keep = keep ? 1 : 0;
     for (int c = 0; c < NC && keep; ++c) {
       for (int t = 0; t < m.T; ++t) io.keepv[c][t] = io.k0 + t <= K ? keep[c * K + io.k0 + t - 1] : nullptr;
@@ -470,7 +471,7 @@ gpuqt_status run_march(const Handle* h, int B, int fam, int K, const double2* xa
       if (last && !su->keep) su->last[c] = pool->take();
       io.acc_out[c] = last && !su->keep ? su->last[c] : su->acc[c];
     }
-    HIP_TRY(launch_march(h->lat.pattern, h->hop_mode, fam, m.lanes, A, io, s));
+    HIP_TRY(launch_march(h->lat.pattern, h->hop_mode, fam, m.lanes, m.patch, A, io, s));
     if (q == 0) {
       for (const double2* p : late) pool->give(p);
     } else if (!keep) {
@@ -914,11 +915,14 @@ gpuqt_status gpuqt_build_h(const gpuqt_h_desc* desc, void* stream, gpuqt_h* out)
       for (int lb = 0; lb < kNumB; ++lb) {
         MarchPlan mp;
         size_t o[2] = {0, 0};
-        if (sh.T > 0 && plan_march(h->lat, L.seg_off, sh.T, 1 << lb, h->G, cus, sh.lanes, sh.max_tile_x, &mp)) {
+        if (sh.T > 0) (void)plan_march(h->lat, L.seg_off, sh.T, 1 << lb, h->G, cus, sh.lanes, sh.max_tile_x, &mp);
+        (void)plan_patch(h->lat, L.seg_off, f, 1 << lb, h->G, cus, &mp);
+        if (mp.T > 0) {
           Handle::MarchDev& md = h->march[f][lb];
           md.T = mp.T;
           md.lanes = mp.lanes;
           md.items = mp.items;
+          md.patch = mp.patch;
           auto put = [&](const void* src, size_t bytes) {
             const size_t off = round_up(march_host.size(), 16);
             march_host.resize(off + bytes);
@@ -933,7 +937,7 @@ gpuqt_status gpuqt_build_h(const gpuqt_h_desc* desc, void* stream, gpuqt_h* out)
       }
     }
     up((void**)&h->d_march, march_host.data(), march_host.size());
-    if (h->lat.dx_ok) up((void**)&h->d_dxcol, h->lat.dxcol.data(), h->lat.dxcol.size() * 8);
+    if (h->lat.dx_ok && !h->lat.dxcol.empty()) up((void**)&h->d_dxcol, h->lat.dxcol.data(), h->lat.dxcol.size() * 8);
     if (!h->d_march) h->lat.pattern = MARCH_NONE;
     for (int f = 0; f < kMarchFamilies && h->d_march; ++f)
       for (int lb = 0; lb < kNumB; ++lb) {

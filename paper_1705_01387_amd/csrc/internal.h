@@ -170,7 +170,7 @@ struct Handle {
   struct MarchDev {
     const MarchSeg* segs = nullptr;
     const int32_t* item0 = nullptr;
-    int32_t T = 0, lanes = 0, items = 0;
+    int32_t T = 0, lanes = 0, items = 0, patch = 0;
   };
   MarchDev march[kMarchFamilies][kNumB];
   char* d_march = nullptr;
@@ -187,6 +187,7 @@ struct Handle {
     A.segs = m.segs;
     A.n_seg = n_seg;
     A.items = m.items;
+    A.T = m.T;
     A.B = B;
     A.parity = lat.parity;
     A.n = n;

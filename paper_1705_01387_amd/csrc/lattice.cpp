@@ -77,20 +77,35 @@ bool detect_lattice(const gpuqt_h_desc* d, const HostLayout& L, const int32_t bo
       M->dims.insert(M->dims.end(), dims, dims + 3);
     }
     M->pattern = MARCH_BRICK;
+  } else if (L.uniform_width == 2 && d->nn && d->nbr) {
+    // rings in natural order, at least three sites each
+    for (int s = 0; s < n_seg; ++s) {
+      const int64_t off = L.seg_off[s], n = L.seg_off[s + 1] - off, k = d->max_nn;
+      if (n < 3 || n > (int64_t(1) << 30)) return false;
+      for (int64_t x = 0; x < n; ++x) {
+        const int32_t* c = d->nbr + (off + x) * k;
+        const int64_t xp = off + (x + 1 == n ? 0 : x + 1), xm = off + (x == 0 ? n - 1 : x - 1);
+        if (d->nn[off + x] != 2 || !((c[0] == xp && c[1] == xm) || (c[0] == xm && c[1] == xp))) return false;
+      }
+      M->dims.insert(M->dims.end(), {(int32_t)n, 1, 1});
+    }
+    M->pattern = MARCH_CHAIN;
   } else {
     return false;
   }
   // rows (planes) of blocks of 16 vectors are addressed with 32-bit byte offsets
   for (int s = 0; s < n_seg; ++s)
-    if ((int64_t)M->dims[3 * s] * M->dims[3 * s + 1] >= (int64_t(1) << 24)) {
+    if (M->pattern != MARCH_CHAIN && (int64_t)M->dims[3 * s] * M->dims[3 * s + 1] >= (int64_t(1) << 24)) {
       M->pattern = MARCH_NONE;
       return false;
     }
   // one pass over the rows: the stored slot of each square neighbour (needed where every
   // entry has its own hopping: it must be the same on every row) and the position steps
-  const bool square = M->pattern == MARCH_SQUARE;
-  const bool slots = square && L.hop_mode != HOP_UNIFORM;
-  const int K = L.uniform_width, S = L.S;
+  const bool chain = M->pattern == MARCH_CHAIN;
+  const bool slots = (M->pattern == MARCH_SQUARE || chain) && L.hop_mode != HOP_UNIFORM;
+  const int K = L.uniform_width, ls = __builtin_ctz((unsigned)L.S);
+  auto entry = [&](int64_t r) { return ((r >> ls) * ((int64_t)K << ls)) + (r & (L.S - 1)); };
+  auto diff = [&](int64_t e) { return L.hop_mode == HOP_DICT ? L.dxtab[L.hidx[e]] : L.dx[e]; };
   bool dx_ok = true;
   size_t col0 = 0;
   for (int s = 0; s < n_seg; ++s) {
@@ -99,18 +114,23 @@ bool detect_lattice(const gpuqt_h_desc* d, const HostLayout& L, const int32_t bo
     M->dxcol.resize(col0 + Lx, 0.0);
     double* dxc = M->dxcol.data() + col0;
     col0 += Lx;
+    for (int64_t x = 0; x < Lx; ++x)
+      for (int j = 0; j < K; ++j) {
+        const int64_t e = entry(off + x) + ((int64_t)j << ls);
+        if (L.col[e] == off + (x + 1 == Lx ? 0 : x + 1)) dxc[x] = diff(e);
+      }
     for (int64_t z = 0; z < Ly * Lm; ++z) {
       const int64_t row = off + z * Lx;
       const int64_t up = off + (z + 1 == Lm ? 0 : z + 1) * Lx, dn = off + (z == 0 ? Lm - 1 : z - 1) * Lx;
       for (int64_t x = 0; x < Lx; ++x) {
-        const int64_t r = row + x, e0 = (r / S) * ((int64_t)K * S) + r % S;
+        const int64_t r = row + x, e0 = entry(r);
         const int64_t xp = row + (x + 1 == Lx ? 0 : x + 1), xm = row + (x == 0 ? Lx - 1 : x - 1);
         for (int j = 0; j < K; ++j) {
-          const int64_t e = e0 + (int64_t)j * S, c = L.col[e];
+          const int64_t e = e0 + ((int64_t)j << ls), c = L.col[e];
           if (slots) {
             const int64_t want[4] = {xp, xm, up + x, dn + x};
             int q = 0;
-            while (q < 4 && want[q] != c) ++q;
+            while (q < 4 && want[q] != c) ++q;   // (a chain's rows have only the first two)
             if (q == 4) {
               M->pattern = MARCH_NONE;
               return false;
@@ -122,22 +142,23 @@ bool detect_lattice(const gpuqt_h_desc* d, const HostLayout& L, const int32_t bo
             }
           }
           if (!dx_ok) continue;
-          const double v = L.hop_mode == HOP_DICT ? L.dxtab[L.hidx[e]] : L.dx[e];
+          const double v = diff(e);
           if (c == xp) {
-            if (z == 0) dxc[x] = v;
-            dx_ok = dx_ok && v == dxc[x];
+            dx_ok = v == dxc[x];
           } else if (c != xm) {
-            dx_ok = dx_ok && v == 0.0;
-          } else if (z > 0) {   // (row 0's +x differences are known by now)
-            dx_ok = dx_ok && v == -dxc[x == 0 ? Lx - 1 : x - 1];
+            dx_ok = v == 0.0;
+          } else {
+            dx_ok = v == -dxc[x == 0 ? Lx - 1 : x - 1];
           }
         }
       }
     }
   }
-  if (M->pattern == MARCH_BOX)   // one value in the whole box
-    for (double v : M->dxcol) dx_ok = dx_ok && v == M->dxcol[0];
   M->dx = M->dxcol[0];
+  if (M->pattern == MARCH_BOX || chain) {   // one value everywhere
+    for (double v : M->dxcol) dx_ok = dx_ok && v == M->dx;
+    M->dxcol.clear();
+  }
   M->dx_ok = dx_ok ? 1 : 0;
   return true;
 }
@@ -153,6 +174,7 @@ bool detect_lattice(const gpuqt_h_desc* d, const HostLayout& L, const int32_t bo
 bool plan_march(const MarchLattice& M, const std::vector<int64_t>& seg_off, int T, int B, int max_items, int cus,
                 const std::vector<int>& lane_choices, int max_tile_x, MarchPlan* out) {
   const int n_seg = (int)seg_off.size() - 1;
+  if (M.pattern == MARCH_CHAIN) return false;
   const bool box = M.pattern == MARCH_BOX;
   double best = 0.0;
   const double idle = T >= 8 ? 0.7 : 0.1;
@@ -248,6 +270,96 @@ bool plan_march(const MarchLattice& M, const std::vector<int64_t>& seg_off, int 
     }
   }
   return out->T > 0;
+}
+
+// The time of a launch, us: a march's run of zc + 2 T iterations with w workgroups of 128 lanes on a
+// CU, and rounds of patches of `lanes` cells, one on a CU at a time.  Fitted to 64^2 .. 724^2
+// squares, eight steps of one vector (patches measured at one and four rounds, 256^2 and 512^2: one
+// chain with dots 7.9 and 20, two with dots 11.8 and 40, two with sums 10.4 and 33; marches: one
+// chain 18 and 23, two with dots 26 and 36, two with sums 34 and 42).  So patches up to about 256^2 elements
+// x vectors in four rounds, marches beyond.
+static double march_us(const MarchPlan& p, int T, int chains, int B, int cus) {
+  int zc = 0;
+  for (const MarchSeg& s : p.segs) zc = std::max(zc, s.zc);
+  const double w = (double)p.items * B * p.lanes / 128.0 / cus;
+  return 4.0 + (zc + 2 * T) * (T >= 8 ? 0.4 + 0.28 * w : 0.2 + 0.37 * chains * w);
+}
+static double patch_us(int64_t items, int64_t per, int lanes, int family, int B, int cus) {
+  const double round = family == MF_PAIR ? 9.4 : family == MF_SYM || family == MF_EVO ? 4.1 : 7.5;
+  return 3.0 + round * (lanes / 1024.0) * (double)(per * ((items * B + cus - 1) / cus));
+}
+
+bool plan_patch(const MarchLattice& M, const std::vector<int64_t>& seg_off, int family, int B, int max_items, int cus,
+                MarchPlan* out) {
+  const int n_seg = (int)seg_off.size() - 1;
+  const int chains = family == MF_SYM || family == MF_EVO ? 1 : 2;
+  auto ceil_div = [](auto a, auto b) { return (a + b - 1) / b; };
+  const int64_t n = seg_off[n_seg];
+  // segment s in tiles of at most tx x ty cells with margins of T, several to a work item where a
+  // tile each would be more items than a workspace has partial sums for
+  auto cut = [&](int s, int T, int tx, int ty, MarchSeg* q) {
+    q->off = seg_off[s];
+    q->Lx = M.dims[3 * s];
+    q->Ly = 1;
+    q->Lm = M.dims[3 * s + 2];
+    q->nx = (int32_t)ceil_div(q->Lx, tx - 2 * T);
+    q->ux = (int32_t)ceil_div(q->Lx, q->nx);
+    q->nx = (int32_t)ceil_div(q->Lx, q->ux);
+    q->tx = q->ux + 2 * T;
+    q->ny = (int32_t)ceil_div(q->Lm, ty == 1 ? 1 : ty - 2 * T);
+    q->uy = (int32_t)ceil_div(q->Lm, q->ny);
+    q->ny = (int32_t)ceil_div(q->Lm, q->uy);
+    q->ty = ty == 1 ? 1 : q->uy + 2 * T;
+    const int64_t tiles = (int64_t)q->nx * q->ny;
+    const int64_t room = std::max<int64_t>(1, max_items * (seg_off[s + 1] - seg_off[s]) / n);
+    q->zc = tiles <= room ? 1 : (int32_t)ceil_div(tiles, room);
+    return tiles <= room ? tiles : ceil_div(tiles, (int64_t)q->zc);
+  };
+  int bT = 0, blanes = 0, btx = 0, bty = 0;
+  double best_us = out->T > 0 ? march_us(*out, out->T, chains, B, cus) / out->T : 0.0;
+  auto consider = [&](int T, int lanes, int tx, int ty) {
+    int64_t items = 0, per = 1;
+    MarchSeg q = MarchSeg();
+    for (int s = 0; s < n_seg; ++s) {
+      items += cut(s, T, tx, ty, &q);
+      per = std::max<int64_t>(per, q.zc);
+      if (items > max_items) return;
+    }
+    const double us = patch_us(items, per, lanes, family, B, cus) / T;
+    if (best_us > 0.0 && us >= best_us) return;
+    best_us = us;
+    bT = T;
+    blanes = lanes;
+    btx = tx;
+    bty = ty;
+  };
+  if (M.pattern == MARCH_CHAIN) {
+    for (int T : {24, 16, 8}) {
+      consider(T, 256, 256 * (chains == 1 ? 4 : 2), 1);
+      if (bT > 0) break;   // (more work items than partial sums: fewer steps need no more)
+    }
+  } else if (M.pattern == MARCH_SQUARE || M.pattern == MARCH_BRICK) {
+    for (int lanes : {640, 1024})
+      for (int tx = 18; tx <= 64; tx += 2)
+        if (lanes / tx > 16) consider(8, lanes, tx, lanes / tx);
+  }
+  if (bT == 0) return false;
+  *out = MarchPlan();
+  out->T = bT;
+  out->patch = 1;
+  out->lanes = blanes;
+  out->item0.assign(1, 0);
+  int32_t dx0 = 0;
+  for (int s = 0; s < n_seg; ++s) {
+    MarchSeg q = MarchSeg();
+    q.item0 = out->items;
+    out->items += (int32_t)cut(s, bT, btx, bty, &q);
+    q.dx0 = dx0;
+    dx0 += q.Lx;
+    out->segs.push_back(q);
+    out->item0.push_back(out->items);
+  }
+  return true;
 }
 
 }  // namespace gpuqt

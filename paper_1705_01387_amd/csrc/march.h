@@ -1,6 +1,6 @@
 // Lattice marches: several Chebyshev steps per launch on lattices whose rows have
-// a fixed neighbour pattern (march_core.h has the kernel; layout.cpp recognises
-// the lattices and cuts them into tiles).  Not part of the public ABI.
+// a fixed neighbour pattern (march_core.h has the marches' kernel, patch_core.h that of
+// chains and small lattices; lattice.cpp recognises the lattices and cuts them into tiles).  Not part of the public ABI.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -17,14 +17,16 @@ namespace gpuqt {
 //   SQUARE  +x, -x, +y, -y                 (segments may be squares of any sizes)
 //   BRICK   +x, -x, +y where x + y + parity is even, else -y   (honeycomb)
 //   BOX     +x, -x, +y, -y, +z, -z         (one hopping)
-enum MarchPattern { MARCH_NONE = 0, MARCH_SQUARE = 1, MARCH_BRICK = 2, MARCH_BOX = 3 };
+//   CHAIN   +x, -x
+enum MarchPattern { MARCH_NONE = 0, MARCH_SQUARE = 1, MARCH_BRICK = 2, MARCH_BOX = 3, MARCH_CHAIN = 4 };
 
 // Families of the marches: one chain with its moment dots, two chains with
 // theirs, one and two chains with their running sums (evolution), and the
 // coupled chains of the evolution + commutator series.
 enum MarchFamily { MF_SYM = 0, MF_PAIR = 1, MF_EVO = 2, MF_EVO2 = 3, MF_MSD = 4, kMarchFamilies = 5 };
 
-constexpr int kMarchMaxSteps = 8;
+constexpr int kMarchMaxSteps = 24;
+constexpr int kPatchUnroll = 4;
 
 // One segment's tiles.  The march runs along the slowest direction (Lm rows or
 // planes); a workgroup holds tx x ty cells of the other directions (ty = 1 in two
@@ -34,7 +36,7 @@ struct MarchSeg {
   int64_t off;              // first row
   int32_t Lx, Ly, Lm;       // Ly = 1 in two dimensions
   int32_t tx, ty, ux, uy;   // cells of a tile and how many of them it owns
-  int32_t nx, ny, zc;       // tiles in x and y, rows (planes) per run
+  int32_t nx, ny, zc;       // tiles in x and y; rows (planes) per run, or (patches) tiles per work item
   int32_t item0;            // first work item of the segment
   int32_t dx0;              // first column of the segment in dxcol (two dimensions)
 };
@@ -42,6 +44,7 @@ struct MarchSeg {
 // A launch plan of one family and block width: T steps per launch.
 struct MarchPlan {
   int32_t T = 0;            // 0: no march for this family
+  int32_t patch = 0;        // 1: patches (patch_core.h), 0: marches
   int32_t lanes = 0;        // threads per workgroup
   int32_t items = 0;        // work items of one vector; a launch has items x B workgroups
   std::vector<MarchSeg> segs;
@@ -66,6 +69,7 @@ struct MarchLattice {
 struct MarchMat {
   const MarchSeg* segs;
   int32_t n_seg, items, B;
+  int32_t T;                    // steps per launch (patches)
   int32_t parity;
   int64_t n;                    // rows of all segments: the stride between two vectors
   const double* diag;
@@ -90,6 +94,7 @@ struct MarchIO {
   const double2* acc_in[2];     // running sums (evolution families)
   double2* acc_out[2];
   int32_t first, k0, k_end;     // steps past k_end leave no dots and no sums
+  int32_t steps;                // patches: steps of this launch, a multiple of kPatchUnroll (<= T)
   int32_t zero_b;               // first launch: chain b starts from zero (xb not read)
   double2* part;                // dots: [row][items][B], rows 2k - 1 and 2k of step k (row 0 on the first)
   int32_t keep;                 // 1: every step's elements go to keep[chain][step - k0] (NULL: dropped)
@@ -122,8 +127,12 @@ struct MarchShape {
   int max_tile_x = 0;
 };
 MarchShape march_shape(int pattern, int hop_mode, int family);
-hipError_t launch_march(int pattern, int hop_mode, int family, int lanes, const MarchMat& A, const MarchIO& io,
-                        hipStream_t s);
+hipError_t launch_march(int pattern, int hop_mode, int family, int lanes, int patch, const MarchMat& A,
+                        const MarchIO& io, hipStream_t s);
+// Patches instead of marches where they take less time (plan_march's answer in *out, or none), for
+// two-dimensional patterns; always for a chain, which has no marches.
+bool plan_patch(const MarchLattice& M, const std::vector<int64_t>& seg_off, int family, int B, int max_items, int cus,
+                MarchPlan* out);
 // planar[c * n + r] = rows[r * B + c], and back
 hipError_t launch_to_planar(int64_t n, int B, const double2* rows, double2* planar, hipStream_t s);
 hipError_t launch_from_planar(int64_t n, int B, const double2* planar, double2* rows, hipStream_t s);

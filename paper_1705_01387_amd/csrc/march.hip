@@ -18,10 +18,23 @@ hipError_t launch_brick_real(int family, int lanes, const MarchMat& A, const Mar
 hipError_t launch_brick_complex(int family, int lanes, const MarchMat& A, const MarchIO& io, hipStream_t s);
 hipError_t launch_brick_dict(int family, int lanes, const MarchMat& A, const MarchIO& io, hipStream_t s);
 hipError_t launch_box_uniform(int family, int lanes, const MarchMat& A, const MarchIO& io, hipStream_t s);
+hipError_t patch_square_uniform(int family, int lanes, const MarchMat& A, const MarchIO& io, hipStream_t s);
+hipError_t patch_square_real(int family, int lanes, const MarchMat& A, const MarchIO& io, hipStream_t s);
+hipError_t patch_square_complex(int family, int lanes, const MarchMat& A, const MarchIO& io, hipStream_t s);
+hipError_t patch_square_dict(int family, int lanes, const MarchMat& A, const MarchIO& io, hipStream_t s);
+hipError_t patch_brick_uniform(int family, int lanes, const MarchMat& A, const MarchIO& io, hipStream_t s);
+hipError_t patch_brick_real(int family, int lanes, const MarchMat& A, const MarchIO& io, hipStream_t s);
+hipError_t patch_brick_complex(int family, int lanes, const MarchMat& A, const MarchIO& io, hipStream_t s);
+hipError_t patch_brick_dict(int family, int lanes, const MarchMat& A, const MarchIO& io, hipStream_t s);
+hipError_t patch_chain_uniform(int family, int lanes, const MarchMat& A, const MarchIO& io, hipStream_t s);
+hipError_t patch_chain_real(int family, int lanes, const MarchMat& A, const MarchIO& io, hipStream_t s);
+hipError_t patch_chain_complex(int family, int lanes, const MarchMat& A, const MarchIO& io, hipStream_t s);
+hipError_t patch_chain_dict(int family, int lanes, const MarchMat& A, const MarchIO& io, hipStream_t s);
 }  // namespace march
 
 MarchShape march_shape(int pattern, int hop_mode, int family) {
   MarchShape m;
+  if (pattern == MARCH_CHAIN) return m;   // patches only
   m.T = march::steps_of(pattern, hop_mode, family);
   m.max_tile_x = march::kMaxTileX;
   if (pattern == MARCH_BOX) m.lanes = {1024};
@@ -29,8 +42,25 @@ MarchShape march_shape(int pattern, int hop_mode, int family) {
   return m;
 }
 
-hipError_t launch_march(int pattern, int hop_mode, int family, int lanes, const MarchMat& A, const MarchIO& io,
-                        hipStream_t s) {
+hipError_t launch_march(int pattern, int hop_mode, int family, int lanes, int patch, const MarchMat& A,
+                        const MarchIO& io, hipStream_t s) {
+  if (patch) {
+    switch (pattern * 4 + hop_mode) {
+      case MARCH_SQUARE * 4 + HOP_UNIFORM: return march::patch_square_uniform(family, lanes, A, io, s);
+      case MARCH_SQUARE * 4 + HOP_REAL: return march::patch_square_real(family, lanes, A, io, s);
+      case MARCH_SQUARE * 4 + HOP_COMPLEX: return march::patch_square_complex(family, lanes, A, io, s);
+      case MARCH_SQUARE * 4 + HOP_DICT: return march::patch_square_dict(family, lanes, A, io, s);
+      case MARCH_BRICK * 4 + HOP_UNIFORM: return march::patch_brick_uniform(family, lanes, A, io, s);
+      case MARCH_BRICK * 4 + HOP_REAL: return march::patch_brick_real(family, lanes, A, io, s);
+      case MARCH_BRICK * 4 + HOP_COMPLEX: return march::patch_brick_complex(family, lanes, A, io, s);
+      case MARCH_BRICK * 4 + HOP_DICT: return march::patch_brick_dict(family, lanes, A, io, s);
+      case MARCH_CHAIN * 4 + HOP_UNIFORM: return march::patch_chain_uniform(family, lanes, A, io, s);
+      case MARCH_CHAIN * 4 + HOP_REAL: return march::patch_chain_real(family, lanes, A, io, s);
+      case MARCH_CHAIN * 4 + HOP_COMPLEX: return march::patch_chain_complex(family, lanes, A, io, s);
+      case MARCH_CHAIN * 4 + HOP_DICT: return march::patch_chain_dict(family, lanes, A, io, s);
+      default: return hipErrorInvalidValue;
+    }
+  }
   switch (pattern * 4 + hop_mode) {
     case MARCH_SQUARE * 4 + HOP_UNIFORM: return march::launch_square_uniform(family, lanes, A, io, s);
     case MARCH_SQUARE * 4 + HOP_REAL: return march::launch_square_real(family, lanes, A, io, s);

@@ -45,6 +45,39 @@ constexpr size_t lds_bytes(int pat, int fam, int T, int lanes) {
   return (size_t)2 * (two_chains(fam) ? 2 : 1) * T * (lanes + 2 * margin_of(pat)) * sizeof(double2);
 }
 
+// Sums over the wavefront of N values a lane holds (N a power of two, at most 64): while
+// more than one is left, a lane hands half of them to the lane `off` away and takes that
+// lane's other half, so that N values cost N - 1 exchanges (not 6 N); the last steps add the
+// copies up.  Afterwards lane l holds the sum of value wave_slot<N>(l) of all lanes.
+// (A bit select, not a conditional: that becomes an index into v, a chain of compares.)
+template <int N>
+__device__ __forceinline__ double wave_sums(double (&v)[N]) {
+  const int lane = threadIdx.x & 63;
+  int off = 32;
+#pragma unroll
+  for (int half = N / 2; half >= 1; half >>= 1, off >>= 1) {
+    const uint32_t m32 = (lane & off) ? 0xffffffffu : 0u;
+    const uint64_t m = ((uint64_t)m32 << 32) | m32;
+#pragma unroll
+    for (int i = 0; i < half; ++i) {
+      const uint64_t lo = __builtin_bit_cast(uint64_t, v[i]), hi = __builtin_bit_cast(uint64_t, v[i + half]);
+      const double keep = __builtin_bit_cast(double, (hi & m) | (lo & ~m));
+      const double give = __builtin_bit_cast(double, (lo & m) | (hi & ~m));
+      v[i] = keep + __shfl_xor(give, off);
+    }
+  }
+#pragma unroll
+  for (; off >= 1; off >>= 1) v[0] += __shfl_xor(v[0], off);
+  return v[0];
+}
+template <int N>
+__device__ __forceinline__ int wave_slot(int lane) {
+  int i = 0, off = 32;
+#pragma unroll
+  for (int half = N / 2; half >= 1; half >>= 1, off >>= 1) i |= (lane & off) ? half : 0;
+  return i;
+}
+
 // One row (plane) of a vector as a buffer: its base is the same in every lane and
 // stays in scalar registers, a lane adds a 32-bit byte offset, and an access past
 // the row (offset kNoLane) reads zero and stores nothing, so that masked stores
@@ -441,28 +474,23 @@ __global__ __launch_bounds__(LANES, PAT == MARCH_BOX ? 4 : FAM == MF_PAIR ? 1 : 
   while (i + 2 <= z1) three(std::false_type{});
   while (i < z1 + T) three(std::true_type{});
   if constexpr (DOTS) {
-    // one partial per dot and workgroup: wavefront butterfly, then the wavefronts in order
+    // one partial per dot and workgroup: the wavefront's sums, then the wavefronts in order
     double* red = reinterpret_cast<double*>(lds);
-    const int wave = l >> 6, nw2 = LANES >> 6;
-    auto wsum = [](double v) {
+    const int wave = l >> 6, lane = l & 63, nw2 = LANES >> 6;
+    constexpr int ND = 4 * T + 2, N = ND <= 16 ? 16 : ND <= 32 ? 32 : 64;
+    double v[N];
 #pragma unroll
-      for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
-      return v;
-    };
-    constexpr int ND = 4 * T + 2;
-    double v[ND];
-#pragma unroll
-    for (int s = 0; s < T; ++s) {
-      v[4 * s] = wsum(own ? ar[s] : 0.0);
-      v[4 * s + 1] = IM ? wsum(own ? ai[s] : 0.0) : 0.0;
-      v[4 * s + 2] = wsum(own ? cr[s] : 0.0);
-      v[4 * s + 3] = NC == 2 ? wsum(own ? ci[s] : 0.0) : 0.0;
+    for (int s = 0; s < N / 4; ++s) {
+      v[4 * s] = s < T && own ? ar[s < T ? s : 0] : 0.0;
+      v[4 * s + 1] = s < T && own ? ai[s < T ? s : 0] : 0.0;
+      v[4 * s + 2] = s < T && own ? cr[s < T ? s : 0] : 0.0;
+      v[4 * s + 3] = s < T && own ? ci[s < T ? s : 0] : 0.0;
     }
-    v[4 * T] = wsum(own ? zr : 0.0);
-    v[4 * T + 1] = wsum(own ? zi : 0.0);
-    if ((l & 63) == 0)
-#pragma unroll
-      for (int d = 0; d < ND; ++d) red[wave * ND + d] = v[d];
+    v[4 * T] = own ? zr : 0.0;
+    v[4 * T + 1] = own ? zi : 0.0;
+    const double z = wave_sums<N>(v);
+    const int d = wave_slot<N>(lane);
+    if ((lane & (64 / N - 1)) == 0 && d < ND) red[wave * ND + d] = z;
     __syncthreads();
     if (l < 2 * T + 1) {
       double re = 0.0, im = 0.0;

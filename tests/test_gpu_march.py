@@ -35,8 +35,21 @@ def sheet(Lx, Ly, seed, **kw):
     return I.square(Lx, Ly, W=2.0, seed=seed, **kw)
 
 
-# name: (model, build options, march expected).  Tiles own 64 - 2 T or 128 - 2 T cells of a row (T = 8: 48 and
-# 112) or, in a box, tiles of at most 1024 cells with margins of T.
+def shuffled(m, seed):
+    order = np.argsort(np.random.default_rng(seed).random(m.nbr.shape), axis=1)
+    m.nbr = np.take_along_axis(m.nbr, order, 1)
+    m.hop = None if m.hop is None else np.take_along_axis(m.hop, order, 1)
+    return m
+
+
+def twisted(m, phase=0.3):
+    m.hop = np.tile(np.array([np.exp(1j * phase), np.exp(-1j * phase), -1.0, -1.0]), (m.n, 1))
+    return m
+
+
+# name: (model, build options, march expected).  These squares and brick lattices are small enough for
+# patches (at most 1024 cells with margins of 8) at every block width; a box has tiles of at most 1024
+# cells with margins of T.
 CASES = {
     "square48x40": lambda: (sheet(48, 40, 1), {}, True),
     "square49x3": lambda: (sheet(49, 3, 2), {}, True),
@@ -55,10 +68,18 @@ CASES = {
     "box26x27x9": lambda: (I.box(26, 27, 9, W=3.0, seed=17), {}, True),
     "box3x4x30": lambda: (I.box(3, 4, 30, W=3.0, seed=18, slot_seed=19), {}, True),
     "box45x11x5": lambda: (I.box(45, 11, 5, W=3.0, seed=20), {}, True),
-    # no march: open in x, next-nearest neighbours, a chain
+    # chains: patches of 1024 (one chain of the recurrence) or 512 cells with margins of 24
+    "chain976": lambda: (I.chain(976, W=1.0, seed=23), {}, True),
+    "chain2465": lambda: (shuffled(I.chain(2465, W=1.0, seed=24), 25), {}, True),
+    "chain3": lambda: (I.chain(3, W=1.0, seed=26), {}, True),
+    "chain_real_entries": lambda: (I.bond_disorder(I.chain(1400, W=1.0, seed=27), 0.2, 28),
+                                   dict(no_dictionary=True), True),
+    "chain_complex_table": lambda: (I.bond_disorder(I.chain(465, W=1.0, seed=29), 0.2, 30, max_phase=0.5), {}, True),
+    "chain_complex_entries": lambda: (I.bond_disorder(I.chain(977, W=1.0, seed=31), 0.2, 32, max_phase=0.5),
+                                      dict(no_dictionary=True), True),
+    # no march: open in x, next-nearest neighbours
     "open": lambda: (sheet(30, 20, 21, periodic_x=False), {}, False),
     "nnn": lambda: (sheet(30, 20, 22, t2=-0.2), {}, False),
-    "chain": lambda: (I.chain(500, W=1.0, seed=23), {}, False),
 }
 
 
@@ -102,11 +123,53 @@ def test_march_matches_oracle_and_general(gpu, name, B):
     assert err(got["zero"], O.commutator_evolve(Hs / dE, XH / dE, phi, 0.9, dE)) < TOL
 
 
+# Marches: tiles own 64 - 2 T or 128 - 2 T cells of a row (T = 8: 48 and 112, 5: 54 and 118).
+LARGE = {
+    "square_48k": lambda: (sheet(48 * 12, 210, 70), {}),
+    "square_48k+1": lambda: (sheet(48 * 12 + 1, 203, 71), {}),
+    "square_narrow": lambda: (sheet(5, 24000, 72), {}),
+    "square_flat": lambda: (sheet(24000, 5, 73), {}),
+    "square_real_entries": lambda: (I.bond_disorder(sheet(400, 303, 74), 0.2, 75), dict(no_dictionary=True)),
+    "square_complex_table": lambda: (twisted(sheet(390, 311, 76)), {}),
+    "square_complex_entries": lambda: (I.bond_disorder(sheet(401, 300, 77), 0.2, 78, max_phase=0.5),
+                                       dict(no_dictionary=True, slice_height=32)),
+    "brick_uniform": lambda: (I.honeycomb(120, 480, W=2.0, seed=79), {}),
+    "brick_flux_table": lambda: (I.honeycomb(125, 486, flux=1 / (125 * 486), W=2.0, seed=80), {}),
+    "brick_complex_entries": lambda: (I.honeycomb(130, 440, flux=1 / 57200, W=2.0, seed=81), dict(no_dictionary=True)),
+    "brick_real_entries": lambda: (I.bond_disorder(I.honeycomb(118, 500, W=1.0, seed=82), 0.3, 83),
+                                   dict(no_dictionary=True)),
+    "chain": lambda: (I.chain(1200001, W=1.0, seed=84), {}),   # several patches to a workgroup
+}
+
+
+@pytest.mark.parametrize("name", list(LARGE))
+def test_march_large_matches_general(gpu, name):
+    """Lattices too large for patches, against the general kernels."""
+    m, opt = LARGE[name]()
+    B = 2 if name == "chain" else 16
+    say(f"case: march large {name} n={m.n} B={B}")
+    H = P.gpuqt_build_h_from_model(m, **opt)
+    code = H.info.kernel_variant
+    assert code & MARCH == MARCH
+    d, dc = dev(I.random_phase(m.n, B, 85)), dev(I.random_phase(m.n, B, 86))
+    both = []
+    for c in (code, code & ~MARCH):
+        P.gpuqt_set_variant(H, c)
+        both.append(dict(
+            **{f"mu{M}": host(P.gpuqt_moments(H, d, d, M)) for M in (3, 21, 50)},
+            vac=host(P.gpuqt_vac(H, d, [0.02, 1.3], 24)), msd=host(P.gpuqt_msd(H, d, [0.02, 1.3], 24)),
+            one=host(P.gpuqt_evolve(H, d, -0.9)),
+            chi=host(P.gpuqt_evolve(H, d, 0.9, chi=dc, with_commutator=True)[1])))
+    for k in both[0]:
+        assert err(both[0][k], both[1][k]) < TOL, k
+
+
 @pytest.mark.parametrize("B", [1, 4])
 def test_march_segments(gpu, B):
     """Uneven segments of squares (each with its own DeltaE) and of brick lattices in one launch."""
     say(f"case: march segments B={B}")
     sets = [[sheet(37, 5, 40), sheet(130, 21, 41), sheet(3, 3, 42), sheet(50, 64, 43)],
+            [I.chain(3, W=1.0, seed=46), I.chain(2000, W=1.0, seed=47), I.chain(977, W=1.0, seed=48)],
             [I.honeycomb(10, 8, flux=1 / 40, W=1.0, seed=44), I.honeycomb(31, 14, flux=1 / 217, W=1.0, seed=45)]]
     for mods in sets:
         cat = I.concat_segments(mods)
@@ -136,6 +199,9 @@ def test_march_falls_back(gpu):
     m.nbr, m.hop = np.take_along_axis(m.nbr, order, 1), np.take_along_axis(m.hop, order, 1)
     H = P.gpuqt_build_h_from_model(m, no_dictionary=True)
     assert H.info.kernel_variant & MARCH == 0
+    m = I.chain(700, W=1.0, seed=66)
+    m.x = m.x + 0.01 * np.random.default_rng(67).random(m.n)
+    assert P.gpuqt_build_h_from_model(m).info.kernel_variant & MARCH == 1 << 26
     m = sheet(40, 30, 63)
     m.x = m.x + 0.01 * np.random.default_rng(64).random(m.n)
     Hs, V, XH = O.operators(m.nn, m.nbr, m.hop, m.onsite, m.x, m.length_x)
