@@ -497,47 +497,112 @@ __global__ __launch_bounds__(256) void k_sigma(int mode, int n_t, const double* 
   }
 }
 
-// KPM sum of Section 3.3 for one (row r, energy e) per thread.  T_n(E~) by the
-// Chebyshev recurrence, Jackson damping g_n computed in place.
-__global__ __launch_bounds__(256) void k_kpm(int R, int M, const double* __restrict__ C, int n_E,
-                                             const double* __restrict__ E, double inv_dE,
-                                             double pref_base, int jackson, double cot_pa,
-                                             double* __restrict__ out) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
+// KPM sum of Section 3.3, one (row r, energy) per wavefront and kKpmEnergies of them in turn:
+// s = sum_n 2 g_n c_n T_n(x), the damped coefficients of kKpmTile moments at a time in LDS (g_n and its
+// sincospi once a workgroup, not once an energy).  Lane l takes the moments l + 64 i of a tile: T_{n+64} = 2
+// T_64 T_n - T_{n-64} from T_n = cos(n acos x), so no chain is longer than 16 steps (a chain over
+// all moments costs a rounding error that grows with n, and at the band's edges with n^2).
+// Bound by latency: 1001 energies, 1000 moments, one row: 200 us with a thread per energy and one chain
+// over all moments, 7.8 us so.
+constexpr int kKpmTile = 1024, kKpmEnergies = 2, kKpmWaves = 4;
+
+__global__ __launch_bounds__(64 * kKpmWaves) void k_kpm(int R, int M, const double* __restrict__ C, int n_E,
+                                                        const double* __restrict__ E, double inv_dE,
+                                                        double pref_base, int jackson, double cot_pa,
+                                                        double* __restrict__ out) {
+  __shared__ double wc[kKpmTile];
   const int r = blockIdx.y;
-  if (e >= n_E || r >= R) return;
-  const double x = E[e] * inv_dE;
-  if (!(fabs(x) < 1.0)) {
-    out[(int64_t)r * n_E + e] = __builtin_nan("");
-    return;
-  }
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int e0 = (blockIdx.x * kKpmWaves + wave) * kKpmEnergies;
   const double a = 1.0 / (M + 1);
   const double* c = C + (int64_t)r * M;
-  double t0 = 1.0, t1 = x, s = c[0];
-  for (int n = 1; n < M; ++n) {
-    double g = 1.0;
-    if (jackson) {
-      double sn, cs;
-      sincospi(n * a, &sn, &cs);
-      g = (1.0 - n * a) * cs + a * sn * cot_pa;
-    }
-    s += 2.0 * g * t1 * c[n];
-    const double t2 = 2.0 * x * t1 - t0;
-    t0 = t1;
-    t1 = t2;
+  double x[kKpmEnergies], th[kKpmEnergies], c64[kKpmEnergies], s[kKpmEnergies];
+#pragma unroll
+  for (int q = 0; q < kKpmEnergies; ++q) {
+    x[q] = e0 + q < n_E ? E[e0 + q] * inv_dE : 0.0;
+    th[q] = acos(x[q]);                      // (a NaN past the band; not used)
+    c64[q] = 2.0 * cos(64.0 * th[q]);
+    s[q] = 0.0;
   }
-  out[(int64_t)r * n_E + e] = pref_base / sqrt(1.0 - x * x) * s;
+  for (int n0 = 0; n0 < M; n0 += kKpmTile) {
+    const int m = min(kKpmTile, M - n0);
+    __syncthreads();
+    for (int i = threadIdx.x; i < m; i += 64 * kKpmWaves) {
+      const int n = n0 + i;
+      double g = n == 0 ? 1.0 : 2.0;
+      if (jackson && n > 0) {
+        double sn, cs;
+        sincospi(n * a, &sn, &cs);
+        g *= (1.0 - n * a) * cs + a * sn * cot_pa;
+      }
+      wc[i] = g * c[n];
+    }
+    __syncthreads();
+    double t[kKpmEnergies], u[kKpmEnergies];   // T_n, T_{n-64}
+#pragma unroll
+    for (int q = 0; q < kKpmEnergies; ++q) {
+      t[q] = cos((n0 + lane) * th[q]);
+      u[q] = cos((n0 + lane - 64) * th[q]);
+    }
+    for (int i = lane; i < m; i += 64) {
+      const double w = wc[i];
+#pragma unroll
+      for (int q = 0; q < kKpmEnergies; ++q) {
+        s[q] = fma(w, t[q], s[q]);
+        const double v = fma(c64[q], t[q], -u[q]);
+        u[q] = t[q];
+        t[q] = v;
+      }
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < kKpmEnergies; ++q) {
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) s[q] += __shfl_xor(s[q], off);
+    if (lane == 0 && e0 + q < n_E)
+      out[(int64_t)r * n_E + e0 + q] =
+          fabs(x[q]) < 1.0 ? pref_base / sqrt(1.0 - x[q] * x[q]) * s[q] : __builtin_nan("");
+  }
 }
 
-// Transpose of k_kpm: out[r][n] = sum_e g[r][e] pref(E_e) w_n T_n(E~_e), one (row r,
-// moment n) per thread; energies outside the band contribute nothing.
+// Transpose of k_kpm: out[r][n] = sum_e g[r][e] pref(E_e) w_n T_n(E~_e), kKpmMoments moments a
+// workgroup, its threads over the energies; energies outside the band contribute nothing.  Bound by
+// latency: 1001 energies, 512 moments: 506 us with a thread per moment, 8.0 us so (acos, the square
+// root and two cosines once for all of a workgroup's moments).
+constexpr int kKpmMoments = 8;
+
 __global__ __launch_bounds__(256) void k_kpm_adjoint(int R, int M, const double* __restrict__ g, int n_E,
                                                      const double* __restrict__ E, double inv_dE,
                                                      double pref_base, int jackson, double cot_pa,
                                                      double* __restrict__ out) {
-  const int n = blockIdx.x * blockDim.x + threadIdx.x;
-  const int r = blockIdx.y;
-  if (n >= M || r >= R) return;
+  __shared__ double sh[4][kKpmMoments];
+  const int n0 = blockIdx.x * kKpmMoments, r = blockIdx.y;
+  double s[kKpmMoments];
+#pragma unroll
+  for (int i = 0; i < kKpmMoments; ++i) s[i] = 0.0;
+  for (int e = threadIdx.x; e < n_E; e += 256) {
+    const double x = E[e] * inv_dE;
+    if (!(fabs(x) < 1.0)) continue;
+    const double th = acos(x);
+    const double f = g[(int64_t)r * n_E + e] * pref_base / sqrt(1.0 - x * x);
+    double t = cos(n0 * th), u = cos((n0 - 1) * th);
+#pragma unroll
+    for (int i = 0; i < kKpmMoments; ++i) {
+      s[i] = fma(f, t, s[i]);
+      const double v = fma(2.0 * x, t, -u);
+      u = t;
+      t = v;
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < kKpmMoments; ++i) {
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) s[i] += __shfl_xor(s[i], off);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6][i] = s[i];
+  }
+  __syncthreads();
+  const int n = n0 + threadIdx.x;
+  if (threadIdx.x >= kKpmMoments || n >= M) return;
   const double a = 1.0 / (M + 1);
   double wn = n == 0 ? 1.0 : 2.0;
   if (jackson && n > 0) {
@@ -545,13 +610,9 @@ __global__ __launch_bounds__(256) void k_kpm_adjoint(int R, int M, const double*
     sincospi(n * a, &sn, &cs);
     wn *= (1.0 - n * a) * cs + a * sn * cot_pa;
   }
-  double s = 0.0;
-  for (int e = 0; e < n_E; ++e) {
-    const double x = E[e] * inv_dE;
-    if (!(fabs(x) < 1.0)) continue;
-    s += g[(int64_t)r * n_E + e] * pref_base / sqrt(1.0 - x * x) * cos(n * acos(x));
-  }
-  out[(int64_t)r * M + n] = wn * s;
+  double v = 0.0;
+  for (int w = 0; w < 4; ++w) v += sh[w][threadIdx.x];
+  out[(int64_t)r * M + n] = wn * v;
 }
 
 // Bandwidth probe: one 16-byte element per thread over a grid that covers the
@@ -683,7 +744,8 @@ hipError_t launch_kpm(int R, int M, const double* C, int n_E, const double* E, d
   if (R <= 0 || n_E <= 0) return hipSuccess;
   const double a = 1.0 / (M + 1);
   const double cot_pa = cos(M_PI * a) / sin(M_PI * a);
-  k_kpm<<<dim3((n_E + 255) / 256, R), 256, 0, s>>>(R, M, C, n_E, E, inv_dE, pref_base, jackson, cot_pa,
+  constexpr int per = kKpmWaves * kKpmEnergies;
+  k_kpm<<<dim3((n_E + per - 1) / per, R), 64 * kKpmWaves, 0, s>>>(R, M, C, n_E, E, inv_dE, pref_base, jackson, cot_pa,
                                                    out);
   return hipGetLastError();
 }
@@ -693,7 +755,7 @@ hipError_t launch_kpm_adjoint(int R, int M, const double* g, int n_E, const doub
   if (R <= 0 || M <= 0) return hipSuccess;
   const double a = 1.0 / (M + 1);
   const double cot_pa = cos(M_PI * a) / sin(M_PI * a);
-  k_kpm_adjoint<<<dim3((M + 255) / 256, R), 256, 0, s>>>(R, M, g, n_E, E, inv_dE, pref_base, jackson,
+  k_kpm_adjoint<<<dim3((M + kKpmMoments - 1) / kKpmMoments, R), 256, 0, s>>>(R, M, g, n_E, E, inv_dE, pref_base, jackson,
                                                          cot_pa, out);
   return hipGetLastError();
 }
