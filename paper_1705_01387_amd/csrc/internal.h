@@ -190,6 +190,7 @@ struct Handle {
     A.T = m.T;
     A.B = B;
     A.parity = lat.parity;
+    A.open = lat.open;
     A.n = n;
     A.diag = d_diag;
     A.seg_hop = d_seg_hop;

@@ -55,6 +55,32 @@ bool brick_dims(const gpuqt_h_desc* d, int64_t off, int64_t n, int32_t dims[3], 
   return false;
 }
 
+// Lx of a segment of n rows that is a square open in x and periodic in y (each at least 3), its
+// neighbours in any order; 0: it is not.
+int64_t open_square(const gpuqt_h_desc* d, int64_t off, int64_t n) {
+  const int64_t k = d->max_nn;
+  if (n < 9 || d->nn[off] != 3) return 0;
+  int64_t c[3] = {d->nbr[off * k] - off, d->nbr[off * k + 1] - off, d->nbr[off * k + 2] - off};
+  std::sort(c, c + 3);   // 1, Lx, (Ly - 1) Lx
+  const int64_t Lx = c[1];
+  if (c[0] != 1 || Lx < 3 || n % Lx || n / Lx < 3) return 0;
+  const int64_t Ly = n / Lx;
+  for (int64_t y = 0; y < Ly; ++y) {
+    const int64_t row = off + y * Lx, up = off + (y + 1 == Ly ? 0 : y + 1) * Lx, dn = off + (y == 0 ? Ly - 1 : y - 1) * Lx;
+    for (int64_t x = 0; x < Lx; ++x) {
+      const int edge = (x == 0 ? 2 : 0) | (x + 1 == Lx ? 1 : 0);
+      int seen = edge;
+      const int nn = d->nn[row + x];
+      for (int j = 0; j < nn && j < 4; ++j) {
+        const int64_t q = d->nbr[(row + x) * k + j];
+        seen |= q == row + x + 1 && !(edge & 1) ? 1 : q == row + x - 1 && !(edge & 2) ? 2 : q == up + x ? 4 : q == dn + x ? 8 : 16;
+      }
+      if (seen != 15 || nn != (edge ? 3 : 4)) return 0;
+    }
+  }
+  return Lx;
+}
+
 }  // namespace
 
 bool detect_lattice(const gpuqt_h_desc* d, const HostLayout& L, const int32_t box[3],
@@ -90,6 +116,14 @@ bool detect_lattice(const gpuqt_h_desc* d, const HostLayout& L, const int32_t bo
       M->dims.insert(M->dims.end(), {(int32_t)n, 1, 1});
     }
     M->pattern = MARCH_CHAIN;
+  } else if (L.uniform_width == 0 && L.hop_mode == HOP_UNIFORM && d->max_nn >= 4 && d->nn && d->nbr) {
+    for (int s = 0; s < n_seg; ++s) {
+      const int64_t n = L.seg_off[s + 1] - L.seg_off[s], Lx = open_square(d, L.seg_off[s], n);
+      if (Lx == 0 || n > INT32_MAX) return false;
+      M->dims.insert(M->dims.end(), {(int32_t)Lx, 1, (int32_t)(n / Lx)});
+    }
+    M->pattern = MARCH_SQUARE;
+    M->open = 1;
   } else {
     return false;
   }
@@ -103,8 +137,9 @@ bool detect_lattice(const gpuqt_h_desc* d, const HostLayout& L, const int32_t bo
   // entry has its own hopping: it must be the same on every row) and the position steps
   const bool chain = M->pattern == MARCH_CHAIN;
   const bool slots = (M->pattern == MARCH_SQUARE || chain) && L.hop_mode != HOP_UNIFORM;
-  const int K = L.uniform_width, ls = __builtin_ctz((unsigned)L.S);
-  auto entry = [&](int64_t r) { return ((r >> ls) * ((int64_t)K << ls)) + (r & (L.S - 1)); };
+  const int K = M->open ? 4 : L.uniform_width, ls = __builtin_ctz((unsigned)L.S);
+  auto entry = [&](int64_t r) { return L.slice_ptr[r >> ls] + (r & (L.S - 1)); };
+  auto width = [&](int64_t r) { return M->open ? d->nn[r] : K; };
   auto diff = [&](int64_t e) { return L.hop_mode == HOP_DICT ? L.dxtab[L.hidx[e]] : L.dx[e]; };
   bool dx_ok = true;
   size_t col0 = 0;
@@ -115,7 +150,7 @@ bool detect_lattice(const gpuqt_h_desc* d, const HostLayout& L, const int32_t bo
     double* dxc = M->dxcol.data() + col0;
     col0 += Lx;
     for (int64_t x = 0; x < Lx; ++x)
-      for (int j = 0; j < K; ++j) {
+      for (int j = 0, w = width(off + x); j < w; ++j) {
         const int64_t e = entry(off + x) + ((int64_t)j << ls);
         if (L.col[e] == off + (x + 1 == Lx ? 0 : x + 1)) dxc[x] = diff(e);
       }
@@ -125,7 +160,7 @@ bool detect_lattice(const gpuqt_h_desc* d, const HostLayout& L, const int32_t bo
       for (int64_t x = 0; x < Lx; ++x) {
         const int64_t r = row + x, e0 = entry(r);
         const int64_t xp = row + (x + 1 == Lx ? 0 : x + 1), xm = row + (x == 0 ? Lx - 1 : x - 1);
-        for (int j = 0; j < K; ++j) {
+        for (int j = 0, w = width(r); j < w; ++j) {
           const int64_t e = e0 + ((int64_t)j << ls), c = L.col[e];
           if (slots) {
             const int64_t want[4] = {xp, xm, up + x, dn + x};

@@ -13,7 +13,7 @@
 namespace gpuqt {
 
 // Neighbour patterns.  Rows are (x, y[, z]) in natural order, periodic in every
-// direction.  The slots of a row, in the order the kernels name them:
+// direction (SQUARE with one hopping: or open in x).  The slots of a row, in the order the kernels name them:
 //   SQUARE  +x, -x, +y, -y                 (segments may be squares of any sizes)
 //   BRICK   +x, -x, +y where x + y + parity is even, else -y   (honeycomb)
 //   BOX     +x, -x, +y, -y, +z, -z         (one hopping)
@@ -55,6 +55,7 @@ struct MarchPlan {
 struct MarchLattice {
   int32_t pattern = MARCH_NONE;
   int32_t parity = 0;           // BRICK
+  int32_t open = 0;             // 1: no bonds between the columns Lx - 1 and 0 (SQUARE, one hopping)
   int32_t slot[6] = {0, 0, 0, 0, 0, 0};   // stored slot of each neighbour above (per-entry hoppings)
   // position differences: that of the +x neighbour of each column (dxcol, [sum of the Lx], the
   // -x neighbour of the next column having its negative), the same on every row of a
@@ -70,7 +71,7 @@ struct MarchMat {
   const MarchSeg* segs;
   int32_t n_seg, items, B;
   int32_t T;                    // steps per launch (patches)
-  int32_t parity;
+  int32_t parity, open;
   int64_t n;                    // rows of all segments: the stride between two vectors
   const double* diag;
   const double* seg_hop;        // uniform hopping per segment

@@ -82,9 +82,6 @@ __device__ __forceinline__ int wave_slot(int lane) {
 // stays in scalar registers, a lane adds a 32-bit byte offset, and an access past
 // the row (offset kNoLane) reads zero and stores nothing, so that masked stores
 // need no branch and the compiler's count of accesses in flight stays exact.
-#ifndef MWPE
-#define MWPE (PAT == MARCH_BOX ? 4 : 2)
-#endif
 constexpr uint32_t kNoLane = 0xfffffff0u;
 struct RowBuf {
   __amdgpu_buffer_rsrc_t r;
@@ -164,7 +161,9 @@ __global__ __launch_bounds__(LANES, PAT == MARCH_BOX ? 4 : FAM == MF_PAIR ? 1 : 
   bool own = l < S.tx * S.ty && txi >= T && txi < T + S.ux && X < S.Lx;
   if (BOX) own = own && tyi >= T && tyi < T + S.uy && Y < S.Ly;
   const uint32_t cell = (uint32_t)(yw * S.Lx + xw);
-  const uint32_t vo = (cell * (uint32_t)sb + (KEEP ? (uint32_t)col : 0u)) * (uint32_t)sizeof(double2), dof = cell * (uint32_t)sizeof(double);
+  // past the edge of a lattice that is open in x: elements read as zero, and no hopping keeps them so
+  const bool out = PAT == MARCH_SQUARE && !ENTRY && A.open && (X < 0 || X >= S.Lx);
+  const uint32_t vo = out ? kNoLane : (cell * (uint32_t)sb + (KEEP ? (uint32_t)col : 0u)) * (uint32_t)sizeof(double2), dof = cell * (uint32_t)sizeof(double);
   const uint32_t so = own ? vo : kNoLane;
   const int64_t plane = (int64_t)S.Lx * S.Ly;
   const uint32_t nv = (uint32_t)(plane * sb) * (uint32_t)sizeof(double2);   // bytes of a row of a vector
@@ -172,7 +171,7 @@ __global__ __launch_bounds__(LANES, PAT == MARCH_BOX ? 4 : FAM == MF_PAIR ? 1 : 
   const int me = margin_of(PAT) + l;
   const int up = BOX ? S.tx : 1;
 
-  const double hu2 = ENTRY ? 0.0 : 2.0 * A.seg_hop[sg];
+  const double hu2 = ENTRY || out ? 0.0 : 2.0 * A.seg_hop[sg];
   // position differences of this lane's x neighbours
   const double hdx = FAM == MF_MSD && BOX ? hu2 * A.dx : 0.0;
   double dxp = 0.0, dxm = 0.0;

@@ -59,7 +59,7 @@ __global__ __launch_bounds__(LANES) void k_patch(MarchMat A, MarchIO io) {
   const int l = threadIdx.x, cells = S.tx * S.ty, up = FLAT ? 0 : S.tx;
   auto wrap = [](int v, int L) { v %= L; return v < 0 ? v + L : v; };
 
-  const double hu2 = ENTRY ? 0.0 : 2.0 * A.seg_hop[sg];
+  const double hus = ENTRY ? 0.0 : 2.0 * A.seg_hop[sg];
   const int wave = l >> 6, lane = l & 63;
   for (int e = l; e < 2 * NC * SLOTS; e += LANES) (&lds[0][0][0])[e] = make_double2(0.0, 0.0);
   __syncthreads();
@@ -72,7 +72,7 @@ __global__ __launch_bounds__(LANES) void k_patch(MarchMat A, MarchIO io) {
   const int iy = uni(q / S.nx), ix = q - iy * S.nx;
   bool own[C], vert[C];
   int64_t at[C];
-  double d2[C], dxp[C], dxm[C];
+  double d2[C], hu[C], dxp[C], dxm[C];
   hv_t hop[C][ENTRY ? K : 1];
   double2 x[C][NC], w[C][NC], acc[C][DOTS ? 1 : NC];
 #pragma unroll
@@ -87,6 +87,9 @@ __global__ __launch_bounds__(LANES) void k_patch(MarchMat A, MarchIO io) {
     const int64_t row = S.off + (int64_t)yw * S.Lx + xw;
     at[j] = KEEP ? row * sb + col : (int64_t)col * A.n + row;
     d2[j] = 2.0 * A.diag[row];
+    // past the edge of a lattice that is open in x: elements start as zero, and no hopping keeps them so
+    const bool out = PAT == MARCH_SQUARE && !ENTRY && A.open && (X < 0 || X >= S.Lx);
+    hu[j] = out ? 0.0 : hus;
     if constexpr (ENTRY) {
       const int64_t e = (row >> A.S_log2) * ((int64_t)K << A.S_log2) + (row & ((1 << A.S_log2) - 1));
 #pragma unroll
@@ -104,9 +107,9 @@ __global__ __launch_bounds__(LANES) void k_patch(MarchMat A, MarchIO io) {
     }
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-      const bool z = FIRST && c == 1 && io.zero_b;
+      const bool z = out || (FIRST && c == 1 && io.zero_b);
       x[j][c] = z ? make_double2(0.0, 0.0) : io.x[c][at[j]];
-      w[j][c] = FIRST ? make_double2(0.0, 0.0) : io.w[c][at[j]];
+      w[j][c] = FIRST || out ? make_double2(0.0, 0.0) : io.w[c][at[j]];
       if constexpr (!DOTS)
         acc[j][c] = FIRST ? cscale(io.J[(int64_t)sg * io.ldJ], x[j][c]) : io.acc_in[c][at[j]];
     }
@@ -172,6 +175,7 @@ __global__ __launch_bounds__(LANES) void k_patch(MarchMat A, MarchIO io) {
             axpy(t, hop[j][K - 2], L[up]);
           }
         } else {
+          const double hu2 = PAT == MARCH_SQUARE ? hu[j] : hus;
           double2 n = cadd(xp, xm);
           if constexpr (FAM == MF_MSD) {
             if (c == 0)

@@ -36,7 +36,9 @@ def sheet(Lx, Ly, seed, **kw):
 
 
 def shuffled(m, seed):
-    order = np.argsort(np.random.default_rng(seed).random(m.nbr.shape), axis=1)
+    key = np.random.default_rng(seed).random(m.nbr.shape)
+    key[np.arange(m.nbr.shape[1]) >= m.nn[:, None]] = 2.0     # (padding stays last)
+    order = np.argsort(key, axis=1)
     m.nbr = np.take_along_axis(m.nbr, order, 1)
     m.hop = None if m.hop is None else np.take_along_axis(m.hop, order, 1)
     return m
@@ -77,8 +79,11 @@ CASES = {
     "chain_complex_table": lambda: (I.bond_disorder(I.chain(465, W=1.0, seed=29), 0.2, 30, max_phase=0.5), {}, True),
     "chain_complex_entries": lambda: (I.bond_disorder(I.chain(977, W=1.0, seed=31), 0.2, 32, max_phase=0.5),
                                       dict(no_dictionary=True), True),
-    # no march: open in x, next-nearest neighbours
-    "open": lambda: (sheet(30, 20, 21, periodic_x=False), {}, False),
+    "open48x20": lambda: (sheet(48, 20, 21, periodic_x=False), {}, True),
+    "open3x130": lambda: (sheet(3, 130, 33, periodic_x=False), {}, True),
+    "open113x3": lambda: (shuffled(sheet(113, 3, 34, periodic_x=False), 35), {}, True),
+    # no march: open in x with per-bond hoppings, next-nearest neighbours
+    "open_entries": lambda: (I.bond_disorder(sheet(30, 20, 36, periodic_x=False), 0.2, 37), {}, False),
     "nnn": lambda: (sheet(30, 20, 22, t2=-0.2), {}, False),
 }
 
@@ -138,6 +143,7 @@ LARGE = {
     "brick_complex_entries": lambda: (I.honeycomb(130, 440, flux=1 / 57200, W=2.0, seed=81), dict(no_dictionary=True)),
     "brick_real_entries": lambda: (I.bond_disorder(I.honeycomb(118, 500, W=1.0, seed=82), 0.3, 83),
                                    dict(no_dictionary=True)),
+    "open": lambda: (sheet(48 * 9 + 2, 277, 87, periodic_x=False), {}),
     "chain": lambda: (I.chain(1200001, W=1.0, seed=84), {}),   # several patches to a workgroup
 }
 
