@@ -409,7 +409,8 @@ gpuqt_status gpuqt_vac_backward_tape_workspace_size(gpuqt_h h, int32_t B, int32_
  * periods of 1024 rows or more: workgroups then sweep bands of W rows of the
  * period one period after another, so rows D apart are visited W rows apart);
  * bit 26: on a lattice with a fixed neighbour pattern (a periodic simple cubic box with one
- * hopping; segments that are all periodic squares; segments that are all periodic brick-wall
+ * hopping; segments that are all periodic squares, with next-nearest neighbours or without,
+ * or squares of one hopping open in x; segments that are all periodic brick-wall
  * honeycombs, rows x + Lx y with the neighbours x +- 1 and one of y +- 1, Lx and Ly even;
  * segments that are all rings with the neighbours x +- 1), natural order, the marches:
  * several recurrence steps per launch in one sweep along the slowest direction (rings and

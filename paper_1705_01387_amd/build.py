@@ -19,7 +19,8 @@ SOURCES = ["kernels.hip", "kernels_adjoint.hip", "api.cpp", "layout.cpp", "io.cp
            "march_box_uniform.hip",
            "patch_square_uniform.hip", "patch_square_real.hip", "patch_square_complex.hip", "patch_square_dict.hip",
            "patch_brick_uniform.hip", "patch_brick_real.hip", "patch_brick_complex.hip", "patch_brick_dict.hip",
-           "patch_chain.hip"]
+           "patch_chain.hip",
+           "patch_nnn_uniform.hip", "patch_nnn_real.hip", "patch_nnn_complex.hip", "patch_nnn_dict.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I", os.path.join(ROOT, "include")]

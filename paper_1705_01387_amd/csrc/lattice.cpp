@@ -103,6 +103,18 @@ bool detect_lattice(const gpuqt_h_desc* d, const HostLayout& L, const int32_t bo
       M->dims.insert(M->dims.end(), dims, dims + 3);
     }
     M->pattern = MARCH_BRICK;
+  } else if (L.uniform_width == 8 && d->nn && d->nbr) {
+    // row 0's neighbours sorted: 1, Lx - 1, Lx, ...; the slots, the same on every row, are checked below
+    for (int s = 0; s < n_seg; ++s) {
+      const int64_t off = L.seg_off[s], n = L.seg_off[s + 1] - off;
+      int32_t c[8];
+      std::copy(d->nbr + off * d->max_nn, d->nbr + off * d->max_nn + 8, c);
+      std::sort(c, c + 8);
+      const int64_t Lx = c[2] - off;
+      if (Lx < 3 || n % Lx || n / Lx < 3 || n > INT32_MAX) return false;
+      M->dims.insert(M->dims.end(), {(int32_t)Lx, 1, (int32_t)(n / Lx)});
+    }
+    M->pattern = MARCH_NNN;
   } else if (L.uniform_width == 2 && d->nn && d->nbr) {
     // rings in natural order, at least three sites each
     for (int s = 0; s < n_seg; ++s) {
@@ -136,7 +148,9 @@ bool detect_lattice(const gpuqt_h_desc* d, const HostLayout& L, const int32_t bo
   // one pass over the rows: the stored slot of each square neighbour (needed where every
   // entry has its own hopping: it must be the same on every row) and the position steps
   const bool chain = M->pattern == MARCH_CHAIN;
-  const bool slots = (M->pattern == MARCH_SQUARE || chain) && L.hop_mode != HOP_UNIFORM;
+  const bool diag = M->pattern == MARCH_NNN;
+  const bool slots = diag || ((M->pattern == MARCH_SQUARE || chain) && L.hop_mode != HOP_UNIFORM);
+  const int nw = diag ? 8 : 4;
   const int K = M->open ? 4 : L.uniform_width, ls = __builtin_ctz((unsigned)L.S);
   auto entry = [&](int64_t r) { return L.slice_ptr[r >> ls] + (r & (L.S - 1)); };
   auto width = [&](int64_t r) { return M->open ? d->nn[r] : K; };
@@ -162,11 +176,14 @@ bool detect_lattice(const gpuqt_h_desc* d, const HostLayout& L, const int32_t bo
         const int64_t xp = row + (x + 1 == Lx ? 0 : x + 1), xm = row + (x == 0 ? Lx - 1 : x - 1);
         for (int j = 0, w = width(r); j < w; ++j) {
           const int64_t e = e0 + ((int64_t)j << ls), c = L.col[e];
+          bool right = c == xp, left = c == xm;
           if (slots) {
-            const int64_t want[4] = {xp, xm, up + x, dn + x};
+            const int64_t want[8] = {xp, xm, up + x, dn + x, up + xp - row, up + xm - row, dn + xp - row, dn + xm - row};
             int q = 0;
-            while (q < 4 && want[q] != c) ++q;   // (a chain's rows have only the first two)
-            if (q == 4) {
+            while (q < nw && want[q] != c) ++q;   // (a chain's rows have only the first two)
+            right = q == 0 || q == 4 || q == 6;
+            left = q == 1 || q == 5 || q == 7;
+            if (q == nw) {
               M->pattern = MARCH_NONE;
               return false;
             }
@@ -178,9 +195,9 @@ bool detect_lattice(const gpuqt_h_desc* d, const HostLayout& L, const int32_t bo
           }
           if (!dx_ok) continue;
           const double v = diff(e);
-          if (c == xp) {
+          if (right) {
             dx_ok = v == dxc[x];
-          } else if (c != xm) {
+          } else if (!left) {
             dx_ok = v == 0.0;
           } else {
             dx_ok = v == -dxc[x == 0 ? Lx - 1 : x - 1];
@@ -209,7 +226,7 @@ bool detect_lattice(const gpuqt_h_desc* d, const HostLayout& L, const int32_t bo
 bool plan_march(const MarchLattice& M, const std::vector<int64_t>& seg_off, int T, int B, int max_items, int cus,
                 const std::vector<int>& lane_choices, int max_tile_x, MarchPlan* out) {
   const int n_seg = (int)seg_off.size() - 1;
-  if (M.pattern == MARCH_CHAIN) return false;
+  if (M.pattern == MARCH_CHAIN || M.pattern == MARCH_NNN) return false;
   const bool box = M.pattern == MARCH_BOX;
   double best = 0.0;
   const double idle = T >= 8 ? 0.7 : 0.1;
@@ -307,23 +324,15 @@ bool plan_march(const MarchLattice& M, const std::vector<int64_t>& seg_off, int 
   return out->T > 0;
 }
 
-// The time of a launch, us: a march's run of zc + 2 T iterations with w workgroups of 128 lanes on a
-// CU, and rounds of patches of `lanes` cells, one on a CU at a time.  Fitted to 64^2 .. 724^2
-// squares, eight steps of one vector (patches measured at one and four rounds, 256^2 and 512^2: one
-// chain with dots 7.9 and 20, two with dots 11.8 and 40, two with sums 10.4 and 33; marches: one
-// chain 18 and 23, two with dots 26 and 36, two with sums 34 and 42).  So patches up to about 256^2 elements
-// x vectors in four rounds, marches beyond.
-static double march_us(const MarchPlan& p, int T, int chains, int B, int cus) {
-  int zc = 0;
-  for (const MarchSeg& s : p.segs) zc = std::max(zc, s.zc);
-  const double w = (double)p.items * B * p.lanes / 128.0 / cus;
-  return 4.0 + (zc + 2 * T) * (T >= 8 ? 0.4 + 0.28 * w : 0.2 + 0.37 * chains * w);
-}
-static double patch_us(int64_t items, int64_t per, int lanes, int family, int B, int cus) {
-  const double round = family == MF_PAIR ? 9.4 : family == MF_SYM || family == MF_EVO ? 4.1 : 7.5;
-  return 3.0 + round * (lanes / 1024.0) * (double)(per * ((items * B + cus - 1) / cus));
-}
-
+// A CU holds one workgroup of 640 or 1024 cells at a time, so a launch costs rounds of
+// workgroups.  Chains: 24 steps.  In two dimensions eight steps where one round does (64^2, us a step
+// of one / two chains with dots in 640 cells 1.06 / 1.48, in 1024 1.28 / 1.95; 256^2 in 1024 cells 1.38 / 2.03 against
+// 2.00 / 2.69 with four steps), else four, whose smaller margins mean fewer patches (512^2: 3.2 / 4.9
+// against 4.0 / 6.2; next-nearest neighbours 4.7 / 6.7 against 6.1 / 9.3).  Where the lattice has marches
+// they are the faster beyond two rounds (two rounds, 512^2: patches 3.2 / 4.9 and with sums 3.1 / 5.2, marches
+// 3.3 / 4.8 and 3.9 / 6.1; four, 512^2 and two vectors: 5.6 / 8.9 and 4.9 / 9.5 against 4.3 / 5.8 and 5.5 / 9.4);
+// next-nearest neighbours have none, and four steps a launch beat single ones at every size (1000^2: 14.4 /
+// 21 against 22 / 33, with sums 12.5 / 20 against 28 / 45).
 bool plan_patch(const MarchLattice& M, const std::vector<int64_t>& seg_off, int family, int B, int max_items, int cus,
                 MarchPlan* out) {
   const int n_seg = (int)seg_off.size() - 1;
@@ -351,7 +360,7 @@ bool plan_patch(const MarchLattice& M, const std::vector<int64_t>& seg_off, int 
     return tiles <= room ? tiles : ceil_div(tiles, (int64_t)q->zc);
   };
   int bT = 0, blanes = 0, btx = 0, bty = 0;
-  double best_us = out->T > 0 ? march_us(*out, out->T, chains, B, cus) / out->T : 0.0;
+  int64_t brounds = 0, bitems = 0;
   auto consider = [&](int T, int lanes, int tx, int ty) {
     int64_t items = 0, per = 1;
     MarchSeg q = MarchSeg();
@@ -360,23 +369,27 @@ bool plan_patch(const MarchLattice& M, const std::vector<int64_t>& seg_off, int 
       per = std::max<int64_t>(per, q.zc);
       if (items > max_items) return;
     }
-    const double us = patch_us(items, per, lanes, family, B, cus) / T;
-    if (best_us > 0.0 && us >= best_us) return;
-    best_us = us;
+    const int64_t rounds = per * ceil_div(items * B, (int64_t)cus);
+    // among equals the narrowest for one round (64^2: 4 x 16 owned cells 1.06 us a step, 6 x 13 cells 1.18), the fewest for more
+    if (bT > 0 && (rounds > brounds || (rounds == brounds && (rounds == 1 || items >= bitems)))) return;
     bT = T;
     blanes = lanes;
     btx = tx;
     bty = ty;
+    brounds = rounds;
+    bitems = items;
   };
   if (M.pattern == MARCH_CHAIN) {
-    for (int T : {24, 16, 8}) {
-      consider(T, 256, 256 * (chains == 1 ? 4 : 2), 1);
-      if (bT > 0) break;   // (more work items than partial sums: fewer steps need no more)
+    consider(24, 256, 256 * (chains == 1 ? 4 : 2), 1);
+  } else if (M.pattern != MARCH_BOX) {
+    const int shapes[3][2] = {{8, 640}, {8, 1024}, {4, 1024}};
+    for (const auto& sh : shapes) {
+      if (bT > 0 && brounds == 1) break;
+      bT = 0;
+      for (int tx = 2 * sh[0] + 2; tx <= 64; tx += 2)
+        if (sh[1] / tx > 2 * sh[0]) consider(sh[0], sh[1], tx, sh[1] / tx);
     }
-  } else if (M.pattern == MARCH_SQUARE || M.pattern == MARCH_BRICK) {
-    for (int lanes : {640, 1024})
-      for (int tx = 18; tx <= 64; tx += 2)
-        if (lanes / tx > 16) consider(8, lanes, tx, lanes / tx);
+    if (out->T > 0 && brounds > 2) return false;
   }
   if (bT == 0) return false;
   *out = MarchPlan();

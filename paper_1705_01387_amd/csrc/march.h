@@ -18,7 +18,8 @@ namespace gpuqt {
 //   BRICK   +x, -x, +y where x + y + parity is even, else -y   (honeycomb)
 //   BOX     +x, -x, +y, -y, +z, -z         (one hopping)
 //   CHAIN   +x, -x
-enum MarchPattern { MARCH_NONE = 0, MARCH_SQUARE = 1, MARCH_BRICK = 2, MARCH_BOX = 3, MARCH_CHAIN = 4 };
+//   NNN     +x, -x, +y, -y, +x+y, -x+y, +x-y, -x-y   (squares of any sizes)
+enum MarchPattern { MARCH_NONE = 0, MARCH_SQUARE = 1, MARCH_BRICK = 2, MARCH_BOX = 3, MARCH_CHAIN = 4, MARCH_NNN = 5 };
 
 // Families of the marches: one chain with its moment dots, two chains with
 // theirs, one and two chains with their running sums (evolution), and the
@@ -56,7 +57,7 @@ struct MarchLattice {
   int32_t pattern = MARCH_NONE;
   int32_t parity = 0;           // BRICK
   int32_t open = 0;             // 1: no bonds between the columns Lx - 1 and 0 (SQUARE, one hopping)
-  int32_t slot[6] = {0, 0, 0, 0, 0, 0};   // stored slot of each neighbour above (per-entry hoppings)
+  int32_t slot[8] = {0, 0, 0, 0, 0, 0, 0, 0};   // stored slot of each neighbour above (per-entry hoppings)
   // position differences: that of the +x neighbour of each column (dxcol, [sum of the Lx], the
   // -x neighbour of the next column having its negative), the same on every row of a
   // segment, 0 for the other neighbours; in a box one value, dx
@@ -79,7 +80,7 @@ struct MarchMat {
   const uint16_t* hidx;         // table index per entry
   const double2* htab;
   int32_t S_log2, K;
-  int32_t slot[6];
+  int32_t slot[8];
   double dx;                    // BOX
   const double* dxcol;          // two dimensions
 };
@@ -131,7 +132,7 @@ MarchShape march_shape(int pattern, int hop_mode, int family);
 hipError_t launch_march(int pattern, int hop_mode, int family, int lanes, int patch, const MarchMat& A,
                         const MarchIO& io, hipStream_t s);
 // Patches instead of marches where they take less time (plan_march's answer in *out, or none), for
-// two-dimensional patterns; always for a chain, which has no marches.
+// two-dimensional patterns; chains and NNN have no marches.
 bool plan_patch(const MarchLattice& M, const std::vector<int64_t>& seg_off, int family, int B, int max_items, int cus,
                 MarchPlan* out);
 // planar[c * n + r] = rows[r * B + c], and back

@@ -26,15 +26,19 @@ hipError_t patch_brick_uniform(int family, int lanes, const MarchMat& A, const M
 hipError_t patch_brick_real(int family, int lanes, const MarchMat& A, const MarchIO& io, hipStream_t s);
 hipError_t patch_brick_complex(int family, int lanes, const MarchMat& A, const MarchIO& io, hipStream_t s);
 hipError_t patch_brick_dict(int family, int lanes, const MarchMat& A, const MarchIO& io, hipStream_t s);
+hipError_t patch_nnn_uniform(int family, int lanes, const MarchMat& A, const MarchIO& io, hipStream_t s);
 hipError_t patch_chain_uniform(int family, int lanes, const MarchMat& A, const MarchIO& io, hipStream_t s);
+hipError_t patch_nnn_real(int family, int lanes, const MarchMat& A, const MarchIO& io, hipStream_t s);
 hipError_t patch_chain_real(int family, int lanes, const MarchMat& A, const MarchIO& io, hipStream_t s);
+hipError_t patch_nnn_complex(int family, int lanes, const MarchMat& A, const MarchIO& io, hipStream_t s);
 hipError_t patch_chain_complex(int family, int lanes, const MarchMat& A, const MarchIO& io, hipStream_t s);
+hipError_t patch_nnn_dict(int family, int lanes, const MarchMat& A, const MarchIO& io, hipStream_t s);
 hipError_t patch_chain_dict(int family, int lanes, const MarchMat& A, const MarchIO& io, hipStream_t s);
 }  // namespace march
 
 MarchShape march_shape(int pattern, int hop_mode, int family) {
   MarchShape m;
-  if (pattern == MARCH_CHAIN) return m;   // patches only
+  if (pattern == MARCH_CHAIN || pattern == MARCH_NNN) return m;   // patches only
   m.T = march::steps_of(pattern, hop_mode, family);
   m.max_tile_x = march::kMaxTileX;
   if (pattern == MARCH_BOX) m.lanes = {1024};
@@ -54,9 +58,13 @@ hipError_t launch_march(int pattern, int hop_mode, int family, int lanes, int pa
       case MARCH_BRICK * 4 + HOP_REAL: return march::patch_brick_real(family, lanes, A, io, s);
       case MARCH_BRICK * 4 + HOP_COMPLEX: return march::patch_brick_complex(family, lanes, A, io, s);
       case MARCH_BRICK * 4 + HOP_DICT: return march::patch_brick_dict(family, lanes, A, io, s);
+      case MARCH_NNN * 4 + HOP_UNIFORM: return march::patch_nnn_uniform(family, lanes, A, io, s);
       case MARCH_CHAIN * 4 + HOP_UNIFORM: return march::patch_chain_uniform(family, lanes, A, io, s);
+      case MARCH_NNN * 4 + HOP_REAL: return march::patch_nnn_real(family, lanes, A, io, s);
       case MARCH_CHAIN * 4 + HOP_REAL: return march::patch_chain_real(family, lanes, A, io, s);
+      case MARCH_NNN * 4 + HOP_COMPLEX: return march::patch_nnn_complex(family, lanes, A, io, s);
       case MARCH_CHAIN * 4 + HOP_COMPLEX: return march::patch_chain_complex(family, lanes, A, io, s);
+      case MARCH_NNN * 4 + HOP_DICT: return march::patch_nnn_dict(family, lanes, A, io, s);
       case MARCH_CHAIN * 4 + HOP_DICT: return march::patch_chain_dict(family, lanes, A, io, s);
       default: return hipErrorInvalidValue;
     }

@@ -1,16 +1,17 @@
 // The patch kernel: the steps of march.h's launches for lattices too small for a
-// march to fill the chip, and for chains.  A workgroup holds a patch of cells with a
+// march to fill the chip, for chains and for squares with next-nearest neighbours.  A workgroup holds a patch of cells with a
 // margin of T cells on every side, one cell a lane, takes T steps of the recurrence on
 // it in place and writes the two last ones.  Nothing moves between the steps but the
 // cells' values through LDS (double-buffered: one barrier a step).
 //
 // What bounds it: on a small lattice the launch itself (about 4 us with its loads, stores
-// and the dots' sums) and its barriers: 8 steps of the Hermitian set on 64 x 64 take 5.5 us in
-// workgroups of 512 to 640 cells and 7.5 in 1024, where the march's run of 17 or more iterations takes 14 to
-// 16; on 256 x 256 7.9 against 18.  On a chain the vectors' traffic, two
+// and the dots' sums) and its barriers: 8 steps of the Hermitian set on 64 x 64 take 6.5 us in
+// workgroups of 640 cells, where the march's run of 17 or more iterations takes 14 to
+// 16.  On a chain the vectors' traffic, two
 // elements read and two written for 24 steps, and the double arithmetic: 8 M cells take 8.5 us a step
 // (Hermitian set, 4 cells a lane) and 18 (evolution + commutator, 2 cells a lane, 16 steps: 21) where
-// single steps take 81 and 268.
+// single steps take 81 and 268.  With next-nearest neighbours the LDS reads (eight a cell and step): 512 x 512
+// 4.7 us a step where single steps take 7.6 (Hermitian set), 6.7 and 9.9 (two chains).
 #pragma once
 
 #include "march_core.h"
@@ -27,12 +28,13 @@ __global__ __launch_bounds__(LANES) void k_patch(MarchMat A, MarchIO io) {
   constexpr int NC = two_chains(FAM) ? 2 : 1;
   constexpr bool DOTS = has_dots(FAM);
   constexpr bool FLAT = PAT == MARCH_CHAIN;
-  constexpr int K = FLAT ? 2 : PAT == MARCH_BRICK ? 3 : 4;
+  constexpr bool DIAG = PAT == MARCH_NNN;   // diagonal neighbours too
+  constexpr int K = FLAT ? 2 : PAT == MARCH_BRICK ? 3 : DIAG ? 8 : 4;
   constexpr bool ENTRY = HOP != HOP_UNIFORM;
   constexpr bool CPLX = HOP == HOP_COMPLEX || HOP == HOP_DICT;
   constexpr bool IM = NC == 2 || ENTRY;   // as in k_march
   using hv_t = std::conditional_t<CPLX, double2, double>;
-  constexpr int MARGIN = FLAT ? 1 : kMaxTileX;
+  constexpr int MARGIN = FLAT ? 1 : kMaxTileX + 1;
   constexpr int SLOTS = C * LANES + 2 * MARGIN;
   constexpr int U = kPatchUnroll, NW = LANES / 64;
   // dots of a group of U steps: per step the real part of rows 2k - 1 and 2k, then (IM) the imaginary part of
@@ -162,24 +164,41 @@ __global__ __launch_bounds__(LANES) void k_patch(MarchMat A, MarchIO io) {
             double2 p = make_double2(0.0, 0.0), m = p;
             axpy(p, hop[j][0], xp);
             axpy(m, hop[j][1], xm);
+            if constexpr (DIAG) {
+              axpy(p, hop[j][K - 4], L[up + 1]);
+              axpy(m, hop[j][K - 3], L[up - 1]);
+              axpy(p, hop[j][K - 2], L[1 - up]);
+              axpy(m, hop[j][K - 1], L[-1 - up]);
+            }
             if (c == 0) sx = make_double2(fma(dxp[j], p.x, dxm[j] * m.x), fma(dxp[j], p.y, dxm[j] * m.y));
             t = cadd(t, cadd(p, m));
           } else {
             axpy(t, hop[j][0], xp);
             axpy(t, hop[j][1], xm);
+            if constexpr (DIAG) {
+              axpy(t, hop[j][K - 4], L[up + 1]);
+              axpy(t, hop[j][K - 3], L[up - 1]);
+              axpy(t, hop[j][K - 2], L[1 - up]);
+              axpy(t, hop[j][K - 1], L[-1 - up]);
+            }
           }
           if constexpr (PAT == MARCH_BRICK) {
             axpy(t, hop[j][K - 1], L[vert[j] ? up : -up]);
           } else if constexpr (!FLAT) {
-            axpy(t, hop[j][K - 1], L[-up]);
-            axpy(t, hop[j][K - 2], L[up]);
+            axpy(t, hop[j][DIAG ? 3 : K - 1], L[-up]);
+            axpy(t, hop[j][DIAG ? 2 : K - 2], L[up]);
           }
         } else {
           const double hu2 = PAT == MARCH_SQUARE ? hu[j] : hus;
-          double2 n = cadd(xp, xm);
+          double2 n = cadd(xp, xm), np = xp, nm = xm;   // (np, nm: neighbours at x + 1 and x - 1)
+          if constexpr (DIAG) {
+            np = cadd(np, cadd(L[up + 1], L[1 - up]));
+            nm = cadd(nm, cadd(L[up - 1], L[-1 - up]));
+            n = cadd(np, nm);
+          }
           if constexpr (FAM == MF_MSD) {
             if (c == 0)
-              sx = make_double2(hu2 * fma(dxp[j], xp.x, dxm[j] * xm.x), hu2 * fma(dxp[j], xp.y, dxm[j] * xm.y));
+              sx = make_double2(hu2 * fma(dxp[j], np.x, dxm[j] * nm.x), hu2 * fma(dxp[j], np.y, dxm[j] * nm.y));
           }
           if constexpr (PAT == MARCH_BRICK) {
             n = cadd(n, L[vert[j] ? up : -up]);
@@ -273,8 +292,8 @@ __global__ __launch_bounds__(LANES) void k_patch(MarchMat A, MarchIO io) {
 }
 
 
-// Workgroups: 640 or 1024 cells in two dimensions, eight steps; 256 lanes of four (one chain) or
-// two cells on a chain, 24 steps.
+// Workgroups: 640 or 1024 cells in two dimensions, eight or four steps; 256 lanes of four (one
+// chain) or two cells on a chain, 24 steps (plan_patch).
 constexpr int patch_cells(int fam) { return two_chains(fam) ? 2 : 4; }
 
 template <int PAT, int HOP>

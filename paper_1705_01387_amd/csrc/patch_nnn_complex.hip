@@ -1,0 +1,12 @@
+// Patch kernels of the square pattern with next-nearest neighbours, a complex hopping per entry.
+#include "patch_core.h"
+
+namespace gpuqt {
+namespace march {
+
+hipError_t patch_nnn_complex(int family, int lanes, const MarchMat& A, const MarchIO& io, hipStream_t s) {
+  return launch_patch_pattern<MARCH_NNN, HOP_COMPLEX>(family, lanes, A, io, s);
+}
+
+}  // namespace march
+}  // namespace gpuqt

@@ -82,9 +82,14 @@ CASES = {
     "open48x20": lambda: (sheet(48, 20, 21, periodic_x=False), {}, True),
     "open3x130": lambda: (sheet(3, 130, 33, periodic_x=False), {}, True),
     "open113x3": lambda: (shuffled(sheet(113, 3, 34, periodic_x=False), 35), {}, True),
-    # no march: open in x with per-bond hoppings, next-nearest neighbours
+    "nnn_uniform": lambda: (sheet(30, 20, 22, t1=-0.5, t2=-0.5), {}, True),
+    "nnn_table": lambda: (sheet(33, 41, 22, t2=-0.2), {}, True),
+    "nnn3x3": lambda: (sheet(3, 3, 38, t2=-0.2), {}, True),
+    "nnn_real_entries": lambda: (I.bond_disorder(sheet(17, 60, 39, t2=-0.3), 0.2, 40), dict(no_dictionary=True), True),
+    "nnn_complex_entries": lambda: (I.bond_disorder(sheet(50, 16, 41, t2=-0.3), 0.2, 42, max_phase=0.5),
+                                    dict(no_dictionary=True), True),
+    # no march: open in x with per-bond hoppings
     "open_entries": lambda: (I.bond_disorder(sheet(30, 20, 36, periodic_x=False), 0.2, 37), {}, False),
-    "nnn": lambda: (sheet(30, 20, 22, t2=-0.2), {}, False),
 }
 
 
@@ -143,6 +148,7 @@ LARGE = {
     "brick_complex_entries": lambda: (I.honeycomb(130, 440, flux=1 / 57200, W=2.0, seed=81), dict(no_dictionary=True)),
     "brick_real_entries": lambda: (I.bond_disorder(I.honeycomb(118, 500, W=1.0, seed=82), 0.3, 83),
                                    dict(no_dictionary=True)),
+    "nnn": lambda: (sheet(190, 121, 88, t2=-0.2), {}),
     "open": lambda: (sheet(48 * 9 + 2, 277, 87, periodic_x=False), {}),
     "chain": lambda: (I.chain(1200001, W=1.0, seed=84), {}),   # several patches to a workgroup
 }
