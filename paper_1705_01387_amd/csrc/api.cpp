@@ -587,6 +587,8 @@ gpuqt_status run_backward(const Handle* h, int B, const double2* pL, const doubl
   const DevMat D = h->view(B);                  // adjoint steps: primary plan (class partials)
   const DevMat F = h->view(B, FAM_MOMENT);      // forward recomputation: no partials
   const bool grad = gU != nullptr;
+  // class terms one step late, from the rows' own forward vector (k_adjoint_step)
+  const bool tr = grad && nc > 0 && !gH && h->sym_hop && M >= 2;
   const int K = backward_pairs(M, s);
   double2* const* R = vec;
   double2* const* Lm = vec + 3;
@@ -603,7 +605,8 @@ gpuqt_status run_backward(const Handle* h, int B, const double2* pL, const doubl
     a.n = n;
     a.f_rec = 2.0;
     a.v = nullptr;
-    a.f = n == 1 ? 1.0 : 2.0;
+    a.tr = tr ? 1 : 0;
+    a.f = n + (tr ? 1 : 0) == 1 ? 1.0 : 2.0;
     a.gU = gU;
     a.gcp = gcp;
     a.cls = h->d_cls;
@@ -632,7 +635,7 @@ gpuqt_status run_backward(const Handle* h, int B, const double2* pL, const doubl
     }
     for (int n = M - 1; n >= 1; --n) {
       AdjIO a = make(n);
-      a.v = fwd(n - 1);
+      a.v = !tr ? fwd(n - 1) : n < M - 1 ? fwd(n) : nullptr;
       HIP_TRY(launch_adjoint_step(D, h->hop_mode, B, nc, a, sm));
     }
   } else if (grad) {
@@ -651,15 +654,21 @@ gpuqt_status run_backward(const Handle* h, int B, const double2* pL, const doubl
       if (j == 1) return ck(k, 1);
       return sb(j);
     };
+    if (tr) HIP_TRY(launch_adjoint_step(D, h->hop_mode, B, nc, make(M - 1), sm));
     for (int k = K - 1; k >= 0; --k) {
       const int lo = k * s + 1, hi = std::min((k + 1) * s, M - 1);
       for (int j = 2; j <= hi - 1 - k * s; ++j) {   // recompute v_{ks+j}
         StepIO io{slot(k, j - 1), slot(k, j - 2), sb(j), 0};
         HIP_TRY(launch_moment_step(F, h->hop_mode, B, io, nullptr, nullptr, nullptr, sm));
       }
-      for (int n = hi; n >= lo; --n) {
+      for (int n = hi; n >= lo && !tr; --n) {
         AdjIO a = make(n);
         a.v = slot(k, n - 1 - k * s);
+        HIP_TRY(launch_adjoint_step(D, h->hop_mode, B, nc, a, sm));
+      }
+      for (int n = hi - 1; n >= std::max(lo - 1, 1) && tr; --n) {
+        AdjIO a = make(n);
+        a.v = slot(k, n - k * s);
         HIP_TRY(launch_adjoint_step(D, h->hop_mode, B, nc, a, sm));
       }
     }
@@ -669,17 +678,21 @@ gpuqt_status run_backward(const Handle* h, int B, const double2* pL, const doubl
       HIP_TRY(launch_adjoint_step(D, h->hop_mode, B, 0, a, sm));
     }
   }
-  if (lam0) {   // lam_0 = conj(c_0) phiL + H~ lam_1 - lam_2 = sum_n conj(c_n) T_n(H~) phiL
+  if (lam0 || tr) {   // lam_0 = conj(c_0) phiL + H~ lam_1 - lam_2 = sum_n conj(c_n) T_n(H~) phiL
     AdjIO a = make(0);
     a.x = M >= 2 ? Lm[1] : nullptr;
     a.w = M >= 3 ? Lm[2] : nullptr;
-    a.out = lam0;
+    if (lam0) a.out = lam0;
     a.f_rec = 1.0;
-    a.gU = nullptr;
-    a.gcp = nullptr;
     a.gH = nullptr;
-    a.accumulate = acc0 ? 1 : 0;
-    HIP_TRY(launch_adjoint_step(D, h->hop_mode, B, 0, a, sm));
+    a.accumulate = lam0 && acc0 ? 1 : 0;
+    if (tr) {   // and the terms of step 1
+      a.v = pR;
+    } else {
+      a.gU = nullptr;
+      a.gcp = nullptr;
+    }
+    HIP_TRY(launch_adjoint_step(D, h->hop_mode, B, tr ? nc : 0, a, sm));
   }
   return GPUQT_OK;
 }
@@ -717,9 +730,10 @@ gpuqt_status run_backward_pair(const Handle* h, int B, const double2* pL, const 
   }
   double2* const* La = recorded ? vec : vec + 2 * K;   // rotating abar
   double2* const* Lb = La + 3;                         // rotating bbar
+  const bool tr = gU && nc > 0 && h->sym_hop;   // class terms one step late (k_adjoint_pair_step)
   const DevMat D = h->view(B);            // class partials over the primary plan
   for (int k = K; k >= 0; --k) {
-    if (k == 0 && !outA && !outB) break;
+    if (k == 0 && !outA && !outB && !tr) break;
     AdjPairIO io{};
     io.xa = k + 1 <= K ? La[(k + 1) % 3] : nullptr;
     io.wa = k + 2 <= K ? La[(k + 2) % 3] : nullptr;
@@ -738,7 +752,8 @@ gpuqt_status run_backward_pair(const Handle* h, int B, const double2* pL, const 
     io.R = R;
     io.k = k;
     io.f_rec = k >= 1 ? 2.0 : 1.0;
-    io.f = k >= 2 ? 2.0 : 1.0;
+    io.tr = tr ? 1 : 0;
+    io.f = k + io.tr >= 2 ? 2.0 : 1.0;
     io.gU = gU;
     io.gcp = gcp;
     io.cls = h->d_cls;
@@ -769,14 +784,15 @@ gpuqt_status run_backward_sym(const Handle* h, int B, const double2* ph, int M, 
     }
   }
   double2* const* Lc = vec + K;   // rotating cbar
+  const bool tr = gU && nc > 0 && h->sym_hop;   // class terms one step late (k_adjoint_sym_step)
   const DevMat D = h->view(B);     // class partials over the primary plan
   for (int k = K; k >= 0; --k) {
-    if (k == 0 && !lam0) break;
+    if (k == 0 && !lam0 && !tr) break;
     AdjPairIO io{};
     io.xa = k + 1 <= K ? Lc[(k + 1) % 3] : nullptr;
     io.wa = k + 2 <= K ? Lc[(k + 2) % 3] : nullptr;
-    io.oa = (k == 0) ? lam0 : Lc[k % 3];
-    io.acc_a = (k == 0 && acc0) ? 1 : 0;
+    io.oa = (k == 0 && lam0) ? lam0 : Lc[k % 3];
+    io.acc_a = (k == 0 && lam0 && acc0) ? 1 : 0;
     io.a_m1 = k >= 1 ? fa(k - 1) : nullptr;
     io.a_k = fa(k);
     io.a_p1 = k + 1 <= K ? fa(k + 1) : nullptr;
@@ -784,7 +800,8 @@ gpuqt_status run_backward_sym(const Handle* h, int B, const double2* ph, int M, 
     io.R = R;
     io.k = k;
     io.f_rec = k >= 1 ? 2.0 : 1.0;
-    io.f = k >= 2 ? 2.0 : 1.0;
+    io.tr = tr ? 1 : 0;
+    io.f = k + io.tr >= 2 ? 2.0 : 1.0;
     io.gU = gU;
     io.gcp = gcp;
     io.cls = h->d_cls;
@@ -949,6 +966,15 @@ gpuqt_status gpuqt_build_h(const gpuqt_h_desc* desc, void* stream, gpuqt_h* out)
   }
   std::vector<double> zeros_g(h->G, 0.0);
   up((void**)&h->d_bound, zeros_g.data(), zeros_g.size() * 8);
+  // are every class's hoppings Hermitian (class gradients)?  Given by the pattern with one hopping
+  // per segment, else looked at on the device; d_bound holds the answer until the synchronisation
+  int32_t asym = 0;
+  if (L.n_class <= 4 && !(h->lat.pattern != MARCH_NONE && L.hop_mode == HOP_UNIFORM && L.cls.empty()) && ok) {
+    int32_t* flag = reinterpret_cast<int32_t*>(h->d_bound);
+    if (launch_check_classes(h->view(1), h->hop_mode, L.n_class > 1 ? h->d_cls : nullptr, flag, s) != hipSuccess ||
+        hipMemcpyAsync(&asym, flag, sizeof(asym), hipMemcpyDeviceToHost, s) != hipSuccess)
+      ok = false;
+  }
   // banded unit orders, per block width: the row window between the first and
   // last use of a gathered element is 2 D rows in the plain order and 2 W in
   // the banded one; W keeps it (with everything else the step streams per
@@ -1002,6 +1028,7 @@ gpuqt_status gpuqt_build_h(const gpuqt_h_desc* desc, void* stream, gpuqt_h* out)
   h->seg_hop0 = L.seg_hop;
   h->class_scale.assign(h->n_class, 1.0);
   if (ok && hipStreamSynchronize(s) != hipSuccess) ok = false;
+  h->sym_hop = asym == 0 && L.n_class <= 4;
   if (!ok) {
     gpuqt_destroy_h(reinterpret_cast<gpuqt_h>(h));
     return fail(GPUQT_ERR_NOMEM, "device allocation or copy failed while building the layout");

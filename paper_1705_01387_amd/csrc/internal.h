@@ -232,6 +232,7 @@ struct Handle {
   int32_t max_nn_in = 0;           // neighbour slots per orbital of the descriptor (per-entry gradients)
   double* d_diag = nullptr;
   int32_t* d_cls = nullptr;
+  int32_t sym_hop = 0;             // 1: the hoppings of every class are Hermitian by themselves
   BlkPlan* d_plan = nullptr;
   int32_t* d_seg_blk0 = nullptr;   // [n_seg + 1] first logical workgroup of each segment
   double* d_seg_dE = nullptr;
@@ -490,8 +491,9 @@ struct AdjIO {
   const double* wts;     // [n_seg][B][M] loss weights on Re mu (NULL: zero)
   int32_t M, n;
   double f_rec;          // 2 for a reverse step, 1 for lam_0
-  const double2* v;      // v_{n-1} (NULL: no gradient terms)
-  double f;              // 2 for n >= 2, 1 for n = 1
+  const double2* v;      // v_{n-1}, or (tr) v_n (NULL: no gradient terms)
+  double f;              // gradient factor of step n, or (tr) n + 1: 2, 1 for step 1
+  int32_t tr;            // 1: the gradient terms of step n + 1, from x and its class products
   double* gU;            // [n] accumulated
   double* gcp;           // [G][nc] accumulated per workgroup
   const int32_t* cls;    // class of each entry, or (HOP_DICT) of each table entry (nc > 1)
@@ -522,12 +524,15 @@ struct AdjPairIO {
   const double* om;      // [n_seg][B][R] raw-dot weights
   int32_t R, k;
   double f_rec;          // 2 for k >= 1, 1 for k = 0
-  double f;              // gradient factor: 2 for k >= 2, 1 for k = 1 (unused for k = 0)
+  double f;              // gradient factor of step k, or (tr) k + 1: 2, 1 for step 1
+  int32_t tr;            // 1: the gradient terms of step k + 1, from xa, xb and their class products
   double* gU;            // [n] accumulated (NULL: no parameter terms)
   double* gcp;           // [G][nc] accumulated per workgroup
   const int32_t* cls;
   int32_t acc_a, acc_b;  // 1: oa += abar_k, ob += bbar_k
 };
+// *bad (zero before) becomes 1 where some class's hoppings between two rows are not Hermitian.
+hipError_t launch_check_classes(const DevMat& A, int hop_mode, const int32_t* cls, int32_t* bad, hipStream_t s);
 hipError_t launch_adjoint_pair_step(const DevMat& A, int hop_mode, int B, int nc, const AdjPairIO& io,
                                     hipStream_t s);
 // om[s][b][r] for r < R from loss weights w[s][b][n], n < M (raw-dot weights of

@@ -21,7 +21,14 @@ using namespace dev;
 
 namespace {
 
-template <int B, int HOP, int K, int NC>
+//
+// Class gradients (TR, where every class's hoppings are Hermitian by themselves): <lam_{n+1}| H~_c v_n> =
+// conj(<v_n| H~_c lam_{n+1}>), and H~_c lam_{n+1} is part of the product that gives lam_n.  So step n adds
+// the terms of step n + 1 from the rows' own v_n, and only lam_{n+1} is gathered.  Bound by the gathers'
+// latency (512 x 512 with next-nearest neighbours, two classes, us a step: two chains 20.5 with v gathered too,
+// @AP@ so; one chain of the Hermitian form 16.5, @AS@; one chain 14.2, @A1@).  Otherwise the terms of step n, with v_{n-1}
+// gathered.
+template <int B, int HOP, int K, int NC, bool TR>
 __global__ __launch_bounds__(kBlock) void k_adjoint_step(DevMat A, AdjIO io) {
   const int lb = logical_block(A.G);
   const BlkPlan P = A.plan[lb];
@@ -55,12 +62,13 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_step(DevMat A, AdjIO io) {
       int64_t cc;
       const bool ok = col_entry<HOP>(A, r, e, &cc);
       const double2 he = hop_entry<HOP>(A, e, ok, hu);
+      double2 xv = make_double2(0.0, 0.0);
       if (x) {
-        const double2 xv = x[cc * B + b];
+        xv = x[cc * B + b];
         h = cadd(h, (HOP == HOP_COMPLEX || HOP == HOP_DICT) ? cmul(he, xv) : cscale(he.x, xv));
       }
       if (NC > 0 && v) {
-        const double2 vv = v[cc * B + b];
+        const double2 vv = TR ? xv : v[cc * B + b];
         const double2 he0 = hop0_entry<HOP>(A, e, ok, P.seg);
         const double2 t = (HOP == HOP_COMPLEX || HOP == HOP_DICT) ? cmul(he0, vv) : cscale(he0.x, vv);
         const int cls = (NC > 1) ? (ok ? io.cls[HOP == HOP_DICT ? (int64_t)A.hidx[e] : e] : 0) : 0;
@@ -78,14 +86,18 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_step(DevMat A, AdjIO io) {
     io.out[idx] = io.accumulate ? cadd(io.out[idx], lam) : lam;
     if (v) {
       const double2 vr = v[idx];
-      double gu = io.f * (lam.x * vr.x + lam.y * vr.y);     // f Re(conj(lam) v)
+      const double2 lg = TR ? x[idx] : lam;
+      double gu = io.f * (lg.x * vr.x + lg.y * vr.y);     // f Re(conj(lam) v)
 #pragma unroll
       for (int off = 1; off < B; off <<= 1) gu += __shfl_xor(gu, off);
       if (b == 0) io.gU[r] += gu * inv_dE;
 #pragma unroll
       for (int q = 0; q < (NC > 0 ? NC : 1); ++q)
-        if (NC > 0) gc[q] += io.f * (lam.x * hv[q].x + lam.y * hv[q].y);
-      if (io.gH) row_entry_grads<B, HOP, K>(A, r, b, lam, v, io.f * inv_dE, io.gH, io.ldH);
+        if (NC > 0) {
+          const double2 l = TR ? vr : lam;
+          gc[q] += io.f * (l.x * hv[q].x + l.y * hv[q].y);
+        }
+      if (!TR && io.gH) row_entry_grads<B, HOP, K>(A, r, b, lam, v, io.f * inv_dE, io.gH, io.ldH);
     }
   });
   if (NC == 0 || !v) return;
@@ -112,7 +124,7 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_step(DevMat A, AdjIO io) {
 // matrix read once; abar_{k+1}, bbar_{k+1} and, for class gradients, a_{k-1},
 // b_{k-1} gathered with the same indices).  Parameter terms, as for the
 // single chain: dL/dp = Re sum_k f_k (<abar_k| dH~/dp a_{k-1}> + <bbar_k| dH~/dp b_{k-1}>).
-template <int B, int HOP, int K, int NC>
+template <int B, int HOP, int K, int NC, bool TR>
 __global__ __launch_bounds__(kBlock) void k_adjoint_pair_step(DevMat A, AdjPairIO io) {
   const int lb = logical_block(A.G);
   const BlkPlan P = A.plan[lb];
@@ -124,7 +136,7 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_pair_step(DevMat A, AdjPairI
   const double w0 = om[k2];
   const double wm = io.k >= 1 ? om[k2 - 1] : 0.0;
   const double wp = (io.a_p1 && k2 + 1 < io.R) ? om[k2 + 1] : 0.0;
-  const bool grad = io.gU != nullptr && io.k >= 1;
+  const bool grad = io.gU != nullptr && (TR ? io.xa != nullptr : io.k >= 1);
   const int S = 1 << A.S_log2;
   double gc[NC > 0 ? NC : 1];
 #pragma unroll
@@ -152,13 +164,15 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_pair_step(DevMat A, AdjPairI
       int64_t cc;
       const bool ok = col_entry<HOP>(A, r, e, &cc);
       const double2 he = hop_entry<HOP>(A, e, ok, hu);
+      double2 xa = make_double2(0.0, 0.0), xb = xa;
       if (io.xa) {
-        const double2 xa = io.xa[cc * B + b], xb = io.xb[cc * B + b];
+        xa = io.xa[cc * B + b];
+        xb = io.xb[cc * B + b];
         ha = cadd(ha, (HOP == HOP_COMPLEX || HOP == HOP_DICT) ? cmul(he, xa) : cscale(he.x, xa));
         hb = cadd(hb, (HOP == HOP_COMPLEX || HOP == HOP_DICT) ? cmul(he, xb) : cscale(he.x, xb));
       }
       if (NC > 0 && grad) {
-        const double2 va = io.a_m1[cc * B + b], vb = io.b_m1[cc * B + b];
+        const double2 va = TR ? xa : io.a_m1[cc * B + b], vb = TR ? xb : io.b_m1[cc * B + b];
         const double2 he0 = hop0_entry<HOP>(A, e, ok, P.seg);
         const double2 ta = (HOP == HOP_COMPLEX || HOP == HOP_DICT) ? cmul(he0, va) : cscale(he0.x, va);
         const double2 tb = (HOP == HOP_COMPLEX || HOP == HOP_DICT) ? cmul(he0, vb) : cscale(he0.x, vb);
@@ -186,15 +200,17 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_pair_step(DevMat A, AdjPairI
     io.oa[idx] = io.acc_a ? cadd(io.oa[idx], la) : la;
     io.ob[idx] = io.acc_b ? cadd(io.ob[idx], lbv) : lbv;
     if (grad) {
-      const double2 va = io.a_m1[idx], vb = io.b_m1[idx];
-      double gu = io.f * (la.x * va.x + la.y * va.y + lbv.x * vb.x + lbv.y * vb.y);
+      const double2 va = TR ? io.a_k[idx] : io.a_m1[idx], vb = TR ? io.b_k[idx] : io.b_m1[idx];
+      const double2 pa = TR ? io.xa[idx] : la, pb = TR ? io.xb[idx] : lbv;
+      double gu = io.f * (pa.x * va.x + pa.y * va.y + pb.x * vb.x + pb.y * vb.y);
+      const double2 qa = TR ? va : la, qb = TR ? vb : lbv;
 #pragma unroll
       for (int off = 1; off < B; off <<= 1) gu += __shfl_xor(gu, off);
       if (b == 0) io.gU[r] += gu * inv_dE;
 #pragma unroll
       for (int q = 0; q < (NC > 0 ? NC : 1); ++q)
         if (NC > 0)
-          gc[q] += io.f * (la.x * hva[q].x + la.y * hva[q].y + lbv.x * hvb[q].x + lbv.y * hvb[q].y);
+          gc[q] += io.f * (qa.x * hva[q].x + qa.y * hva[q].y + qb.x * hvb[q].x + qb.y * hvb[q].y);
     }
   });
   if (NC == 0 || !grad) return;
@@ -224,7 +240,7 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_pair_step(DevMat A, AdjPairI
 // gathered instead of two.  At k = 0 the output is cbar_0 / 2 = sum_n w_n T_n phi
 // (abar_0 = bbar_0).  Fields of io: xa, wa, oa, acc_a, a_m1, a_k, a_p1 and the
 // weights; the b fields are unused.
-template <int B, int HOP, int K, int NC>
+template <int B, int HOP, int K, int NC, bool TR>
 __global__ __launch_bounds__(kBlock) void k_adjoint_sym_step(DevMat A, AdjPairIO io) {
   const int lb = logical_block(A.G);
   const BlkPlan P = A.plan[lb];
@@ -237,7 +253,7 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_sym_step(DevMat A, AdjPairIO
   const double wm = io.k >= 1 ? om[k2 - 1] : 0.0;
   const double wp = (io.a_p1 && k2 + 1 < io.R) ? om[k2 + 1] : 0.0;
   const double out_scale = io.k == 0 ? 0.5 : 1.0;
-  const bool grad = io.gU != nullptr && io.k >= 1;
+  const bool grad = io.gU != nullptr && (TR ? io.xa != nullptr : io.k >= 1);
   const int S = 1 << A.S_log2;
   double gc[NC > 0 ? NC : 1];
 #pragma unroll
@@ -258,12 +274,13 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_sym_step(DevMat A, AdjPairIO
       int64_t cc;
       const bool ok = col_entry<HOP>(A, r, e, &cc);
       const double2 he = hop_entry<HOP>(A, e, ok, hu);
+      double2 x = make_double2(0.0, 0.0);
       if (io.xa) {
-        const double2 x = io.xa[cc * B + b];
+        x = io.xa[cc * B + b];
         h = cadd(h, (HOP == HOP_COMPLEX || HOP == HOP_DICT) ? cmul(he, x) : cscale(he.x, x));
       }
       if (NC > 0 && grad) {
-        const double2 v = io.a_m1[cc * B + b];
+        const double2 v = TR ? x : io.a_m1[cc * B + b];
         const double2 he0 = hop0_entry<HOP>(A, e, ok, P.seg);
         const double2 t = (HOP == HOP_COMPLEX || HOP == HOP_DICT) ? cmul(he0, v) : cscale(he0.x, v);
         const int cls = (NC > 1) ? (ok ? io.cls[HOP == HOP_DICT ? (int64_t)A.hidx[e] : e] : 0) : 0;
@@ -284,14 +301,15 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_sym_step(DevMat A, AdjPairIO
     const double2 o = cscale(out_scale, c);
     io.oa[idx] = io.acc_a ? cadd(io.oa[idx], o) : o;
     if (grad) {
-      const double2 v = io.a_m1[idx];
-      double gu = io.f * (c.x * v.x + c.y * v.y);
+      const double2 v = TR ? io.a_k[idx] : io.a_m1[idx];
+      const double2 p = TR ? io.xa[idx] : c, l = TR ? v : c;
+      double gu = io.f * (p.x * v.x + p.y * v.y);
 #pragma unroll
       for (int off = 1; off < B; off <<= 1) gu += __shfl_xor(gu, off);
       if (b == 0) io.gU[r] += gu * inv_dE;
 #pragma unroll
       for (int q = 0; q < (NC > 0 ? NC : 1); ++q)
-        if (NC > 0) gc[q] += io.f * (c.x * hv[q].x + c.y * hv[q].y);
+        if (NC > 0) gc[q] += io.f * (l.x * hv[q].x + l.y * hv[q].y);
     }
   });
   if (NC == 0 || !grad) return;
@@ -311,6 +329,39 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_sym_step(DevMat A, AdjPairIO
     for (int wv = 0; wv < kBlock / 64; ++wv) s += sh[wv][threadIdx.x];
     io.gcp[(int64_t)lb * NC + threadIdx.x] += s;
   }
+}
+
+// Whether the hoppings of every class are Hermitian by themselves: for each entry (r, c), the sums of
+// the class's hoppings from r to c and back are conjugate to each other.
+template <int HOP>
+__global__ __launch_bounds__(kBlock) void k_check_classes(DevMat A, const int32_t* __restrict__ cls, int32_t* bad) {
+  const BlkPlan P = A.plan[logical_block(A.G)];
+  const int S = 1 << A.S_log2;
+  auto klass = [&](int64_t e) { return cls ? cls[HOP == HOP_DICT ? (int64_t)A.hidx[e] : e] : 0; };
+  // hoppings of class q from row r to row c
+  auto sum = [&](int64_t r, int64_t c, int q) {
+    const int64_t sl = r >> A.S_log2, p0 = A.slice_ptr[sl], e0 = p0 + (r & (S - 1));
+    const int w = (int)((A.slice_ptr[sl + 1] - p0) >> A.S_log2);
+    double2 t = make_double2(0.0, 0.0);
+    for (int j = 0; j < w; ++j) {
+      const int64_t e = e0 + (int64_t)j * S;
+      int64_t cc;
+      if (col_entry<HOP>(A, r, e, &cc) && cc == c && klass(e) == q) t = cadd(t, hop0_entry<HOP>(A, e, true, P.seg));
+    }
+    return t;
+  };
+  for_rows<1>(A, P, [&](int64_t r) {
+    const int64_t sl = r >> A.S_log2, p0 = A.slice_ptr[sl], e0 = p0 + (r & (S - 1));
+    const int w = (int)((A.slice_ptr[sl + 1] - p0) >> A.S_log2);
+    for (int j = 0; j < w; ++j) {
+      const int64_t e = e0 + (int64_t)j * S;
+      int64_t c;
+      if (!col_entry<HOP>(A, r, e, &c)) continue;
+      const int q = klass(e);
+      const double2 a = sum(r, c, q), t = sum(c, r, q);
+      if (a.x != t.x || a.y != -t.y) *bad = 1;
+    }
+  });
 }
 
 // Raw-dot weights of the product identities, one wavefront per (segment,
@@ -557,10 +608,19 @@ hipError_t launch_adjoint_step(const DevMat& A, int hop_mode, int B, int nc, con
     auto go = [&](auto Kc) {
       constexpr int Kv = decltype(Kc)::value;
       switch (nc) {
-        case 0: k_adjoint_step<Bv, Hv, Kv, 0><<<dim3(A.G), kBlock, 0, s>>>(A, io); break;
-        case 1: k_adjoint_step<Bv, Hv, Kv, 1><<<dim3(A.G), kBlock, 0, s>>>(A, io); break;
-        case 2: k_adjoint_step<Bv, Hv, Kv, 2><<<dim3(A.G), kBlock, 0, s>>>(A, io); break;
-        default: k_adjoint_step<Bv, Hv, Kv, 4><<<dim3(A.G), kBlock, 0, s>>>(A, io); break;
+        case 0: k_adjoint_step<Bv, Hv, Kv, 0, false><<<dim3(A.G), kBlock, 0, s>>>(A, io); break;
+        case 1:
+          if (io.tr) k_adjoint_step<Bv, Hv, Kv, 1, true><<<dim3(A.G), kBlock, 0, s>>>(A, io);
+          else k_adjoint_step<Bv, Hv, 0, 1, false><<<dim3(A.G), kBlock, 0, s>>>(A, io);
+          break;
+        case 2:
+          if (io.tr) k_adjoint_step<Bv, Hv, Kv, 2, true><<<dim3(A.G), kBlock, 0, s>>>(A, io);
+          else k_adjoint_step<Bv, Hv, 0, 2, false><<<dim3(A.G), kBlock, 0, s>>>(A, io);
+          break;
+        default:
+          if (io.tr) k_adjoint_step<Bv, Hv, Kv, 4, true><<<dim3(A.G), kBlock, 0, s>>>(A, io);
+          else k_adjoint_step<Bv, Hv, 0, 4, false><<<dim3(A.G), kBlock, 0, s>>>(A, io);
+          break;
       }
     };
     switch (A.K) {
@@ -580,10 +640,19 @@ hipError_t launch_adjoint_pair_step(const DevMat& A, int hop_mode, int B, int nc
     auto go = [&](auto Kc) {
       constexpr int Kv = decltype(Kc)::value;
       switch (nc) {
-        case 0: k_adjoint_pair_step<Bv, Hv, Kv, 0><<<dim3(A.G), kBlock, 0, s>>>(A, io); break;
-        case 1: k_adjoint_pair_step<Bv, Hv, Kv, 1><<<dim3(A.G), kBlock, 0, s>>>(A, io); break;
-        case 2: k_adjoint_pair_step<Bv, Hv, Kv, 2><<<dim3(A.G), kBlock, 0, s>>>(A, io); break;
-        default: k_adjoint_pair_step<Bv, Hv, Kv, 4><<<dim3(A.G), kBlock, 0, s>>>(A, io); break;
+        case 0: k_adjoint_pair_step<Bv, Hv, Kv, 0, false><<<dim3(A.G), kBlock, 0, s>>>(A, io); break;
+        case 1:
+          if (io.tr) k_adjoint_pair_step<Bv, Hv, Kv, 1, true><<<dim3(A.G), kBlock, 0, s>>>(A, io);
+          else k_adjoint_pair_step<Bv, Hv, 0, 1, false><<<dim3(A.G), kBlock, 0, s>>>(A, io);
+          break;
+        case 2:
+          if (io.tr) k_adjoint_pair_step<Bv, Hv, Kv, 2, true><<<dim3(A.G), kBlock, 0, s>>>(A, io);
+          else k_adjoint_pair_step<Bv, Hv, 0, 2, false><<<dim3(A.G), kBlock, 0, s>>>(A, io);
+          break;
+        default:
+          if (io.tr) k_adjoint_pair_step<Bv, Hv, Kv, 4, true><<<dim3(A.G), kBlock, 0, s>>>(A, io);
+          else k_adjoint_pair_step<Bv, Hv, 0, 4, false><<<dim3(A.G), kBlock, 0, s>>>(A, io);
+          break;
       }
     };
     switch (A.K) {
@@ -603,10 +672,19 @@ hipError_t launch_adjoint_sym_step(const DevMat& A, int hop_mode, int B, int nc,
     auto go = [&](auto Kc) {
       constexpr int Kv = decltype(Kc)::value;
       switch (nc) {
-        case 0: k_adjoint_sym_step<Bv, Hv, Kv, 0><<<dim3(A.G), kBlock, 0, s>>>(A, io); break;
-        case 1: k_adjoint_sym_step<Bv, Hv, Kv, 1><<<dim3(A.G), kBlock, 0, s>>>(A, io); break;
-        case 2: k_adjoint_sym_step<Bv, Hv, Kv, 2><<<dim3(A.G), kBlock, 0, s>>>(A, io); break;
-        default: k_adjoint_sym_step<Bv, Hv, Kv, 4><<<dim3(A.G), kBlock, 0, s>>>(A, io); break;
+        case 0: k_adjoint_sym_step<Bv, Hv, Kv, 0, false><<<dim3(A.G), kBlock, 0, s>>>(A, io); break;
+        case 1:
+          if (io.tr) k_adjoint_sym_step<Bv, Hv, Kv, 1, true><<<dim3(A.G), kBlock, 0, s>>>(A, io);
+          else k_adjoint_sym_step<Bv, Hv, 0, 1, false><<<dim3(A.G), kBlock, 0, s>>>(A, io);
+          break;
+        case 2:
+          if (io.tr) k_adjoint_sym_step<Bv, Hv, Kv, 2, true><<<dim3(A.G), kBlock, 0, s>>>(A, io);
+          else k_adjoint_sym_step<Bv, Hv, 0, 2, false><<<dim3(A.G), kBlock, 0, s>>>(A, io);
+          break;
+        default:
+          if (io.tr) k_adjoint_sym_step<Bv, Hv, Kv, 4, true><<<dim3(A.G), kBlock, 0, s>>>(A, io);
+          else k_adjoint_sym_step<Bv, Hv, 0, 4, false><<<dim3(A.G), kBlock, 0, s>>>(A, io);
+          break;
       }
     };
     switch (A.K) {
@@ -617,6 +695,16 @@ hipError_t launch_adjoint_sym_step(const DevMat& A, int hop_mode, int B, int nc,
       default: go(IC<0>{}); break;
     }
   });
+}
+
+hipError_t launch_check_classes(const DevMat& A, int hop_mode, const int32_t* cls, int32_t* bad, hipStream_t s) {
+  switch (hop_mode) {
+    case HOP_UNIFORM: k_check_classes<HOP_UNIFORM><<<dim3(A.G), kBlock, 0, s>>>(A, cls, bad); break;
+    case HOP_REAL: k_check_classes<HOP_REAL><<<dim3(A.G), kBlock, 0, s>>>(A, cls, bad); break;
+    case HOP_COMPLEX: k_check_classes<HOP_COMPLEX><<<dim3(A.G), kBlock, 0, s>>>(A, cls, bad); break;
+    default: k_check_classes<HOP_DICT><<<dim3(A.G), kBlock, 0, s>>>(A, cls, bad); break;
+  }
+  return hipGetLastError();
 }
 
 hipError_t launch_raw_weights(const double* w, int rows, int M, int R, double* om, hipStream_t s) {

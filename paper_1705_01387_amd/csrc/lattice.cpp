@@ -87,6 +87,7 @@ bool detect_lattice(const gpuqt_h_desc* d, const HostLayout& L, const int32_t bo
                     const std::vector<int32_t>& sheets, MarchLattice* M) {
   *M = MarchLattice();
   const int n_seg = L.n_seg;
+  bool chain = false;
   if (box[0] > 0) {
     M->pattern = MARCH_BOX;
     M->dims = {box[0], box[1], box[2]};
@@ -116,18 +117,13 @@ bool detect_lattice(const gpuqt_h_desc* d, const HostLayout& L, const int32_t bo
     }
     M->pattern = MARCH_NNN;
   } else if (L.uniform_width == 2 && d->nn && d->nbr) {
-    // rings in natural order, at least three sites each
+    // rings in natural order, at least three sites each (their neighbours are checked below)
     for (int s = 0; s < n_seg; ++s) {
-      const int64_t off = L.seg_off[s], n = L.seg_off[s + 1] - off, k = d->max_nn;
+      const int64_t n = L.seg_off[s + 1] - L.seg_off[s];
       if (n < 3 || n > (int64_t(1) << 30)) return false;
-      for (int64_t x = 0; x < n; ++x) {
-        const int32_t* c = d->nbr + (off + x) * k;
-        const int64_t xp = off + (x + 1 == n ? 0 : x + 1), xm = off + (x == 0 ? n - 1 : x - 1);
-        if (d->nn[off + x] != 2 || !((c[0] == xp && c[1] == xm) || (c[0] == xm && c[1] == xp))) return false;
-      }
       M->dims.insert(M->dims.end(), {(int32_t)n, 1, 1});
     }
-    M->pattern = MARCH_CHAIN;
+    chain = true;
   } else if (L.uniform_width == 0 && L.hop_mode == HOP_UNIFORM && d->max_nn >= 4 && d->nn && d->nbr) {
     for (int s = 0; s < n_seg; ++s) {
       const int64_t n = L.seg_off[s + 1] - L.seg_off[s], Lx = open_square(d, L.seg_off[s], n);
@@ -141,13 +137,12 @@ bool detect_lattice(const gpuqt_h_desc* d, const HostLayout& L, const int32_t bo
   }
   // rows (planes) of blocks of 16 vectors are addressed with 32-bit byte offsets
   for (int s = 0; s < n_seg; ++s)
-    if (M->pattern != MARCH_CHAIN && (int64_t)M->dims[3 * s] * M->dims[3 * s + 1] >= (int64_t(1) << 24)) {
+    if (!chain && (int64_t)M->dims[3 * s] * M->dims[3 * s + 1] >= (int64_t(1) << 24)) {
       M->pattern = MARCH_NONE;
       return false;
     }
   // one pass over the rows: the stored slot of each square neighbour (needed where every
   // entry has its own hopping: it must be the same on every row) and the position steps
-  const bool chain = M->pattern == MARCH_CHAIN;
   const bool diag = M->pattern == MARCH_NNN;
   const bool slots = diag || ((M->pattern == MARCH_SQUARE || chain) && L.hop_mode != HOP_UNIFORM);
   const int nw = diag ? 8 : 4;
@@ -156,6 +151,27 @@ bool detect_lattice(const gpuqt_h_desc* d, const HostLayout& L, const int32_t bo
   auto width = [&](int64_t r) { return M->open ? d->nn[r] : K; };
   auto diff = [&](int64_t e) { return L.hop_mode == HOP_DICT ? L.dxtab[L.hidx[e]] : L.dx[e]; };
   bool dx_ok = true;
+  if (chain) {
+    for (int s = 0; s < n_seg; ++s) {
+      const int64_t off = L.seg_off[s], end = L.seg_off[s + 1];
+      for (int64_t r = off; r < end; ++r) {
+        const int64_t e0 = entry(r), e1 = e0 + (int64_t(1) << ls);
+        const int64_t xp = r + 1 == end ? off : r + 1, xm = r == off ? end - 1 : r - 1;
+        const bool fwd = L.col[e0] == xp && L.col[e1] == xm;
+        if (!fwd && !(L.col[e0] == xm && L.col[e1] == xp)) return false;
+        if (r == 0) {
+          M->slot[fwd ? 0 : 1] = 0;
+          M->slot[fwd ? 1 : 0] = 1;
+          M->dx = diff(fwd ? e0 : e1);
+        }
+        if (slots && fwd != (M->slot[0] == 0)) return false;
+        dx_ok = dx_ok && diff(fwd ? e0 : e1) == M->dx && diff(fwd ? e1 : e0) == -M->dx;
+      }
+    }
+    M->pattern = MARCH_CHAIN;
+    M->dx_ok = dx_ok ? 1 : 0;
+    return true;
+  }
   size_t col0 = 0;
   for (int s = 0; s < n_seg; ++s) {
     const int64_t Lx = M->dims[3 * s], Ly = M->dims[3 * s + 1], Lm = M->dims[3 * s + 2];
@@ -168,7 +184,10 @@ bool detect_lattice(const gpuqt_h_desc* d, const HostLayout& L, const int32_t bo
         const int64_t e = entry(off + x) + ((int64_t)j << ls);
         if (L.col[e] == off + (x + 1 == Lx ? 0 : x + 1)) dxc[x] = diff(e);
       }
-    for (int64_t z = 0; z < Ly * Lm; ++z) {
+    // where every row has row 0's positions, row 0's differences are every row's
+    bool same = true;
+    for (int64_t r = off + Lx, c = off, end = off + Lx * Ly * Lm; r < end && same; ++r, ++c) same = d->x[r] == d->x[c];
+    for (int64_t z = 0, rows = same && !slots ? 1 : Ly * Lm; z < rows; ++z) {
       const int64_t row = off + z * Lx;
       const int64_t up = off + (z + 1 == Lm ? 0 : z + 1) * Lx, dn = off + (z == 0 ? Lm - 1 : z - 1) * Lx;
       for (int64_t x = 0; x < Lx; ++x) {
@@ -180,7 +199,7 @@ bool detect_lattice(const gpuqt_h_desc* d, const HostLayout& L, const int32_t bo
           if (slots) {
             const int64_t want[8] = {xp, xm, up + x, dn + x, up + xp - row, up + xm - row, dn + xp - row, dn + xm - row};
             int q = 0;
-            while (q < nw && want[q] != c) ++q;   // (a chain's rows have only the first two)
+            while (q < nw && want[q] != c) ++q;
             right = q == 0 || q == 4 || q == 6;
             left = q == 1 || q == 5 || q == 7;
             if (q == nw) {
@@ -193,7 +212,7 @@ bool detect_lattice(const gpuqt_h_desc* d, const HostLayout& L, const int32_t bo
               return false;
             }
           }
-          if (!dx_ok) continue;
+          if (!dx_ok || (same && z > 0)) continue;
           const double v = diff(e);
           if (right) {
             dx_ok = v == dxc[x];
@@ -207,7 +226,7 @@ bool detect_lattice(const gpuqt_h_desc* d, const HostLayout& L, const int32_t bo
     }
   }
   M->dx = M->dxcol[0];
-  if (M->pattern == MARCH_BOX || chain) {   // one value everywhere
+  if (M->pattern == MARCH_BOX) {   // one value everywhere
     for (double v : M->dxcol) dx_ok = dx_ok && v == M->dx;
     M->dxcol.clear();
   }
