@@ -21,6 +21,18 @@ using namespace dev;
 
 namespace {
 
+// f(j) for the entries of a row: K of them unrolled, so that every index, table and gather load is in
+// flight at once instead of one entry's chain after another's, or w.
+template <int K, typename F>
+__device__ __forceinline__ void for_entries(int w, F&& f) {
+  if constexpr (K > 0) {
+#pragma unroll
+    for (int j = 0; j < K; ++j) f(j);
+  } else {
+    for (int j = 0; j < w; ++j) f(j);
+  }
+}
+
 //
 // Class gradients (TR, where every class's hoppings are Hermitian by themselves): <lam_{n+1}| H~_c v_n> =
 // conj(<v_n| H~_c lam_{n+1}>), and H~_c lam_{n+1} is part of the product that gives lam_n.  So step n adds
@@ -56,26 +68,52 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_step(DevMat A, AdjIO io) {
     double2 hv[NC > 0 ? NC : 1];
 #pragma unroll
     for (int c = 0; c < (NC > 0 ? NC : 1); ++c) hv[c] = make_double2(0.0, 0.0);
-    if (x) h = cscale(A.diag[r], x[idx]);
-    for (int j = 0; j < w; ++j) {
-      const int64_t e = e0 + (int64_t)j * S;
-      int64_t cc;
-      const bool ok = col_entry<HOP>(A, r, e, &cc);
-      const double2 he = hop_entry<HOP>(A, e, ok, hu);
-      double2 xv = make_double2(0.0, 0.0);
-      if (x) {
-        xv = x[cc * B + b];
-        h = cadd(h, (HOP == HOP_COMPLEX || HOP == HOP_DICT) ? cmul(he, xv) : cscale(he.x, xv));
-      }
-      if (NC > 0 && v) {
-        const double2 vv = TR ? xv : v[cc * B + b];
-        const double2 he0 = hop0_entry<HOP>(A, e, ok, P.seg);
-        const double2 t = (HOP == HOP_COMPLEX || HOP == HOP_DICT) ? cmul(he0, vv) : cscale(he0.x, vv);
-        const int cls = (NC > 1) ? (ok ? io.cls[HOP == HOP_DICT ? (int64_t)A.hidx[e] : e] : 0) : 0;
+    double gu0 = 0.0;
+    if (v && b == 0) gu0 = io.gU[r];
+    // per-entry gradients: the neighbours' v ahead of lam_n
+    constexpr bool ENT = NC == 0 && K > 0;
+    double2 vn[ENT ? K : 1];
+    if constexpr (ENT) {
+      if (io.gH) {
 #pragma unroll
-        for (int q = 0; q < (NC > 0 ? NC : 1); ++q)
-          if (q == cls) hv[q] = cadd(hv[q], t);
+        for (int j = 0; j < K; ++j) {
+          int64_t cc;
+          (void)col_entry<HOP>(A, r, e0 + (int64_t)j * S, &cc);
+          vn[j] = v[cc * B + b];
+        }
       }
+    }
+    auto mul = [](double2 he, double2 y) {
+      return (HOP == HOP_COMPLEX || HOP == HOP_DICT) ? cmul(he, y) : cscale(he.x, y);
+    };
+    auto add_class = [&](int64_t e, bool ok, double2 y) {
+      const double2 t = mul(hop0_entry<HOP>(A, e, ok, P.seg), y);
+      const int cls = (NC > 1) ? io.cls[HOP == HOP_DICT ? (int64_t)A.hidx[e] : e] : 0;   // (padding adds zero)
+#pragma unroll
+      for (int q = 0; q < (NC > 0 ? NC : 1); ++q) {
+        hv[q].x += q == cls ? t.x : 0.0;
+        hv[q].y += q == cls ? t.y : 0.0;
+      }
+    };
+    if (x) {
+      h = cscale(A.diag[r], x[idx]);
+      for_entries<K>(w, [&](int j) {
+        const int64_t e = e0 + (int64_t)j * S;
+        int64_t cc;
+        const bool ok = col_entry<HOP>(A, r, e, &cc);
+        const double2 xv = x[cc * B + b];
+        h = cadd(h, mul(hop_entry<HOP>(A, e, ok, hu), xv));
+        if constexpr (NC > 0 && TR) add_class(e, ok, xv);
+      });
+    }
+    if constexpr (NC > 0 && !TR) {
+      if (v)
+        for_entries<K>(w, [&](int j) {
+          const int64_t e = e0 + (int64_t)j * S;
+          int64_t cc;
+          const bool ok = col_entry<HOP>(A, r, e, &cc);
+          add_class(e, ok, v[cc * B + b]);
+        });
     }
     double2 lam = cmul(wn, io.phiL[idx]);
     lam = make_double2(fma(io.f_rec, h.x, lam.x), fma(io.f_rec, h.y, lam.y));
@@ -90,14 +128,33 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_step(DevMat A, AdjIO io) {
       double gu = io.f * (lg.x * vr.x + lg.y * vr.y);     // f Re(conj(lam) v)
 #pragma unroll
       for (int off = 1; off < B; off <<= 1) gu += __shfl_xor(gu, off);
-      if (b == 0) io.gU[r] += gu * inv_dE;
+      if (b == 0) io.gU[r] = gu0 + gu * inv_dE;
 #pragma unroll
       for (int q = 0; q < (NC > 0 ? NC : 1); ++q)
         if (NC > 0) {
           const double2 l = TR ? vr : lam;
           gc[q] += io.f * (l.x * hv[q].x + l.y * hv[q].y);
         }
-      if (!TR && io.gH) row_entry_grads<B, HOP, K>(A, r, b, lam, v, io.f * inv_dE, io.gH, io.ldH);
+      if constexpr (ENT) {
+        if (io.gH) {
+          double2 g[K];
+#pragma unroll
+          for (int j = 0; j < K; ++j) {
+            g[j].x = row_lanes_sum<B>(lam.x * vn[j].x + lam.y * vn[j].y);   // conj(lam) v
+            g[j].y = row_lanes_sum<B>(lam.x * vn[j].y - lam.y * vn[j].x);
+          }
+          double* p = io.gH + 2 * r * (int64_t)io.ldH;
+          const double f = io.f * inv_dE;
+          if (b == 0)
+#pragma unroll
+            for (int j = 0; j < K; ++j) {   // (K > 0: every row has K neighbours)
+              p[2 * j] += f * g[j].x;
+              p[2 * j + 1] -= f * g[j].y;
+            }
+        }
+      } else if (!TR && io.gH) {
+        row_entry_grads<B, HOP, K>(A, r, b, lam, v, io.f * inv_dE, io.gH, io.ldH);
+      }
     }
   });
   if (NC == 0 || !v) return;
@@ -154,36 +211,46 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_pair_step(DevMat A, AdjPairI
       hva[c] = make_double2(0.0, 0.0);
       hvb[c] = make_double2(0.0, 0.0);
     }
+    double gu0 = 0.0;
+    if (grad && b == 0) gu0 = io.gU[r];
+    auto mul = [](double2 he, double2 y) {
+      return (HOP == HOP_COMPLEX || HOP == HOP_DICT) ? cmul(he, y) : cscale(he.x, y);
+    };
+    auto add_class = [&](int64_t e, bool ok, double2 ya, double2 yb) {
+      const double2 he0 = hop0_entry<HOP>(A, e, ok, P.seg);
+      const double2 ta = mul(he0, ya), tb = mul(he0, yb);
+      const int cls = (NC > 1) ? io.cls[HOP == HOP_DICT ? (int64_t)A.hidx[e] : e] : 0;   // (padding adds zero)
+#pragma unroll
+      for (int q = 0; q < (NC > 0 ? NC : 1); ++q) {
+        hva[q].x += q == cls ? ta.x : 0.0;
+        hva[q].y += q == cls ? ta.y : 0.0;
+        hvb[q].x += q == cls ? tb.x : 0.0;
+        hvb[q].y += q == cls ? tb.y : 0.0;
+      }
+    };
     if (io.xa) {
       const double d = A.diag[r];
       ha = cscale(d, io.xa[idx]);
       hb = cscale(d, io.xb[idx]);
+      for_entries<K>(w, [&](int j) {
+        const int64_t e = e0 + (int64_t)j * S;
+        int64_t cc;
+        const bool ok = col_entry<HOP>(A, r, e, &cc);
+        const double2 he = hop_entry<HOP>(A, e, ok, hu);
+        const double2 xa = io.xa[cc * B + b], xb = io.xb[cc * B + b];
+        ha = cadd(ha, mul(he, xa));
+        hb = cadd(hb, mul(he, xb));
+        if constexpr (NC > 0 && TR) add_class(e, ok, xa, xb);
+      });
     }
-    for (int j = 0; j < w; ++j) {
-      const int64_t e = e0 + (int64_t)j * S;
-      int64_t cc;
-      const bool ok = col_entry<HOP>(A, r, e, &cc);
-      const double2 he = hop_entry<HOP>(A, e, ok, hu);
-      double2 xa = make_double2(0.0, 0.0), xb = xa;
-      if (io.xa) {
-        xa = io.xa[cc * B + b];
-        xb = io.xb[cc * B + b];
-        ha = cadd(ha, (HOP == HOP_COMPLEX || HOP == HOP_DICT) ? cmul(he, xa) : cscale(he.x, xa));
-        hb = cadd(hb, (HOP == HOP_COMPLEX || HOP == HOP_DICT) ? cmul(he, xb) : cscale(he.x, xb));
-      }
-      if (NC > 0 && grad) {
-        const double2 va = TR ? xa : io.a_m1[cc * B + b], vb = TR ? xb : io.b_m1[cc * B + b];
-        const double2 he0 = hop0_entry<HOP>(A, e, ok, P.seg);
-        const double2 ta = (HOP == HOP_COMPLEX || HOP == HOP_DICT) ? cmul(he0, va) : cscale(he0.x, va);
-        const double2 tb = (HOP == HOP_COMPLEX || HOP == HOP_DICT) ? cmul(he0, vb) : cscale(he0.x, vb);
-        const int cls = (NC > 1) ? (ok ? io.cls[HOP == HOP_DICT ? (int64_t)A.hidx[e] : e] : 0) : 0;
-#pragma unroll
-        for (int q = 0; q < (NC > 0 ? NC : 1); ++q)
-          if (q == cls) {
-            hva[q] = cadd(hva[q], ta);
-            hvb[q] = cadd(hvb[q], tb);
-          }
-      }
+    if constexpr (NC > 0 && !TR) {
+      if (grad)
+        for_entries<K>(w, [&](int j) {
+          const int64_t e = e0 + (int64_t)j * S;
+          int64_t cc;
+          const bool ok = col_entry<HOP>(A, r, e, &cc);
+          add_class(e, ok, io.a_m1[cc * B + b], io.b_m1[cc * B + b]);
+        });
     }
     // direct sensitivities of the raw dots
     double2 ga = cscale(w0, io.b_k[idx]);
@@ -206,7 +273,7 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_pair_step(DevMat A, AdjPairI
       const double2 qa = TR ? va : la, qb = TR ? vb : lbv;
 #pragma unroll
       for (int off = 1; off < B; off <<= 1) gu += __shfl_xor(gu, off);
-      if (b == 0) io.gU[r] += gu * inv_dE;
+      if (b == 0) io.gU[r] = gu0 + gu * inv_dE;
 #pragma unroll
       for (int q = 0; q < (NC > 0 ? NC : 1); ++q)
         if (NC > 0)
@@ -268,26 +335,39 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_sym_step(DevMat A, AdjPairIO
     double2 hv[NC > 0 ? NC : 1];
 #pragma unroll
     for (int c = 0; c < (NC > 0 ? NC : 1); ++c) hv[c] = make_double2(0.0, 0.0);
-    if (io.xa) h = cscale(A.diag[r], io.xa[idx]);
-    for (int j = 0; j < w; ++j) {
-      const int64_t e = e0 + (int64_t)j * S;
-      int64_t cc;
-      const bool ok = col_entry<HOP>(A, r, e, &cc);
-      const double2 he = hop_entry<HOP>(A, e, ok, hu);
-      double2 x = make_double2(0.0, 0.0);
-      if (io.xa) {
-        x = io.xa[cc * B + b];
-        h = cadd(h, (HOP == HOP_COMPLEX || HOP == HOP_DICT) ? cmul(he, x) : cscale(he.x, x));
-      }
-      if (NC > 0 && grad) {
-        const double2 v = TR ? x : io.a_m1[cc * B + b];
-        const double2 he0 = hop0_entry<HOP>(A, e, ok, P.seg);
-        const double2 t = (HOP == HOP_COMPLEX || HOP == HOP_DICT) ? cmul(he0, v) : cscale(he0.x, v);
-        const int cls = (NC > 1) ? (ok ? io.cls[HOP == HOP_DICT ? (int64_t)A.hidx[e] : e] : 0) : 0;
+    double gu0 = 0.0;
+    if (grad && b == 0) gu0 = io.gU[r];
+    auto mul = [](double2 he, double2 y) {
+      return (HOP == HOP_COMPLEX || HOP == HOP_DICT) ? cmul(he, y) : cscale(he.x, y);
+    };
+    auto add_class = [&](int64_t e, bool ok, double2 y) {
+      const double2 t = mul(hop0_entry<HOP>(A, e, ok, P.seg), y);
+      const int cls = (NC > 1) ? io.cls[HOP == HOP_DICT ? (int64_t)A.hidx[e] : e] : 0;   // (padding adds zero)
 #pragma unroll
-        for (int q = 0; q < (NC > 0 ? NC : 1); ++q)
-          if (q == cls) hv[q] = cadd(hv[q], t);
+      for (int q = 0; q < (NC > 0 ? NC : 1); ++q) {
+        hv[q].x += q == cls ? t.x : 0.0;
+        hv[q].y += q == cls ? t.y : 0.0;
       }
+    };
+    if (io.xa) {
+      h = cscale(A.diag[r], io.xa[idx]);
+      for_entries<K>(w, [&](int j) {
+        const int64_t e = e0 + (int64_t)j * S;
+        int64_t cc;
+        const bool ok = col_entry<HOP>(A, r, e, &cc);
+        const double2 x = io.xa[cc * B + b];
+        h = cadd(h, mul(hop_entry<HOP>(A, e, ok, hu), x));
+        if constexpr (NC > 0 && TR) add_class(e, ok, x);
+      });
+    }
+    if constexpr (NC > 0 && !TR) {
+      if (grad)
+        for_entries<K>(w, [&](int j) {
+          const int64_t e = e0 + (int64_t)j * S;
+          int64_t cc;
+          const bool ok = col_entry<HOP>(A, r, e, &cc);
+          add_class(e, ok, io.a_m1[cc * B + b]);
+        });
     }
     // direct sensitivities of the raw dots
     double2 g = cscale(w0, io.a_k[idx]);
@@ -306,7 +386,7 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_sym_step(DevMat A, AdjPairIO
       double gu = io.f * (p.x * v.x + p.y * v.y);
 #pragma unroll
       for (int off = 1; off < B; off <<= 1) gu += __shfl_xor(gu, off);
-      if (b == 0) io.gU[r] += gu * inv_dE;
+      if (b == 0) io.gU[r] = gu0 + gu * inv_dE;
 #pragma unroll
       for (int q = 0; q < (NC > 0 ? NC : 1); ++q)
         if (NC > 0) gc[q] += io.f * (l.x * hv[q].x + l.y * hv[q].y);
