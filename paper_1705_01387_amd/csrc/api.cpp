@@ -573,6 +573,21 @@ struct BwdSource {
   double sgn = 1.0;
 };
 
+// Row order of the reverse steps (class partials over the primary plan).  With class terms, eight neighbours a
+// row and 2^17 or more elements a vector block: the pencil order, whose workgroups hold rows of adjacent lattice
+// lines, so that a line's gathers hit the L1 of its neighbours' (512 x 512 with next-nearest neighbours,
+// every vector kept, 2,570 two-chain and 650 single steps: 88 ms plain, 75 so; 256 x 256 and one vector 0.88
+// against 0.97 ms a moment set, two vectors 1.15 both ways; fewer neighbours or no class terms lose 1 to 25 %).
+DevMat reverse_view(const Handle* h, int B, bool tr) {
+  DevMat D = h->view(B);
+  const int lb = Handle::log2B(B);
+  if (tr && h->uniform_width == 8 && h->n * B >= (int64_t(1) << 17) && h->d_units_p[lb]) {
+    D.pencil = 1;
+    D.units = h->d_units_p[lb];
+  }
+  return D;
+}
+
 // Reverse of the M-step recurrence started at phiR, with phiL the adjoint
 // source: when gU is set, parameter terms go to gU, (nc > 0) gcp and (gH set)
 // the per-entry gradients [n][max_nn] (re, im), with the
@@ -584,11 +599,11 @@ gpuqt_status run_backward(const Handle* h, int B, const double2* pL, const doubl
                           bool acc0, int s, double2* const* vec, hipStream_t sm,
                           double2* const* recorded = nullptr, double* gH = nullptr) {
   // recorded (s = 1 with parameter terms): v_1 .. v_{M-2} = T_n pR already computed
-  const DevMat D = h->view(B);                  // adjoint steps: primary plan (class partials)
   const DevMat F = h->view(B, FAM_MOMENT);      // forward recomputation: no partials
   const bool grad = gU != nullptr;
   // class terms one step late, from the rows' own forward vector (k_adjoint_step)
   const bool tr = grad && nc > 0 && !gH && h->sym_hop && M >= 2;
+  const DevMat D = reverse_view(h, B, tr);
   const int K = backward_pairs(M, s);
   double2* const* R = vec;
   double2* const* Lm = vec + 3;
@@ -731,7 +746,7 @@ gpuqt_status run_backward_pair(const Handle* h, int B, const double2* pL, const 
   double2* const* La = recorded ? vec : vec + 2 * K;   // rotating abar
   double2* const* Lb = La + 3;                         // rotating bbar
   const bool tr = gU && nc > 0 && h->sym_hop;   // class terms one step late (k_adjoint_pair_step)
-  const DevMat D = h->view(B);            // class partials over the primary plan
+  const DevMat D = reverse_view(h, B, tr);
   for (int k = K; k >= 0; --k) {
     if (k == 0 && !outA && !outB && !tr) break;
     AdjPairIO io{};
@@ -785,7 +800,7 @@ gpuqt_status run_backward_sym(const Handle* h, int B, const double2* ph, int M, 
   }
   double2* const* Lc = vec + K;   // rotating cbar
   const bool tr = gU && nc > 0 && h->sym_hop;   // class terms one step late (k_adjoint_sym_step)
-  const DevMat D = h->view(B);     // class partials over the primary plan
+  const DevMat D = reverse_view(h, B, tr);
   for (int k = K; k >= 0; --k) {
     if (k == 0 && !lam0 && !tr) break;
     AdjPairIO io{};

@@ -36,9 +36,10 @@ __device__ __forceinline__ void for_entries(int w, F&& f) {
 //
 // Class gradients (TR, where every class's hoppings are Hermitian by themselves): <lam_{n+1}| H~_c v_n> =
 // conj(<v_n| H~_c lam_{n+1}>), and H~_c lam_{n+1} is part of the product that gives lam_n.  So step n adds
-// the terms of step n + 1 from the rows' own v_n, and only lam_{n+1} is gathered.  Bound by the gathers'
-// latency (512 x 512 with next-nearest neighbours, two classes, us a step: two chains 20.5 with v gathered too,
-// @AP@ so; one chain of the Hermitian form 16.5, @AS@; one chain 14.2, @A1@).  Otherwise the terms of step n, with v_{n-1}
+// the terms of step n + 1 from the rows' own v_n, and only lam_{n+1} is gathered.  Bound by the gathers
+// and the vectors' traffic (512 x 512 with next-nearest neighbours, two classes, us a step: two chains 20.5 with v gathered
+// too and one entry's loads after another's, 16.3 so; one chain of the Hermitian form 16.5, 12.8; one
+// chain 14.2, 10.8).  Otherwise the terms of step n, with v_{n-1}
 // gathered.
 template <int B, int HOP, int K, int NC, bool TR>
 __global__ __launch_bounds__(kBlock) void k_adjoint_step(DevMat A, AdjIO io) {
