@@ -432,8 +432,9 @@ int timing_family(int mf) {
 // become free once the first launch has read its inputs.  dots go to part, sums to su.
 gpuqt_status run_march(const Handle* h, int B, int fam, int K, const double2* xa, const double2* xb, BufPool* pool,
                        const std::vector<const double2*>& late, double2* part, MarchSums* su, hipStream_t s,
-                       double2* const* keep = nullptr) {
-  // keep: every chain vector to its own buffer (rows of B columns), a_k to keep[k-1], b_k to keep[K+k-1]
+                       double2* const* keep = nullptr, bool dots = true) {
+  // keep: every chain vector to its own buffer (rows of B columns), a_k to keep[k-1], b_k to keep[K+k-1];
+  // without dots part is one scratch row
   const Handle::MarchDev& m = h->march[fam][Handle::log2B(B)];
   const MarchMat A = h->march_mat(fam, B);
   const int NC = (fam == MF_SYM || fam == MF_EVO) ? 1 : 2;
@@ -444,7 +445,7 @@ gpuqt_status run_march(const Handle* h, int B, int fam, int K, const double2* xa
   io.zero_b = NC == 2 && !xb;
   io.x[0] = xa;
   io.x[1] = NC == 2 ? (xb ? xb : xa) : nullptr;
-  io.k_end = K;
+  io.k_end = dots ? K : 0;
   io.part = part;
   if (su) {
     io.J = su->J;
@@ -597,8 +598,9 @@ DevMat reverse_view(const Handle* h, int B, bool tr) {
 gpuqt_status run_backward(const Handle* h, int B, const double2* pL, const double2* pR, int M,
                           const BwdSource& src, double* gU, double* gcp, int nc, double2* lam0,
                           bool acc0, int s, double2* const* vec, hipStream_t sm,
-                          double2* const* recorded = nullptr, double* gH = nullptr) {
-  // recorded (s = 1 with parameter terms): v_1 .. v_{M-2} = T_n pR already computed
+                          double2* const* recorded = nullptr, double* gH = nullptr, double2* scratch = nullptr) {
+  // recorded (s = 1 with parameter terms): v_1 .. v_{M-2} = T_n pR already computed; scratch (s = 1): a
+  // partial row that nobody reads
   const DevMat F = h->view(B, FAM_MOMENT);      // forward recomputation: no partials
   const bool grad = gU != nullptr;
   // class terms one step late, from the rows' own forward vector (k_adjoint_step)
@@ -638,7 +640,13 @@ gpuqt_status run_backward(const Handle* h, int B, const double2* pL, const doubl
     // forward: v_1 .. v_{M-2}, every one kept (v_n in sb(n), unless recorded);
     // then the reverse
     auto fwd = [&](int n) -> const double2* { return n == 0 ? pR : recorded ? recorded[n - 1] : sb(n); };
-    if (!recorded) {
+    // (256 x 193, two vectors, an entry's hopping each: 4.4 us a step by the general kernel, 1.6 in patches)
+    if (!recorded && scratch && M >= 3 && h->march_on(MF_SYM, B)) {
+      std::vector<double2*> kept(M - 2);
+      for (int n = 1; n <= M - 2; ++n) kept[n - 1] = sb(n);
+      gpuqt_status st;
+      if ((st = run_march(h, B, MF_SYM, M - 2, pR, nullptr, nullptr, {}, scratch, nullptr, sm, kept.data(), false))) return st;
+    } else if (!recorded) {
       const double2* prev2 = nullptr;
       const double2* prev1 = pR;
       for (int n = 1; n <= M - 2; ++n) {
@@ -733,7 +741,10 @@ gpuqt_status run_backward_pair(const Handle* h, int B, const double2* pL, const 
   double2* const* ch = recorded ? recorded : vec;
   auto fa = [&](int k) -> const double2* { return k == 0 ? pL : ch[k - 1]; };
   auto fb = [&](int k) -> const double2* { return k == 0 ? pR : ch[K + k - 1]; };
-  if (!recorded) {
+  if (!recorded && K > 0 && h->march_on(MF_PAIR, B)) {
+    gpuqt_status st;
+    if ((st = run_march(h, B, MF_PAIR, K, pL, pR, nullptr, {}, scratch, nullptr, sm, vec, false))) return st;
+  } else if (!recorded) {
     TimeScope ts(h, sm, FAM_PAIR, K);
     const DevMat F = h->view(B, FAM_PAIR);
     const int64_t row = (int64_t)F.G * B;
@@ -789,7 +800,10 @@ gpuqt_status run_backward_sym(const Handle* h, int B, const double2* ph, int M, 
   const int R = 2 * K + 2;
   HIP_TRY(launch_raw_weights(wts, h->n_seg * B, M, R, om, sm));
   auto fa = [&](int k) -> const double2* { return k == 0 ? ph : vec[k - 1]; };
-  {
+  if (K > 0 && h->march_on(MF_SYM, B)) {
+    gpuqt_status st;
+    if ((st = run_march(h, B, MF_SYM, K, ph, nullptr, nullptr, {}, scratch, nullptr, sm, vec, false))) return st;
+  } else {
     TimeScope ts(h, sm, FAM_SYM, K);
     const DevMat F = h->view(B, FAM_SYM);
     const int64_t row = (int64_t)F.G * B;
@@ -1695,7 +1709,8 @@ gpuqt_status gpuqt_moments_backward(gpuqt_h hh, int32_t B, const double* phiL, c
     src.wts = w;
     if ((st = run_backward(h, B, reinterpret_cast<const double2*>(phiL),
                            reinterpret_cast<const double2*>(phiR), M, src, grad_onsite, gcp, nc,
-                           reinterpret_cast<double2*>(lam0), false, s, vec.data(), sm, nullptr, grad_hop)))
+                           reinterpret_cast<double2*>(lam0), false, s, vec.data(), sm, nullptr, grad_hop,
+                           s == 1 ? reinterpret_cast<double2*>(base + W.off_part) + 2 * (int64_t)h->G * B : nullptr)))
       return st;
   }
   if (nc) HIP_TRY(launch_reduce_classes(gcp, h->G, nc, h->n_class, grad_class, sm));
@@ -1856,6 +1871,8 @@ static gpuqt_status vac_backward_impl(const Handle* h, int32_t B, const double* 
       aR = oR;
     }
   }
+  // a partial row that nobody reads (keep: the workspace has five)
+  double2* const scratch = keep && s == 1 ? reinterpret_cast<double2*>(base + W.off_part) + 2 * (int64_t)h->G * B : nullptr;
   // reverse over the rows
   int cl = 0, cr = 0;
   HIP_TRY(launch_scale(D, B, nullptr, gL[0], nullptr, 0, sm));
@@ -1880,7 +1897,7 @@ static gpuqt_status vac_backward_impl(const Handle* h, int32_t B, const double* 
       // per-entry gradients also when every vector is kept: the plain
       // recurrence, not the two-chain form, whose pool it fits)
       if ((st = run_backward(h, B, phiL, psiR(k), M, src, grad_onsite, gcp, nc, gR[cr], true, s,
-                             pool.data(), sm, nullptr, grad_hop)))
+                             pool.data(), sm, nullptr, grad_hop, scratch)))
         return st;
       // gphiL = sum_n w_n T_n psi_R(k) (no parameter terms)
       if ((st = run_backward(h, B, psiR(k), phiL, M, src, nullptr, nullptr, 0, gphiL, false, s,
@@ -1907,10 +1924,10 @@ static gpuqt_status vac_backward_impl(const Handle* h, int32_t B, const double* 
     const std::vector<double2*> rec = tape ? T.evolution(k - 1, npk) : std::vector<double2*>();
     const bool have = tape && npk >= 3;
     if ((st = run_backward(h, B, gL[cl], psiL(k - 1), npk, ev, grad_onsite, gcp, nc, gL[cl ^ 1], false,
-                           s, pool.data(), sm, have ? rec.data() : nullptr, grad_hop)))
+                           s, pool.data(), sm, have ? rec.data() : nullptr, grad_hop, scratch)))
       return st;
     if ((st = run_backward(h, B, gR[cr], psiR(k - 1), npk, ev, grad_onsite, gcp, nc, gR[cr ^ 1], false,
-                           s, pool.data(), sm, have ? rec.data() + (npk - 1) : nullptr, grad_hop)))
+                           s, pool.data(), sm, have ? rec.data() + (npk - 1) : nullptr, grad_hop, scratch)))
       return st;
     cl ^= 1;
     cr ^= 1;

@@ -309,7 +309,7 @@ hipError_t launch_patch_pattern(int family, int lanes, const MarchMat& A, const 
         else k_patch<PAT, F, HOP, L, C, false, KP><<<grid, L, 0, s>>>(A, io);
         return hipGetLastError();
       };
-      if constexpr (F == MF_PAIR || F == MF_EVO2) {
+      if constexpr (F == MF_SYM || F == MF_PAIR || F == MF_EVO2) {
         if (io.keep) return kept(std::true_type{});
       }
       return kept(std::false_type{});
