@@ -1,17 +1,17 @@
 // The patch kernel: the steps of march.h's launches for lattices too small for a
-// march to fill the chip, for chains and for squares with next-nearest neighbours.  A workgroup holds a patch of cells with a
-// margin of T cells on every side, one cell a lane, takes T steps of the recurrence on
-// it in place and writes the two last ones.  Nothing moves between the steps but the
+// march to fill the chip, for chains and for squares with next-nearest neighbours.  A
+// workgroup holds a patch of cells with a margin of T cells on every side, one cell a lane,
+// takes T steps of the recurrence on it in place and writes the two last ones.  Nothing moves between the steps but the
 // cells' values through LDS (double-buffered: one barrier a step).
 //
 // What bounds it: on a small lattice the launch itself (about 4 us with its loads, stores
 // and the dots' sums) and its barriers: 8 steps of the Hermitian set on 64 x 64 take 6.5 us in
-// workgroups of 640 cells, where the march's run of 17 or more iterations takes 14 to
-// 16.  On a chain the vectors' traffic, two
-// elements read and two written for 24 steps, and the double arithmetic: 8 M cells take 8.5 us a step
-// (Hermitian set, 4 cells a lane) and 18 (evolution + commutator, 2 cells a lane, 16 steps: 21) where
-// single steps take 81 and 268.  With next-nearest neighbours the LDS reads (eight a cell and step): 512 x 512
-// 4.7 us a step where single steps take 7.6 (Hermitian set), 6.7 and 9.9 (two chains).
+// workgroups of 640 cells, where the march's run of 17 or more iterations takes 14 to 16.
+// On a chain the vectors' traffic, two elements read and two written for 24 steps, and the
+// double arithmetic: 8 M cells take 8.5 us a step (Hermitian set, 4 cells a lane) and 18
+// (evolution + commutator, 2 cells a lane; 21 with 16 steps) where single steps take 81 and
+// 268.  With next-nearest neighbours the LDS reads, eight a cell and step: 512 x 512 takes
+// 4.7 us a step (Hermitian set) and 6.7 (two chains) where single steps take 7.6 and 9.9.
 #pragma once
 
 #include "march_core.h"
@@ -20,9 +20,9 @@ namespace gpuqt {
 namespace march {
 
 // C cells a lane (cell = lane + j LANES of the patch; C = 1 in two dimensions); io.steps steps,
-// at most the margin A.T and a multiple of kPatchUnroll: the loop is unrolled that far and no further, since a workgroup runs
-// its code once and longer code waits for instructions (8 steps of the Hermitian set on
-// 64 x 64: 9.5 us unrolled, 7.1 us rolled).
+// at most the margin A.T and a multiple of kPatchUnroll: the loop is unrolled that far and no
+// further, since a workgroup runs its code once and longer code waits for instructions (8 steps
+// of the Hermitian set on 64 x 64: 9.5 us unrolled, 7.1 us rolled).
 template <int PAT, int FAM, int HOP, int LANES, int C, bool FIRST, bool KEEP>
 __global__ __launch_bounds__(LANES) void k_patch(MarchMat A, MarchIO io) {
   constexpr int NC = two_chains(FAM) ? 2 : 1;
