@@ -202,15 +202,13 @@ bool detect_lattice(const gpuqt_h_desc* d, const HostLayout& L, const int32_t bo
             while (q < nw && want[q] != c) ++q;
             right = q == 0 || q == 4 || q == 6;
             left = q == 1 || q == 5 || q == 7;
-            if (q == nw) {
+            // the first row has to name each neighbour once, the others in its order
+            const bool first = s == 0 && z == 0 && x == 0;
+            if (q == nw || (first ? M->slot[q] >= 0 : M->slot[q] != j)) {
               M->pattern = MARCH_NONE;
               return false;
             }
-            if (s == 0 && z == 0 && x == 0) M->slot[q] = j;
-            if (M->slot[q] != j) {
-              M->pattern = MARCH_NONE;
-              return false;
-            }
+            M->slot[q] = j;
           }
           if (!dx_ok || (same && z > 0)) continue;
           const double v = diff(e);

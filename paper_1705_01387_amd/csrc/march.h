@@ -57,7 +57,7 @@ struct MarchLattice {
   int32_t pattern = MARCH_NONE;
   int32_t parity = 0;           // BRICK
   int32_t open = 0;             // 1: no bonds between the columns Lx - 1 and 0 (SQUARE, one hopping)
-  int32_t slot[8] = {0, 0, 0, 0, 0, 0, 0, 0};   // stored slot of each neighbour above (per-entry hoppings)
+  int32_t slot[8] = {-1, -1, -1, -1, -1, -1, -1, -1};   // stored slot of each neighbour above (-1: not looked at)
   // position differences: that of the +x neighbour of each column (dxcol, [sum of the Lx], the
   // -x neighbour of the next column having its negative), the same on every row of a
   // segment, 0 for the other neighbours; in a box one value, dx
