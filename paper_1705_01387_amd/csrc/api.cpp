@@ -535,7 +535,8 @@ gpuqt_status march_velocity(const Handle* h, int B, const double2* in, double2* 
 // One time step of planar chains: out_a = U(dt) a, and (fam MF_EVO2) out_b = U(dt) b or (MF_MSD)
 // out_b = [X, U(dt)] a + U(dt) b, b NULL for zero.  The pool holds 4 buffers per chain, of which
 // `late` may come back after the first launch.  move: the sums end in buffers taken from the
-// pool instead (su.last), out_a and out_b being scratch until then.
+// pool instead (su.last), out_a and out_b being scratch until then.  keep (Np >= 2): chain vectors of their
+// own, as in run_march, and every vector then has rows of B columns.
 gpuqt_status march_evolve(const Handle* h, int B, int fam, double dt, int Np, const double2* a, const double2* b,
                           double2* out_a, double2* out_b, BufPool* pool, const std::vector<const double2*>& late,
                           double* Jtab, bool move, MarchSums* su, hipStream_t s, double2* const* keep = nullptr) {
@@ -548,11 +549,6 @@ gpuqt_status march_evolve(const Handle* h, int B, int fam, double dt, int Np, co
   su->sgn = dt >= 0 ? 1.0 : -1.0;
   if (Np == 1) {
     gpuqt_status st;
-    if (keep) {   // rows of B columns
-      HIP_TRY(launch_scale(h->view(B), B, a, out_a, Jtab, Np, s));
-      HIP_TRY(launch_scale(h->view(B), B, b, out_b, Jtab, Np, s));
-      return GPUQT_OK;
-    }
     if (move) {
       su->last[0] = pool->take();
       su->last[1] = fam == MF_EVO ? nullptr : pool->take();
@@ -1543,7 +1539,7 @@ static gpuqt_status vac_impl(const Handle* h, int32_t B, const double* phi, int3
       double2* Rn = tape ? T.psiR(k + 1) : Rbuf[ri ^ 1];
       // both states advance with the same U(-dt): one two-chain series
       const std::vector<double2*> ev = tape ? T.evolution(k, np_k) : std::vector<double2*>();
-      if (marched) {
+      if (marched && np_k > 1) {   // (one term has no chain: the states are scaled, row by row of B)
         MarchSums su;
         if ((st = march_evolve(h, B, MF_EVO2, -dt[k], np_k, psiL, psiR, Ln, Rn, nullptr, {}, J, false, &su, s,
                                ev.data())))
