@@ -490,11 +490,12 @@ gpuqt_status run_march(const Handle* h, int B, int fam, int K, const double2* xa
 }
 
 // Moments of the Hermitian set phi ([n][B], or planar) into mu (complex) or mu_re, by the march
-// when the handle has it and `buf` holds four vectors, else by the general step with buf[0], buf[1].
+// when that pays and `buf` holds four vectors (planar: always, march_on and four vectors given), else by the
+// general step with buf[0], buf[1].
 gpuqt_status run_moment_set(const Handle* h, int B, const double2* phi, bool planar, int M, double2* part,
                             double2* const* buf, int nbuf, double2* mu, double* mu_re, hipStream_t s) {
   gpuqt_status st;
-  if (nbuf >= 4 && h->march_on(MF_SYM, B)) {
+  if (planar || (nbuf >= 4 && h->march_pays(MF_SYM, B, pair_steps(M), 1))) {
     const double2* x = phi;
     BufPool pool;
     std::vector<const double2*> late;
@@ -637,7 +638,7 @@ gpuqt_status run_backward(const Handle* h, int B, const double2* pL, const doubl
     // then the reverse
     auto fwd = [&](int n) -> const double2* { return n == 0 ? pR : recorded ? recorded[n - 1] : sb(n); };
     // (256 x 193, two vectors, an entry's hopping each: 4.4 us a step by the general kernel, 1.6 in patches)
-    if (!recorded && scratch && M >= 3 && h->march_on(MF_SYM, B)) {
+    if (!recorded && scratch && M >= 3 && h->march_pays(MF_SYM, B, M - 2, 0)) {
       std::vector<double2*> kept(M - 2);
       for (int n = 1; n <= M - 2; ++n) kept[n - 1] = sb(n);
       gpuqt_status st;
@@ -737,7 +738,7 @@ gpuqt_status run_backward_pair(const Handle* h, int B, const double2* pL, const 
   double2* const* ch = recorded ? recorded : vec;
   auto fa = [&](int k) -> const double2* { return k == 0 ? pL : ch[k - 1]; };
   auto fb = [&](int k) -> const double2* { return k == 0 ? pR : ch[K + k - 1]; };
-  if (!recorded && K > 0 && h->march_on(MF_PAIR, B)) {
+  if (!recorded && h->march_pays(MF_PAIR, B, K, 0)) {
     gpuqt_status st;
     if ((st = run_march(h, B, MF_PAIR, K, pL, pR, nullptr, {}, scratch, nullptr, sm, vec, false))) return st;
   } else if (!recorded) {
@@ -796,7 +797,7 @@ gpuqt_status run_backward_sym(const Handle* h, int B, const double2* ph, int M, 
   const int R = 2 * K + 2;
   HIP_TRY(launch_raw_weights(wts, h->n_seg * B, M, R, om, sm));
   auto fa = [&](int k) -> const double2* { return k == 0 ? ph : vec[k - 1]; };
-  if (K > 0 && h->march_on(MF_SYM, B)) {
+  if (h->march_pays(MF_SYM, B, K, 0)) {
     gpuqt_status st;
     if ((st = run_march(h, B, MF_SYM, K, ph, nullptr, nullptr, {}, scratch, nullptr, sm, vec, false))) return st;
   } else {
@@ -965,6 +966,8 @@ gpuqt_status gpuqt_build_h(const gpuqt_h_desc* desc, void* stream, gpuqt_h* out)
           md.lanes = mp.lanes;
           md.items = mp.items;
           md.patch = mp.patch;
+          md.launch_us = plan_launch_us(h->lat, h->hop_mode, f, 1 << lb, cus, mp);
+          md.step_us = general_step_us(f, h->hop_mode, h->n, h->nnz, 1 << lb);
           auto put = [&](const void* src, size_t bytes) {
             const size_t off = round_up(march_host.size(), 16);
             march_host.resize(off + bytes);
@@ -1309,7 +1312,10 @@ gpuqt_status gpuqt_evolve(gpuqt_h hh, int32_t B, double dt, int32_t Np, const do
   double2* out = reinterpret_cast<double2*>(psi_out);
   double2* cout = reinterpret_cast<double2*>(chi_out);
   const WsLayout WM = ws_layout(h, march_vectors(op), B, 0, np);
-  if (march_covers(h, op, B) && ws_bytes >= WM.total) {
+  // (a block's inputs and outputs change layout; one term is a scaling of each)
+  const int mf = chi_out ? MF_MSD : MF_EVO;
+  if (ws_bytes >= WM.total && (np > 1 ? h->march_pays(mf, B, np - 1, (chi_in ? 2 : 1) + (chi_out ? 2 : 1))
+                                      : B == 1 && h->march_on(mf, B))) {
     hipStream_t s = static_cast<hipStream_t>(stream);
     BufPool pool;
     for (int i = 0; i < march_vectors(op); ++i) pool.free.push_back(reinterpret_cast<double2*>(base + i * WM.vec_bytes));
@@ -1329,7 +1335,7 @@ gpuqt_status gpuqt_evolve(gpuqt_h hh, int32_t B, double dt, int32_t Np, const do
     const double2 *pa = nullptr, *pb = nullptr;
     if ((st = planar(in, &pa)) || (st = planar(cin, &pb))) return st;
     MarchSums su;
-    if ((st = march_evolve(h, B, chi_out ? MF_MSD : MF_EVO, dt, np, pa, pb, out, cout, &pool, late, J, B > 1, &su, s)))
+    if ((st = march_evolve(h, B, mf, dt, np, pa, pb, out, cout, &pool, late, J, B > 1, &su, s)))
       return st;
     if (B > 1) {
       HIP_TRY(launch_from_planar(h->n, B, su.last[0], out, s));
@@ -1375,9 +1381,14 @@ static gpuqt_status check_series(const Handle* h, int32_t B, const double* phi, 
   return GPUQT_OK;
 }
 
-static int max_terms(const Handle* h, int32_t n_t, const double* dt, int32_t Np) {
+// (all, if set: the terms of every step)
+static int max_terms(const Handle* h, int32_t n_t, const double* dt, int32_t Np, std::vector<int>* all = nullptr) {
   int best = 1;
-  for (int k = 0; k < n_t; ++k) best = std::max(best, terms_for(h, dt[k], Np));
+  for (int k = 0; k < n_t; ++k) {
+    const int np = terms_for(h, dt[k], Np);
+    best = std::max(best, np);
+    if (all) all->push_back(np);
+  }
   return best;
 }
 
@@ -1419,6 +1430,17 @@ struct VacTape {
   }
 };
 
+// Whether a series of n_t rows (GPUQT_OP_VAC, GPUQT_OP_MSD) and time steps of `terms` goes to the marches as a whole:
+// the rows' moment sets and the steps together take no longer than by the general kernels.  (One family may
+// lose and the other win: a box of 125^3, two chains 56 us a step against 51, two-vector evolution 51 against 73.)
+static bool series_pays(const Handle* h, int op, int B, int n_t, int M, const std::vector<int>& terms) {
+  if (!march_covers(h, op, B)) return false;
+  const bool vac = op == GPUQT_OP_VAC;
+  double loss = n_t * h->march_loss_us(vac ? MF_PAIR : MF_SYM, B, pair_steps(M)) + planar_us(h->n, B);
+  for (int np : terms) loss += h->march_loss_us(vac ? MF_EVO2 : MF_MSD, B, np - 1);
+  return loss <= 0.0;
+}
+
 static gpuqt_status vac_tape_check(const Handle* h, int B, int n_t, int M, int P, void* tape,
                                    size_t tape_bytes, VacTape* T) {
   T->vec_bytes = round_up((size_t)h->n * (size_t)B * 16u, 256);
@@ -1437,7 +1459,7 @@ static gpuqt_status vac_tape_check(const Handle* h, int B, int n_t, int M, int P
 // the second launch may overwrite, and psi_R, which it may not; the evolution to the next
 // row may overwrite both states once its first launch has read them.
 static gpuqt_status vac_march(const Handle* h, int32_t B, const double2* phi, int32_t n_t, const double* dt, int32_t M,
-                              int32_t Np, double* out, char* base, const WsLayout& W, hipStream_t s) {
+                              const std::vector<int>& terms, double* out, char* base, const WsLayout& W, hipStream_t s) {
   gpuqt_status st;
   BufPool pool;
   for (int i = 0; i < march_vectors(GPUQT_OP_VAC); ++i)
@@ -1466,13 +1488,12 @@ static gpuqt_status vac_march(const Handle* h, int32_t B, const double2* phi, in
       pool.give(phiL);
     }
     if (k + 1 < n_t) {
-      const int np = terms_for(h, dt[k], Np);
       double2 *Ln = pool.take(), *Rn = pool.take();
       std::vector<const double2*> late = {psiR};
       if (own_L) late.push_back(psiL);
       BufPool q = pool;
       MarchSums su;
-      if ((st = march_evolve(h, B, MF_EVO2, -dt[k], np, psiL, psiR, Ln, Rn, &q, late, J, false, &su, s))) return st;
+      if ((st = march_evolve(h, B, MF_EVO2, -dt[k], terms[k], psiL, psiR, Ln, Rn, &q, late, J, false, &su, s))) return st;
       for (const double2* p : late) pool.give(p);
       psiL = Ln;
       psiR = Rn;
@@ -1488,7 +1509,8 @@ static gpuqt_status vac_impl(const Handle* h, int32_t B, const double* phi, int3
   gpuqt_status st = check_series(h, B, phi, n_t, dt, M, Np, out);
   if (st) return st;
   if (n_t == 0 || M == 0) return GPUQT_OK;
-  const int np = max_terms(h, n_t - 1, dt, Np);
+  std::vector<int> terms;
+  const int np = max_terms(h, n_t - 1, dt, Np, &terms);
   VacTape T;
   if (tape && (st = vac_tape_check(h, B, n_t, M, np, tape, tape_bytes, &T))) return st;
   const WsLayout W = ws_layout(h, op_vectors(GPUQT_OP_VAC), B, moment_rows(M), np);
@@ -1501,9 +1523,9 @@ static gpuqt_status vac_impl(const Handle* h, int32_t B, const double* phi, int3
   double2* part = reinterpret_cast<double2*>(base + W.off_part);
   double* J = reinterpret_cast<double*>(base + W.off_J);
   const WsLayout WM = ws_layout(h, march_vectors(GPUQT_OP_VAC), B, moment_rows(M), np);
-  const bool marched = march_covers(h, GPUQT_OP_VAC, B) && ws_bytes >= WM.total;
+  const bool marched = series_pays(h, GPUQT_OP_VAC, B, n_t, M, terms) && ws_bytes >= WM.total;
   if (marched && !tape)
-    return vac_march(h, B, reinterpret_cast<const double2*>(phi), n_t, dt, M, Np, out, base, WM, s);
+    return vac_march(h, B, reinterpret_cast<const double2*>(phi), n_t, dt, M, terms, out, base, WM, s);
   const DevMat D = h->view(B);
   // psi_L = phi (input, read only), psi_R = V phi
   const double2* psiL = reinterpret_cast<const double2*>(phi);
@@ -1534,7 +1556,7 @@ static gpuqt_status vac_impl(const Handle* h, int32_t B, const double* phi, int3
       HIP_TRY(launch_reduce_moments(part, M, h->G_of(B, FAM_PAIR), B, h->n_seg, h->blk0_of(B, FAM_PAIR), 1,
                                     nullptr, out + row * k, s));
     if (k + 1 < n_t) {
-      const int np_k = terms_for(h, dt[k], Np);
+      const int np_k = terms[k];
       double2* Ln = tape ? T.psiL(k + 1) : (psiL == Lbuf[0]) ? Lbuf[1] : Lbuf[0];
       double2* Rn = tape ? T.psiR(k + 1) : Rbuf[ri ^ 1];
       // both states advance with the same U(-dt): one two-chain series
@@ -1587,7 +1609,8 @@ gpuqt_status gpuqt_msd(gpuqt_h hh, int32_t B, const double* phi, int32_t n_t, co
   gpuqt_status st = check_series(h, B, phi, n_t, dt, M, Np, out);
   if (st) return st;
   if (n_t == 0 || M == 0) return GPUQT_OK;
-  const int np = max_terms(h, n_t, dt, Np);
+  std::vector<int> terms;
+  const int np = max_terms(h, n_t, dt, Np, &terms);
   const WsLayout W = ws_layout(h, op_vectors(GPUQT_OP_MSD), B, moment_rows(M), np);
   if (!ws || ws_bytes < W.total) return fail(GPUQT_ERR_WORKSPACE, "workspace too small");
   if (!aligned16(ws)) return fail(GPUQT_ERR_ARG, "workspace is not 16-byte aligned");
@@ -1598,7 +1621,7 @@ gpuqt_status gpuqt_msd(gpuqt_h hh, int32_t B, const double* phi, int32_t n_t, co
   double2* part = reinterpret_cast<double2*>(base + W.off_part);
   double* J = reinterpret_cast<double*>(base + W.off_J);
   const WsLayout WM = ws_layout(h, march_vectors(GPUQT_OP_MSD), B, moment_rows(M), np);
-  if (march_covers(h, GPUQT_OP_MSD, B) && ws_bytes >= WM.total) {
+  if (series_pays(h, GPUQT_OP_MSD, B, n_t, M, terms) && ws_bytes >= WM.total) {
     // by the marches: every vector planar; psi of row 0 may be the caller's phi, chi is
     // zero there, and both may be overwritten once a step's first launch has read them
     BufPool pool;
@@ -1621,7 +1644,7 @@ gpuqt_status gpuqt_msd(gpuqt_h hh, int32_t B, const double* phi, int32_t n_t, co
       if (chi) late.push_back(chi);
       BufPool q = pool;   // every buffer is free again once the step is done
       MarchSums su;
-      if ((st = march_evolve(h, B, MF_MSD, dt[k], terms_for(h, dt[k], Np), psi, chi, Pn, Cn, &q, late, J, false, &su, s)))
+      if ((st = march_evolve(h, B, MF_MSD, dt[k], terms[k], psi, chi, Pn, Cn, &q, late, J, false, &su, s)))
         return st;
       for (const double2* p : late) pool.give(p);
       psi = Pn;
@@ -1640,7 +1663,7 @@ gpuqt_status gpuqt_msd(gpuqt_h hh, int32_t B, const double* phi, int32_t n_t, co
   int pi = 0;
   const int64_t row = (int64_t)h->n_seg * B * M;
   for (int k = 0; k < n_t; ++k) {
-    const int np_k = terms_for(h, dt[k], Np);
+    const int np_k = terms[k];
     double2* Pn = Pbuf[pi];
     double2* Cn = Cbuf[pi];
     if ((st = run_evolve(h, B, dt[k], np_k, psi, Pn, chi, Cn, V(4), V(5), V(6), V(7), V(8), J, s)))

@@ -171,6 +171,7 @@ struct Handle {
     const MarchSeg* segs = nullptr;
     const int32_t* item0 = nullptr;
     int32_t T = 0, lanes = 0, items = 0, patch = 0;
+    double launch_us = 0.0, step_us = 0.0;   // estimated: a launch of T steps, a step of the general kernels
   };
   MarchDev march[kMarchFamilies][kNumB];
   char* d_march = nullptr;
@@ -180,6 +181,21 @@ struct Handle {
   bool march_on(int fam, int B) const {
     return lat.pattern != MARCH_NONE && use_box && march[fam][log2B(B)].T > 0 &&
            (fam != MF_MSD || (use_box_msd && lat.dx_ok));
+  }
+  // Estimated time of K steps by the family's march (march_on) less that by the general kernels: a march
+  // takes whole launches, a patch the steps that are left, rounded up to kPatchUnroll.
+  double march_loss_us(int fam, int B, int K) const {
+    const MarchDev& m = march[fam][log2B(B)];
+    const int left = K % m.T, steps = (left + kPatchUnroll - 1) / kPatchUnroll * kPatchUnroll;
+    double t = K / m.T * m.launch_us;
+    if (left) t += m.patch ? kPatchFixedUs + (m.launch_us - kPatchFixedUs) * steps / m.T : m.launch_us;
+    return t - 1.05 * K * m.step_us;
+  }
+  // Whether K steps go to the march: it exists, is on, and takes no longer with `layouts` changes of a
+  // block's layout.  (Few steps do not fill a launch: 2000 x 2000, one vector, 55 us against 41 for a single Hermitian
+  // step and against 94 for two.)
+  bool march_pays(int fam, int B, int K, int layouts) const {
+    return march_on(fam, B) && march_loss_us(fam, B, K) + layouts * planar_us(n, B) <= 0.0;
   }
   MarchMat march_mat(int fam, int B) const {
     const MarchDev& m = march[fam][log2B(B)];

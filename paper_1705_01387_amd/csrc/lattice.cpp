@@ -427,4 +427,50 @@ bool plan_patch(const MarchLattice& M, const std::vector<int64_t>& seg_off, int 
   return true;
 }
 
+// Estimates from per-step times (events around 64 steps) of every family by marches or patches and by the general
+// kernels: 901 pairs of lattice and block width on one MI355X, boxes of 125 to 2 M sites, squares, open squares and brick
+// lattices of 256 to 1.6 M sites and any shape down to strips of four columns, with one hopping and one an
+// entry, B = 1, 2, 4, 16.  A launch costs a constant and a time per iteration of a round of workgroups.  Where
+// the two times were within a factor of 2.5, the choice by these estimates missed the faster one by 5 % or more
+// in 40 of 900 places, by at most 1.6 (strips); marches everywhere were slower in 500, up to 20 times: small
+// boxes, whose launch takes 14 us or more for three steps of 3.5 us (20^3, one vector: Hermitian step 4.65 us
+// against 3.56 general, MSD term 10.8 against 3.6, two chains 15.3 against 3.8; 60^3: 5.6 / 6.1, 13.3 / 10.9 and
+// 17.9 / 7.2), and strips, whose tiles own few of their cells (5 x 5 x 20,000, four vectors: 93 against
+// 25; squares of 4 x 200,000, four vectors: 42 against 33).
+double plan_launch_us(const MarchLattice& M, int hop_mode, int family, int B, int cus, const MarchPlan& p) {
+  auto ceil_div = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+  const bool one = family == MF_SYM || family == MF_EVO, entry = hop_mode != HOP_UNIFORM;
+  int zc = 0;
+  for (const MarchSeg& q : p.segs) zc = std::max(zc, (int)q.zc);
+  const int64_t per_cu = ceil_div((int64_t)p.items * B, cus);
+  if (p.patch) {
+    if (M.pattern == MARCH_CHAIN) return 8.7 + (entry ? 9.0 : 7.0) * zc * per_cu;
+    const double full = (one ? 4.5 : 6.6) * (entry ? 1.15 : 1.0) * (M.pattern == MARCH_NNN ? 1.5 : 1.0);
+    return kPatchFixedUs + full * (p.T == 8 && p.lanes == 1024 ? 1.5 : 1.0) * zc * per_cu;
+  }
+  const int64_t iters = ceil_div(zc + 2 * p.T, 3) * 3;
+  // fixed time of a launch, time of an iteration: SYM, PAIR, EVO, EVO2, MSD
+  static const double box[5][2] = {{3.0, 1.25}, {3.0, 5.8}, {3.0, 1.5}, {2.0, 3.5}, {2.0, 3.9}};
+  static const double flat[5][2] = {{14.0, 0.30}, {10.0, 0.80}, {8.0, 0.35}, {12.0, 0.70}, {12.0, 0.72}};
+  static const double bonds[5][2] = {{11.0, 0.42}, {9.0, 0.82}, {8.0, 0.48}, {10.0, 0.80}, {10.0, 0.85}};
+  if (M.pattern == MARCH_BOX) return box[family][0] + box[family][1] * iters * per_cu;
+  const double(&c)[2] = entry ? bonds[family] : flat[family];
+  const double waves = 0.5 * (per_cu + (double)p.items * B / cus) * p.lanes / 256.0;   // as in plan_march
+  const double rounds = (double)ceil_div(per_cu, 512 / p.lanes);
+  return c[0] + c[1] * iters * (std::max(waves, 0.75) + (p.T >= 8 ? 0.7 : 0.1) * rounds) * (p.lanes > 64 ? 1.05 : 1.0);
+}
+
+// A step is a launch, at least, and 0.75 of that and its bytes at 5.2 TB/s (the measured steps lie within 15 %,
+// r.m.s.); the gathers of eight neighbours take longer than the bytes.
+double general_step_us(int family, int hop_mode, int64_t n, int64_t nnz, int B) {
+  static const double floor_us[5] = {3.7, 3.7, 2.9, 3.1, 3.3}, vec[5] = {48, 96, 80, 160, 160};
+  const double key[4] = {4, 12, 20, 2};   // bytes of an entry: column and hopping, or a table index
+  const double entry = key[hop_mode] + (family == MF_MSD && hop_mode != HOP_DICT ? 8.0 : 0.0);
+  const double bytes = (double)n * (vec[family] * B + 8.0) + entry * (double)nnz;
+  const double gather = nnz < 8 * n ? 1.0 : family == MF_SYM || family == MF_PAIR ? 1.4 : 1.25;
+  return gather * std::max(floor_us[family] + 0.2 * (B - 1), 0.75 * floor_us[family] + bytes / 5.2e6);
+}
+
+double planar_us(int64_t n, int B) { return B == 1 ? 0.0 : 2.2 + 32.0 * (double)n * B / 5.5e6; }
+
 }  // namespace gpuqt

@@ -48,6 +48,7 @@ struct MarchPlan {
   int32_t patch = 0;        // 1: patches (patch_core.h), 0: marches
   int32_t lanes = 0;        // threads per workgroup
   int32_t items = 0;        // work items of one vector; a launch has items x B workgroups
+  double launch_us = 0.0;   // estimated time of a launch of T steps (plan_launch_us)
   std::vector<MarchSeg> segs;
   std::vector<int32_t> item0;   // [n_seg + 1] first item of each segment
 };
@@ -135,6 +136,12 @@ hipError_t launch_march(int pattern, int hop_mode, int family, int lanes, int pa
 // two-dimensional patterns; chains and NNN have no marches.
 bool plan_patch(const MarchLattice& M, const std::vector<int64_t>& seg_off, int family, int B, int max_items, int cus,
                 MarchPlan* out);
+// Estimated times (microseconds): a launch of the plan's T steps, a single step of a family by the general
+// kernels (nnz: stored entries), and the change of layout of a block of vectors.
+double plan_launch_us(const MarchLattice& M, int hop_mode, int family, int B, int cus, const MarchPlan& p);
+double general_step_us(int family, int hop_mode, int64_t n, int64_t nnz, int B);
+double planar_us(int64_t n, int B);
+constexpr double kPatchFixedUs = 2.3;   // of a patch launch's time, what does not shrink with its steps
 // planar[c * n + r] = rows[r * B + c], and back
 hipError_t launch_to_planar(int64_t n, int B, const double2* rows, double2* planar, hipStream_t s);
 hipError_t launch_from_planar(int64_t n, int B, const double2* planar, double2* rows, hipStream_t s);
