@@ -416,8 +416,11 @@ gpuqt_status gpuqt_vac_backward_tape_workspace_size(gpuqt_h h, int32_t B, int32_
  * several recurrence steps per launch in one sweep along the slowest direction (rings and
  * small lattices: in patches held whole), the intermediate steps held on chip, for the moments of phiL = phiR
  * and the VAC, MSD and evolution series; blocks of vectors are then advanced as separate
- * vectors.  Built handles of such a lattice start with bits 26 and 27 set; the autotuner
- * times the Hermitian step's march against the best general variant and keeps the faster;
+ * vectors.  With bit 26 a call goes to the marches where their estimated time is no longer than
+ * the general kernels' (small boxes, strips of a few columns and calls of few steps stay with
+ * those).  Built handles of such a lattice start with bits 26 and 27 set; the autotuner
+ * times the Hermitian step's march alone, against the best general variant, and keeps the
+ * faster of the two for every family;
  * bit 27: the march of the fused MSD term (where the position differences are +-dx on the
  * x neighbours and 0 on the others);
  * bit 6 (with bit 1): the pencil order instead (built for segments with a row
@@ -434,14 +437,15 @@ gpuqt_status gpuqt_vac_backward_tape_workspace_size(gpuqt_h h, int32_t B, int32_
  * two-chain moment step, the two-vector evolution term and the MSD term are
  * each timed at the same caps and get their own (kernel_variant bits 8-25),
  * the two series terms also with the other load variant (bit 7 when that is
- * faster for the pair of them).
+ * faster for the pair of them); the MSD term is left out where it runs as a march.
  * Synchronises the stream.
  *   ws : device workspace of gpuqt_workspace_size(h, GPUQT_OP_AUTOTUNE, B, 0, 0) bytes
  *        (eight vectors); one of three vectors plus the partial sums tunes the
  *        Hermitian step only.
  *   times_us : NULL or HOST [7], microseconds per step of load/order variants 0..3, of
  *              the pencil order with plain (4) and non-temporal (5) loads, each at its best
- *              cap, and of the lattice march (6); 0 for what this handle and B do not have.
+ *              cap, and of the lattice march (6: per step that its launches took); 0 for what
+ *              this handle and B do not have.
  * Not safe while other calls on the handle are in flight.
  */
 gpuqt_status gpuqt_autotune(gpuqt_h h, int32_t B, void *ws, size_t ws_bytes, void *stream,

@@ -2105,13 +2105,18 @@ gpuqt_status gpuqt_autotune(gpuqt_h hh, int32_t B, void* ws, size_t ws_bytes, vo
             return run_march(h, B, MF_SYM, K, phi, nullptr, &pool, {}, partF, nullptr, s);
           },
           &mb);
-      const double per = (double)mb / ((K + T - 1) / T * T);
+      // steps taken: whole launches of a march; of a patch's last one the steps left, rounded up (run_march)
+      const int taken = !h->march[MF_SYM][lb].patch ? (K + T - 1) / T * T
+                        : K / T * T + (K % T + kPatchUnroll - 1) / kPatchUnroll * kPatchUnroll;
+      const double per = (double)mb / taken;
       if (times_us && !st) times_us[kTuneTimes - 1] = 1e3 * per;
       if (st || per >= (double)best / K) h->use_box = 0;
     }
   }
   const int march_sym = h->use_box;
-  h->use_box = 0;   // the general kernels' caps below
+  h->use_box_msd = h->lat.dx_ok;
+  const bool msd_marches = h->march_pays(MF_MSD, B, kTuneSteps, 0);   // no cap of the general term to look for
+  h->use_box = h->use_box_msd = 0;   // the general kernels' caps below
   // with room for their vectors, each of the two-chain moment, two-vector
   // evolution and MSD families also gets its own cap at this load variant
   if (!st && ws_bytes >= WF.total) {
@@ -2156,7 +2161,7 @@ gpuqt_status gpuqt_autotune(gpuqt_h hh, int32_t B, void* ws, size_t ws_bytes, vo
     for (int flip = 0; flip < 2 && !st; ++flip) {
       h->series_nt_flip = flip;
       float te = 0.0f, tm = 0.0f;
-      if ((st = tune_family(FAM_EVOLVE_PAIR, &te)) || (st = tune_family(FAM_MSD, &tm))) break;
+      if ((st = tune_family(FAM_EVOLVE_PAIR, &te)) || (!msd_marches && (st = tune_family(FAM_MSD, &tm)))) break;
       tot[flip] = te + tm;
       cap_ev[flip] = h->fam_cap[FAM_EVOLVE_PAIR];
       cap_msd[flip] = h->fam_cap[FAM_MSD];
