@@ -152,20 +152,24 @@ bool detect_lattice(const gpuqt_h_desc* d, const HostLayout& L, const int32_t bo
   auto diff = [&](int64_t e) { return L.hop_mode == HOP_DICT ? L.dxtab[L.hidx[e]] : L.dx[e]; };
   bool dx_ok = true;
   if (chain) {
+    const int64_t S = L.S, e00 = entry(0);
+    const bool first = L.col[e00] == 1;   // row 0 names +x first
+    M->slot[0] = first ? 0 : 1;
+    M->slot[1] = first ? 1 : 0;
+    M->dx = diff(first ? e00 : e00 + S);
+    const double* dx = L.hop_mode == HOP_DICT ? nullptr : L.dx.data();
     for (int s = 0; s < n_seg; ++s) {
       const int64_t off = L.seg_off[s], end = L.seg_off[s + 1];
       for (int64_t r = off; r < end; ++r) {
-        const int64_t e0 = entry(r), e1 = e0 + (int64_t(1) << ls);
+        const int64_t e0 = 2 * (r & -S) + (r & (S - 1)), e1 = e0 + S;   // (every row has two entries)
         const int64_t xp = r + 1 == end ? off : r + 1, xm = r == off ? end - 1 : r - 1;
         const bool fwd = L.col[e0] == xp && L.col[e1] == xm;
         if (!fwd && !(L.col[e0] == xm && L.col[e1] == xp)) return false;
-        if (r == 0) {
-          M->slot[fwd ? 0 : 1] = 0;
-          M->slot[fwd ? 1 : 0] = 1;
-          M->dx = diff(fwd ? e0 : e1);
+        if (slots && fwd != first) return false;
+        if (dx_ok) {
+          const double d0 = dx ? dx[e0] : diff(e0), d1 = dx ? dx[e1] : diff(e1);
+          dx_ok = (fwd ? d0 : d1) == M->dx && (fwd ? d1 : d0) == -M->dx;
         }
-        if (slots && fwd != (M->slot[0] == 0)) return false;
-        dx_ok = dx_ok && diff(fwd ? e0 : e1) == M->dx && diff(fwd ? e1 : e0) == -M->dx;
       }
     }
     M->pattern = MARCH_CHAIN;

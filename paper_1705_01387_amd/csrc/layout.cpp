@@ -551,6 +551,18 @@ void pencil_units(const std::vector<int64_t>& seg_off, const std::vector<int64_t
   }
 }
 
+// Whether c[0 .. K) are the K different rows e[0 .. K), in any order.
+template <int K>
+static bool names_each(const int32_t* c, const int64_t (&e)[K]) {
+  int seen = 0;
+  for (int j = 0; j < K; ++j) {
+    int bit = 0;
+    for (int q = 0; q < K; ++q) bit |= c[j] == e[q] ? 1 << q : 0;
+    seen |= bit;
+  }
+  return seen == (1 << K) - 1;
+}
+
 bool detect_sheets(const gpuqt_h_desc* d, const std::vector<int64_t>& seg_off, std::vector<int32_t>* sheet) {
   sheet->clear();
   if (!d || d->max_nn < 4 || !d->nn || !d->nbr || seg_off.size() < 2) return false;
@@ -570,16 +582,13 @@ bool detect_sheets(const gpuqt_h_desc* d, const std::vector<int64_t>& seg_off, s
     if (Lx < 3 || n % Lx != 0) return false;
     const int64_t Ly = n / Lx;
     if (Ly < 3 || n > (int64_t(1) << 24)) return false;
-    for (int64_t i = 0; i < n; ++i) {
-      const int64_t x = i % Lx, y = i / Lx;
-      int64_t e[4] = {(x + 1) % Lx + Lx * y, (x + Lx - 1) % Lx + Lx * y, x + Lx * ((y + 1) % Ly),
-                      x + Lx * ((y + Ly - 1) % Ly)};
-      int64_t c[4];
-      for (int q = 0; q < 4; ++q) c[q] = (int64_t)d->nbr[(a + i) * k + q] - a;
-      std::sort(e, e + 4);
-      std::sort(c, c + 4);
-      for (int q = 0; q < 4; ++q)
-        if (c[q] != e[q]) return false;
+    for (int64_t y = 0, i = 0; y < Ly; ++y) {
+      const int64_t row = a + y * Lx, up = a + (y + 1 == Ly ? 0 : y + 1) * Lx, dn = a + (y == 0 ? Ly - 1 : y - 1) * Lx;
+      for (int64_t x = 0; x < Lx; ++x, ++i) {
+        const int32_t* c = d->nbr + (a + i) * k;
+        const int64_t e[4] = {row + (x + 1 == Lx ? 0 : x + 1), row + (x == 0 ? Lx - 1 : x - 1), up + x, dn + x};
+        if (!names_each<4>(c, e)) return false;
+      }
     }
     out[2 * sg] = (int32_t)Lx;
     out[2 * sg + 1] = (int32_t)Ly;
@@ -608,17 +617,17 @@ bool detect_box(const gpuqt_h_desc* d, int32_t box[3]) {
   // the box kernels address a plane of a block with 32-bit byte offsets: a plane of 16
   // vectors of 16-byte elements must span at most 4 GiB
   if (LxLy > (int64_t(1) << 24)) return false;
-  for (int64_t i = 0; i < n; ++i) {
-    const int64_t x = i % Lx, y = (i / Lx) % Ly, z = i / LxLy;
-    int64_t e[6] = {(x + 1) % Lx + Lx * (y + Ly * z),      (x + Lx - 1) % Lx + Lx * (y + Ly * z),
-                    x + Lx * ((y + 1) % Ly + Ly * z),      x + Lx * ((y + Ly - 1) % Ly + Ly * z),
-                    x + Lx * (y + Ly * ((z + 1) % Lz)),    x + Lx * (y + Ly * ((z + Lz - 1) % Lz))};
-    int64_t c[6];
-    for (int s = 0; s < 6; ++s) c[s] = d->nbr[i * k + s];
-    std::sort(e, e + 6);
-    std::sort(c, c + 6);
-    for (int s = 0; s < 6; ++s)
-      if (c[s] != e[s]) return false;
+  for (int64_t z = 0, i = 0; z < Lz; ++z) {
+    const int64_t zp = (z + 1 == Lz ? 0 : z + 1) * LxLy, zm = (z == 0 ? Lz - 1 : z - 1) * LxLy;
+    for (int64_t y = 0; y < Ly; ++y) {
+      const int64_t row = z * LxLy + y * Lx, in = y * Lx;
+      const int64_t yp = z * LxLy + (y + 1 == Ly ? 0 : y + 1) * Lx, ym = z * LxLy + (y == 0 ? Ly - 1 : y - 1) * Lx;
+      for (int64_t x = 0; x < Lx; ++x, ++i) {
+        const int64_t e[6] = {row + (x + 1 == Lx ? 0 : x + 1), row + (x == 0 ? Lx - 1 : x - 1), yp + x, ym + x,
+                              zp + in + x, zm + in + x};
+        if (!names_each<6>(d->nbr + i * k, e)) return false;
+      }
+    }
   }
   box[0] = (int32_t)Lx;
   box[1] = (int32_t)Ly;
