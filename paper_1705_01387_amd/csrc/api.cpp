@@ -13,7 +13,7 @@
 using namespace gpuqt;
 
 namespace gpuqt {
-// Reverse step of a Hermitian moment set (kernels_adjoint.hip): the two-chain
+// Reverse step of a Hermitian moment set (kernels_adjoint_sym.hip): the two-chain
 // step with both chains equal, one chain gathered; the b fields of io unused.
 hipError_t launch_adjoint_sym_step(const DevMat& A, int hop_mode, int B, int nc, const AdjPairIO& io,
                                    hipStream_t s);

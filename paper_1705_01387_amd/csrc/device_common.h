@@ -1,4 +1,4 @@
-// Device helpers shared by the sparse kernels (kernels.hip, kernels_adjoint.hip):
+// Device helpers shared by the sparse kernels (kernels.hip, kernels_adjoint*.hip):
 // complex FP64 arithmetic, the row product over the sliced-ELL layout, the
 // XCD-aware row schedule, the deterministic workgroup reduction and the
 // compile-time dispatch over (B, hopping mode, row width, load variant).

@@ -14,6 +14,7 @@
 #include <hip/hip_runtime.h>
 
 #include "device_common.h"
+#include "reverse_core.h"
 
 namespace gpuqt {
 
@@ -21,19 +22,6 @@ using namespace dev;
 
 namespace {
 
-// f(j) for the entries of a row: K of them unrolled, so that every index, table and gather load is in
-// flight at once instead of one entry's chain after another's, or w.
-template <int K, typename F>
-__device__ __forceinline__ void for_entries(int w, F&& f) {
-  if constexpr (K > 0) {
-#pragma unroll
-    for (int j = 0; j < K; ++j) f(j);
-  } else {
-    for (int j = 0; j < w; ++j) f(j);
-  }
-}
-
-//
 // Class gradients (TR, where every class's hoppings are Hermitian by themselves): <lam_{n+1}| H~_c v_n> =
 // conj(<v_n| H~_c lam_{n+1}>), and H~_c lam_{n+1} is part of the product that gives lam_n.  So step n adds
 // the terms of step n + 1 from the rows' own v_n, and only lam_{n+1} is gathered.  Bound by the gathers
@@ -69,8 +57,9 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_step(DevMat A, AdjIO io) {
     double2 hv[NC > 0 ? NC : 1];
 #pragma unroll
     for (int c = 0; c < (NC > 0 ? NC : 1); ++c) hv[c] = make_double2(0.0, 0.0);
+    constexpr bool AHEAD = TR || NC == 0;   // gU read ahead of the products
     double gu0 = 0.0;
-    if (v && b == 0) gu0 = io.gU[r];
+    if (AHEAD && v && b == 0) gu0 = io.gU[r];
     // per-entry gradients: the neighbours' v ahead of lam_n
     constexpr bool ENT = NC == 0 && K > 0;
     double2 vn[ENT ? K : 1];
@@ -89,14 +78,28 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_step(DevMat A, AdjIO io) {
     };
     auto add_class = [&](int64_t e, bool ok, double2 y) {
       const double2 t = mul(hop0_entry<HOP>(A, e, ok, P.seg), y);
-      const int cls = (NC > 1) ? io.cls[HOP == HOP_DICT ? (int64_t)A.hidx[e] : e] : 0;   // (padding adds zero)
+      const int cls = NC > 1 && (TR || ok) ? io.cls[HOP == HOP_DICT ? (int64_t)A.hidx[e] : e] : 0;   // (padding adds zero)
 #pragma unroll
       for (int q = 0; q < (NC > 0 ? NC : 1); ++q) {
-        hv[q].x += q == cls ? t.x : 0.0;
-        hv[q].y += q == cls ? t.y : 0.0;
+        if constexpr (TR) {
+          hv[q].x += q == cls ? t.x : 0.0;
+          hv[q].y += q == cls ? t.y : 0.0;
+        } else if (q == cls) {
+          hv[q] = cadd(hv[q], t);
+        }
       }
     };
-    if (x) {
+    if constexpr (NC > 0 && !TR) {   // x and v with one reading of the keys
+      if (x) h = cscale(A.diag[r], x[idx]);
+      for (int j = 0; j < w; ++j) {
+        const int64_t e = e0 + (int64_t)j * S;
+        int64_t cc;
+        const bool ok = col_entry<HOP>(A, r, e, &cc);
+        const double2 he = hop_entry<HOP>(A, e, ok, hu);
+        if (x) h = cadd(h, mul(he, x[cc * B + b]));
+        if (v) add_class(e, ok, v[cc * B + b]);
+      }
+    } else if (x) {   // (one block, so that the row's own loads are in flight with the gathers)
       h = cscale(A.diag[r], x[idx]);
       for_entries<K>(w, [&](int j) {
         const int64_t e = e0 + (int64_t)j * S;
@@ -104,17 +107,8 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_step(DevMat A, AdjIO io) {
         const bool ok = col_entry<HOP>(A, r, e, &cc);
         const double2 xv = x[cc * B + b];
         h = cadd(h, mul(hop_entry<HOP>(A, e, ok, hu), xv));
-        if constexpr (NC > 0 && TR) add_class(e, ok, xv);
+        if constexpr (NC > 0) add_class(e, ok, xv);
       });
-    }
-    if constexpr (NC > 0 && !TR) {
-      if (v)
-        for_entries<K>(w, [&](int j) {
-          const int64_t e = e0 + (int64_t)j * S;
-          int64_t cc;
-          const bool ok = col_entry<HOP>(A, r, e, &cc);
-          add_class(e, ok, v[cc * B + b]);
-        });
     }
     double2 lam = cmul(wn, io.phiL[idx]);
     lam = make_double2(fma(io.f_rec, h.x, lam.x), fma(io.f_rec, h.y, lam.y));
@@ -129,7 +123,7 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_step(DevMat A, AdjIO io) {
       double gu = io.f * (lg.x * vr.x + lg.y * vr.y);     // f Re(conj(lam) v)
 #pragma unroll
       for (int off = 1; off < B; off <<= 1) gu += __shfl_xor(gu, off);
-      if (b == 0) io.gU[r] = gu0 + gu * inv_dE;
+      if (b == 0) io.gU[r] = (AHEAD ? gu0 : io.gU[r]) + gu * inv_dE;
 #pragma unroll
       for (int q = 0; q < (NC > 0 ? NC : 1); ++q)
         if (NC > 0) {
@@ -160,240 +154,6 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_step(DevMat A, AdjIO io) {
   });
   if (NC == 0 || !v) return;
   // class partials: workgroup sum in a fixed order, accumulated per workgroup
-  __shared__ double sh[kBlock / 64][NC > 0 ? NC : 1];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int q = 0; q < (NC > 0 ? NC : 1); ++q) {
-    double s = gc[q];
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off);
-    if (lane == 0) sh[wave][q] = s;
-  }
-  __syncthreads();
-  if (threadIdx.x < (NC > 0 ? NC : 1)) {
-    double s = 0.0;
-#pragma unroll
-    for (int wv = 0; wv < kBlock / 64; ++wv) s += sh[wv][threadIdx.x];
-    io.gcp[(int64_t)lb * NC + threadIdx.x] += s;
-  }
-}
-
-// Reverse step of the two-chain form (both adjoint chains in one launch, the
-// matrix read once; abar_{k+1}, bbar_{k+1} and, for class gradients, a_{k-1},
-// b_{k-1} gathered with the same indices).  Parameter terms, as for the
-// single chain: dL/dp = Re sum_k f_k (<abar_k| dH~/dp a_{k-1}> + <bbar_k| dH~/dp b_{k-1}>).
-template <int B, int HOP, int K, int NC, bool TR>
-__global__ __launch_bounds__(kBlock) void k_adjoint_pair_step(DevMat A, AdjPairIO io) {
-  const int lb = logical_block(A.G);
-  const BlkPlan P = A.plan[lb];
-  const double hu = (HOP == HOP_UNIFORM) ? A.seg_hop[P.seg] : 0.0;
-  const double inv_dE = 1.0 / A.seg_dE[P.seg];
-  const int b = threadIdx.x & (B - 1);
-  const double* om = io.om + ((int64_t)P.seg * B + b) * io.R;
-  const int k2 = 2 * io.k;
-  const double w0 = om[k2];
-  const double wm = io.k >= 1 ? om[k2 - 1] : 0.0;
-  const double wp = (io.a_p1 && k2 + 1 < io.R) ? om[k2 + 1] : 0.0;
-  const bool grad = io.gU != nullptr && (TR ? io.xa != nullptr : io.k >= 1);
-  const int S = 1 << A.S_log2;
-  double gc[NC > 0 ? NC : 1];
-#pragma unroll
-  for (int c = 0; c < (NC > 0 ? NC : 1); ++c) gc[c] = 0.0;
-  for_rows<B>(A, P, [&](int64_t r) {
-    const int64_t idx = r * B + b;
-    const int64_t sl = r >> A.S_log2;
-    const int64_t p0 = A.slice_ptr[sl];
-    const int64_t e0 = p0 + (r & (S - 1));
-    const int w = K > 0 ? K : (int)((A.slice_ptr[sl + 1] - p0) >> A.S_log2);
-    double2 ha = make_double2(0.0, 0.0), hb = make_double2(0.0, 0.0);
-    double2 hva[NC > 0 ? NC : 1], hvb[NC > 0 ? NC : 1];
-#pragma unroll
-    for (int c = 0; c < (NC > 0 ? NC : 1); ++c) {
-      hva[c] = make_double2(0.0, 0.0);
-      hvb[c] = make_double2(0.0, 0.0);
-    }
-    double gu0 = 0.0;
-    if (grad && b == 0) gu0 = io.gU[r];
-    auto mul = [](double2 he, double2 y) {
-      return (HOP == HOP_COMPLEX || HOP == HOP_DICT) ? cmul(he, y) : cscale(he.x, y);
-    };
-    auto add_class = [&](int64_t e, bool ok, double2 ya, double2 yb) {
-      const double2 he0 = hop0_entry<HOP>(A, e, ok, P.seg);
-      const double2 ta = mul(he0, ya), tb = mul(he0, yb);
-      const int cls = (NC > 1) ? io.cls[HOP == HOP_DICT ? (int64_t)A.hidx[e] : e] : 0;   // (padding adds zero)
-#pragma unroll
-      for (int q = 0; q < (NC > 0 ? NC : 1); ++q) {
-        hva[q].x += q == cls ? ta.x : 0.0;
-        hva[q].y += q == cls ? ta.y : 0.0;
-        hvb[q].x += q == cls ? tb.x : 0.0;
-        hvb[q].y += q == cls ? tb.y : 0.0;
-      }
-    };
-    if (io.xa) {
-      const double d = A.diag[r];
-      ha = cscale(d, io.xa[idx]);
-      hb = cscale(d, io.xb[idx]);
-      for_entries<K>(w, [&](int j) {
-        const int64_t e = e0 + (int64_t)j * S;
-        int64_t cc;
-        const bool ok = col_entry<HOP>(A, r, e, &cc);
-        const double2 he = hop_entry<HOP>(A, e, ok, hu);
-        const double2 xa = io.xa[cc * B + b], xb = io.xb[cc * B + b];
-        ha = cadd(ha, mul(he, xa));
-        hb = cadd(hb, mul(he, xb));
-        if constexpr (NC > 0 && TR) add_class(e, ok, xa, xb);
-      });
-    }
-    if constexpr (NC > 0 && !TR) {
-      if (grad)
-        for_entries<K>(w, [&](int j) {
-          const int64_t e = e0 + (int64_t)j * S;
-          int64_t cc;
-          const bool ok = col_entry<HOP>(A, r, e, &cc);
-          add_class(e, ok, io.a_m1[cc * B + b], io.b_m1[cc * B + b]);
-        });
-    }
-    // direct sensitivities of the raw dots
-    double2 ga = cscale(w0, io.b_k[idx]);
-    if (io.k >= 1) ga = cadd(ga, cscale(wm, io.b_m1[idx]));
-    double2 gb = cscale(w0, io.a_k[idx]);
-    if (io.a_p1) gb = cadd(gb, cscale(wp, io.a_p1[idx]));
-    double2 la = make_double2(fma(io.f_rec, ha.x, ga.x), fma(io.f_rec, ha.y, ga.y));
-    double2 lbv = make_double2(fma(io.f_rec, hb.x, gb.x), fma(io.f_rec, hb.y, gb.y));
-    if (io.wa) {
-      const double2 u = io.wa[idx], v = io.wb[idx];
-      la = make_double2(la.x - u.x, la.y - u.y);
-      lbv = make_double2(lbv.x - v.x, lbv.y - v.y);
-    }
-    io.oa[idx] = io.acc_a ? cadd(io.oa[idx], la) : la;
-    io.ob[idx] = io.acc_b ? cadd(io.ob[idx], lbv) : lbv;
-    if (grad) {
-      const double2 va = TR ? io.a_k[idx] : io.a_m1[idx], vb = TR ? io.b_k[idx] : io.b_m1[idx];
-      const double2 pa = TR ? io.xa[idx] : la, pb = TR ? io.xb[idx] : lbv;
-      double gu = io.f * (pa.x * va.x + pa.y * va.y + pb.x * vb.x + pb.y * vb.y);
-      const double2 qa = TR ? va : la, qb = TR ? vb : lbv;
-#pragma unroll
-      for (int off = 1; off < B; off <<= 1) gu += __shfl_xor(gu, off);
-      if (b == 0) io.gU[r] = gu0 + gu * inv_dE;
-#pragma unroll
-      for (int q = 0; q < (NC > 0 ? NC : 1); ++q)
-        if (NC > 0)
-          gc[q] += io.f * (qa.x * hva[q].x + qa.y * hva[q].y + qb.x * hvb[q].x + qb.y * hvb[q].y);
-    }
-  });
-  if (NC == 0 || !grad) return;
-  __shared__ double sh[kBlock / 64][NC > 0 ? NC : 1];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int q = 0; q < (NC > 0 ? NC : 1); ++q) {
-    double s = gc[q];
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off);
-    if (lane == 0) sh[wave][q] = s;
-  }
-  __syncthreads();
-  if (threadIdx.x < (NC > 0 ? NC : 1)) {
-    double s = 0.0;
-#pragma unroll
-    for (int wv = 0; wv < kBlock / 64; ++wv) s += sh[wv][threadIdx.x];
-    io.gcp[(int64_t)lb * NC + threadIdx.x] += s;
-  }
-}
-
-// Reverse step of the Hermitian form (phiL = phiR, one chain a_k = T_k phi):
-// with both chains equal the two adjoints only enter through their sum
-// cbar_k = abar_k + bbar_k,
-//   cbar_k = 2 om_2k a_k + om_2k-1 a_{k-1} + om_2k+1 a_{k+1} + f_rec H~ cbar_{k+1} - cbar_{k+2},
-// and the parameter terms are Re sum_k f_k <cbar_k| dH~/dp a_{k-1}>: one chain
-// gathered instead of two.  At k = 0 the output is cbar_0 / 2 = sum_n w_n T_n phi
-// (abar_0 = bbar_0).  Fields of io: xa, wa, oa, acc_a, a_m1, a_k, a_p1 and the
-// weights; the b fields are unused.
-template <int B, int HOP, int K, int NC, bool TR>
-__global__ __launch_bounds__(kBlock) void k_adjoint_sym_step(DevMat A, AdjPairIO io) {
-  const int lb = logical_block(A.G);
-  const BlkPlan P = A.plan[lb];
-  const double hu = (HOP == HOP_UNIFORM) ? A.seg_hop[P.seg] : 0.0;
-  const double inv_dE = 1.0 / A.seg_dE[P.seg];
-  const int b = threadIdx.x & (B - 1);
-  const double* om = io.om + ((int64_t)P.seg * B + b) * io.R;
-  const int k2 = 2 * io.k;
-  const double w0 = 2.0 * om[k2];
-  const double wm = io.k >= 1 ? om[k2 - 1] : 0.0;
-  const double wp = (io.a_p1 && k2 + 1 < io.R) ? om[k2 + 1] : 0.0;
-  const double out_scale = io.k == 0 ? 0.5 : 1.0;
-  const bool grad = io.gU != nullptr && (TR ? io.xa != nullptr : io.k >= 1);
-  const int S = 1 << A.S_log2;
-  double gc[NC > 0 ? NC : 1];
-#pragma unroll
-  for (int c = 0; c < (NC > 0 ? NC : 1); ++c) gc[c] = 0.0;
-  for_rows<B>(A, P, [&](int64_t r) {
-    const int64_t idx = r * B + b;
-    const int64_t sl = r >> A.S_log2;
-    const int64_t p0 = A.slice_ptr[sl];
-    const int64_t e0 = p0 + (r & (S - 1));
-    const int w = K > 0 ? K : (int)((A.slice_ptr[sl + 1] - p0) >> A.S_log2);
-    double2 h = make_double2(0.0, 0.0);
-    double2 hv[NC > 0 ? NC : 1];
-#pragma unroll
-    for (int c = 0; c < (NC > 0 ? NC : 1); ++c) hv[c] = make_double2(0.0, 0.0);
-    double gu0 = 0.0;
-    if (grad && b == 0) gu0 = io.gU[r];
-    auto mul = [](double2 he, double2 y) {
-      return (HOP == HOP_COMPLEX || HOP == HOP_DICT) ? cmul(he, y) : cscale(he.x, y);
-    };
-    auto add_class = [&](int64_t e, bool ok, double2 y) {
-      const double2 t = mul(hop0_entry<HOP>(A, e, ok, P.seg), y);
-      const int cls = (NC > 1) ? io.cls[HOP == HOP_DICT ? (int64_t)A.hidx[e] : e] : 0;   // (padding adds zero)
-#pragma unroll
-      for (int q = 0; q < (NC > 0 ? NC : 1); ++q) {
-        hv[q].x += q == cls ? t.x : 0.0;
-        hv[q].y += q == cls ? t.y : 0.0;
-      }
-    };
-    if (io.xa) {
-      h = cscale(A.diag[r], io.xa[idx]);
-      for_entries<K>(w, [&](int j) {
-        const int64_t e = e0 + (int64_t)j * S;
-        int64_t cc;
-        const bool ok = col_entry<HOP>(A, r, e, &cc);
-        const double2 x = io.xa[cc * B + b];
-        h = cadd(h, mul(hop_entry<HOP>(A, e, ok, hu), x));
-        if constexpr (NC > 0 && TR) add_class(e, ok, x);
-      });
-    }
-    if constexpr (NC > 0 && !TR) {
-      if (grad)
-        for_entries<K>(w, [&](int j) {
-          const int64_t e = e0 + (int64_t)j * S;
-          int64_t cc;
-          const bool ok = col_entry<HOP>(A, r, e, &cc);
-          add_class(e, ok, io.a_m1[cc * B + b]);
-        });
-    }
-    // direct sensitivities of the raw dots
-    double2 g = cscale(w0, io.a_k[idx]);
-    if (io.k >= 1) g = cadd(g, cscale(wm, io.a_m1[idx]));
-    if (io.a_p1) g = cadd(g, cscale(wp, io.a_p1[idx]));
-    double2 c = make_double2(fma(io.f_rec, h.x, g.x), fma(io.f_rec, h.y, g.y));
-    if (io.wa) {
-      const double2 u = io.wa[idx];
-      c = make_double2(c.x - u.x, c.y - u.y);
-    }
-    const double2 o = cscale(out_scale, c);
-    io.oa[idx] = io.acc_a ? cadd(io.oa[idx], o) : o;
-    if (grad) {
-      const double2 v = TR ? io.a_k[idx] : io.a_m1[idx];
-      const double2 p = TR ? io.xa[idx] : c, l = TR ? v : c;
-      double gu = io.f * (p.x * v.x + p.y * v.y);
-#pragma unroll
-      for (int off = 1; off < B; off <<= 1) gu += __shfl_xor(gu, off);
-      if (b == 0) io.gU[r] = gu0 + gu * inv_dE;
-#pragma unroll
-      for (int q = 0; q < (NC > 0 ? NC : 1); ++q)
-        if (NC > 0) gc[q] += io.f * (l.x * hv[q].x + l.y * hv[q].y);
-    }
-  });
-  if (NC == 0 || !grad) return;
   __shared__ double sh[kBlock / 64][NC > 0 ? NC : 1];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
@@ -682,99 +442,10 @@ __global__ __launch_bounds__(64) void k_reduce_classes(const double* __restrict_
 
 }  // namespace
 
-hipError_t launch_adjoint_step(const DevMat& A, int hop_mode, int B, int nc, const AdjIO& io,
-                               hipStream_t s) {
-  return dispatch_bh(B, hop_mode, [&](auto Bc, auto Hc) {
-    constexpr int Bv = decltype(Bc)::value, Hv = decltype(Hc)::value;
-    auto go = [&](auto Kc) {
-      constexpr int Kv = decltype(Kc)::value;
-      switch (nc) {
-        case 0: k_adjoint_step<Bv, Hv, Kv, 0, false><<<dim3(A.G), kBlock, 0, s>>>(A, io); break;
-        case 1:
-          if (io.tr) k_adjoint_step<Bv, Hv, Kv, 1, true><<<dim3(A.G), kBlock, 0, s>>>(A, io);
-          else k_adjoint_step<Bv, Hv, 0, 1, false><<<dim3(A.G), kBlock, 0, s>>>(A, io);
-          break;
-        case 2:
-          if (io.tr) k_adjoint_step<Bv, Hv, Kv, 2, true><<<dim3(A.G), kBlock, 0, s>>>(A, io);
-          else k_adjoint_step<Bv, Hv, 0, 2, false><<<dim3(A.G), kBlock, 0, s>>>(A, io);
-          break;
-        default:
-          if (io.tr) k_adjoint_step<Bv, Hv, Kv, 4, true><<<dim3(A.G), kBlock, 0, s>>>(A, io);
-          else k_adjoint_step<Bv, Hv, 0, 4, false><<<dim3(A.G), kBlock, 0, s>>>(A, io);
-          break;
-      }
-    };
-    switch (A.K) {
-      case 3: go(IC<3>{}); break;
-      case 4: go(IC<4>{}); break;
-      case 6: go(IC<6>{}); break;
-      case 8: go(IC<8>{}); break;
-      default: go(IC<0>{}); break;
-    }
-  });
-}
-
-hipError_t launch_adjoint_pair_step(const DevMat& A, int hop_mode, int B, int nc, const AdjPairIO& io,
-                                    hipStream_t s) {
-  return dispatch_bh(B, hop_mode, [&](auto Bc, auto Hc) {
-    constexpr int Bv = decltype(Bc)::value, Hv = decltype(Hc)::value;
-    auto go = [&](auto Kc) {
-      constexpr int Kv = decltype(Kc)::value;
-      switch (nc) {
-        case 0: k_adjoint_pair_step<Bv, Hv, Kv, 0, false><<<dim3(A.G), kBlock, 0, s>>>(A, io); break;
-        case 1:
-          if (io.tr) k_adjoint_pair_step<Bv, Hv, Kv, 1, true><<<dim3(A.G), kBlock, 0, s>>>(A, io);
-          else k_adjoint_pair_step<Bv, Hv, 0, 1, false><<<dim3(A.G), kBlock, 0, s>>>(A, io);
-          break;
-        case 2:
-          if (io.tr) k_adjoint_pair_step<Bv, Hv, Kv, 2, true><<<dim3(A.G), kBlock, 0, s>>>(A, io);
-          else k_adjoint_pair_step<Bv, Hv, 0, 2, false><<<dim3(A.G), kBlock, 0, s>>>(A, io);
-          break;
-        default:
-          if (io.tr) k_adjoint_pair_step<Bv, Hv, Kv, 4, true><<<dim3(A.G), kBlock, 0, s>>>(A, io);
-          else k_adjoint_pair_step<Bv, Hv, 0, 4, false><<<dim3(A.G), kBlock, 0, s>>>(A, io);
-          break;
-      }
-    };
-    switch (A.K) {
-      case 3: go(IC<3>{}); break;
-      case 4: go(IC<4>{}); break;
-      case 6: go(IC<6>{}); break;
-      case 8: go(IC<8>{}); break;
-      default: go(IC<0>{}); break;
-    }
-  });
-}
-
-hipError_t launch_adjoint_sym_step(const DevMat& A, int hop_mode, int B, int nc, const AdjPairIO& io,
-                                   hipStream_t s) {
-  return dispatch_bh(B, hop_mode, [&](auto Bc, auto Hc) {
-    constexpr int Bv = decltype(Bc)::value, Hv = decltype(Hc)::value;
-    auto go = [&](auto Kc) {
-      constexpr int Kv = decltype(Kc)::value;
-      switch (nc) {
-        case 0: k_adjoint_sym_step<Bv, Hv, Kv, 0, false><<<dim3(A.G), kBlock, 0, s>>>(A, io); break;
-        case 1:
-          if (io.tr) k_adjoint_sym_step<Bv, Hv, Kv, 1, true><<<dim3(A.G), kBlock, 0, s>>>(A, io);
-          else k_adjoint_sym_step<Bv, Hv, 0, 1, false><<<dim3(A.G), kBlock, 0, s>>>(A, io);
-          break;
-        case 2:
-          if (io.tr) k_adjoint_sym_step<Bv, Hv, Kv, 2, true><<<dim3(A.G), kBlock, 0, s>>>(A, io);
-          else k_adjoint_sym_step<Bv, Hv, 0, 2, false><<<dim3(A.G), kBlock, 0, s>>>(A, io);
-          break;
-        default:
-          if (io.tr) k_adjoint_sym_step<Bv, Hv, Kv, 4, true><<<dim3(A.G), kBlock, 0, s>>>(A, io);
-          else k_adjoint_sym_step<Bv, Hv, 0, 4, false><<<dim3(A.G), kBlock, 0, s>>>(A, io);
-          break;
-      }
-    };
-    switch (A.K) {
-      case 3: go(IC<3>{}); break;
-      case 4: go(IC<4>{}); break;
-      case 6: go(IC<6>{}); break;
-      case 8: go(IC<8>{}); break;
-      default: go(IC<0>{}); break;
-    }
+hipError_t launch_adjoint_step(const DevMat& A, int hop_mode, int B, int nc, const AdjIO& io, hipStream_t s) {
+  return dispatch_reverse(A, hop_mode, B, nc, io.tr, [&](auto Bc, auto Hc, auto Kc, auto Nc, auto Tc) {
+    k_adjoint_step<decltype(Bc)::value, decltype(Hc)::value, decltype(Kc)::value, decltype(Nc)::value, decltype(Tc)::value == 1>
+        <<<dim3(A.G), kBlock, 0, s>>>(A, io);
   });
 }
 
