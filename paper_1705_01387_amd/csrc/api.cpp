@@ -968,7 +968,7 @@ gpuqt_status gpuqt_build_h(const gpuqt_h_desc* desc, void* stream, gpuqt_h* out)
           md.items = mp.items;
           md.patch = mp.patch;
           md.launch_us = plan_launch_us(h->lat, h->hop_mode, f, 1 << lb, cus, mp);
-          md.step_us = general_step_us(f, h->hop_mode, h->n, h->nnz, 1 << lb);
+          for (int t = 0; t < 2; ++t) md.step_us[t] = general_step_us(f, h->hop_mode, h->n, h->nnz, 1 << lb, t == 1);
           auto put = [&](const void* src, size_t bytes) {
             const size_t off = round_up(march_host.size(), 16);
             march_host.resize(off + bytes);
@@ -2117,9 +2117,7 @@ gpuqt_status gpuqt_autotune(gpuqt_h hh, int32_t B, void* ws, size_t ws_bytes, vo
     }
   }
   const int march_sym = h->use_box;
-  h->use_box_msd = h->lat.dx_ok;
-  const bool msd_marches = h->march_pays(MF_MSD, B, kTuneSteps, 0);   // no cap of the general term to look for
-  h->use_box = h->use_box_msd = 0;   // the general kernels' caps below
+  h->use_box = 0;   // the general kernels' caps below
   // with room for their vectors, each of the two-chain moment, two-vector
   // evolution and MSD families also gets its own cap at this load variant
   if (!st && ws_bytes >= WF.total) {
@@ -2157,6 +2155,11 @@ gpuqt_status gpuqt_autotune(gpuqt_h hh, int32_t B, void* ws, size_t ws_bytes, vo
     };
     float t_pair = 0.0f;
     st = tune_family(FAM_PAIR, &t_pair);
+    // no cap of the general MSD term to look for where it runs as a march (the handle is a tuned one by now)
+    h->use_box = march_sym;
+    h->use_box_msd = h->lat.dx_ok;
+    const bool msd_marches = h->march_pays(MF_MSD, B, kTuneSteps, 0);
+    h->use_box = h->use_box_msd = 0;
     // the series families (two-vector evolution and MSD terms) with the handle's
     // load variant and with the other one; the pair of caps of the faster total stays
     float tot[2] = {0.0f, 0.0f};

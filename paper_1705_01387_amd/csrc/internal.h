@@ -171,7 +171,7 @@ struct Handle {
     const MarchSeg* segs = nullptr;
     const int32_t* item0 = nullptr;
     int32_t T = 0, lanes = 0, items = 0, patch = 0;
-    double launch_us = 0.0, step_us = 0.0;   // estimated: a launch of T steps, a step of the general kernels
+    double launch_us = 0.0, step_us[2] = {0.0, 0.0};   // estimated: a launch of T steps, a step of the general kernels (tuned())
   };
   MarchDev march[kMarchFamilies][kNumB];
   char* d_march = nullptr;
@@ -182,6 +182,8 @@ struct Handle {
     return lat.pattern != MARCH_NONE && use_box && march[fam][log2B(B)].T > 0 &&
            (fam != MF_MSD || (use_box_msd && lat.dx_ok));
   }
+  // whether the general kernels run with a row order or caps that were chosen for this handle
+  int tuned() const { return banded || per_cu_cap || family_caps_code(); }
   // Estimated time of K steps by the family's march (march_on) less that by the general kernels: a march
   // takes whole launches, a patch the steps that are left, rounded up to kPatchUnroll.
   double march_loss_us(int fam, int B, int K) const {
@@ -189,11 +191,11 @@ struct Handle {
     const int left = K % m.T, steps = (left + kPatchUnroll - 1) / kPatchUnroll * kPatchUnroll;
     double t = K / m.T * m.launch_us;
     if (left) t += m.patch ? kPatchFixedUs + (m.launch_us - kPatchFixedUs) * steps / m.T : m.launch_us;
-    return t - 1.05 * K * m.step_us;
+    return t - 1.05 * K * m.step_us[tuned()];
   }
   // Whether K steps go to the march: it exists, is on, and takes no longer with `layouts` changes of a
-  // block's layout.  (Few steps do not fill a launch: 2000 x 2000, one vector, 55 us against 41 for a single Hermitian
-  // step and against 94 for two.)
+  // block's layout.  (Few steps do not fill a launch: 700 x 700 open in x, two vectors, a call of one Hermitian
+  // step 49 us against 25, of three 49 against 63.)
   bool march_pays(int fam, int B, int K, int layouts) const {
     return march_on(fam, B) && march_loss_us(fam, B, K) + layouts * planar_us(n, B) <= 0.0;
   }

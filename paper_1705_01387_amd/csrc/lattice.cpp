@@ -431,48 +431,71 @@ bool plan_patch(const MarchLattice& M, const std::vector<int64_t>& seg_off, int 
   return true;
 }
 
-// Estimates from per-step times (events around 64 steps) of every family by marches or patches and by the general
-// kernels: 901 pairs of lattice and block width on one MI355X, boxes of 125 to 2 M sites, squares, open squares and brick
-// lattices of 256 to 1.6 M sites and any shape down to strips of four columns, with one hopping and one an
-// entry, B = 1, 2, 4, 16.  A launch costs a constant and a time per iteration of a round of workgroups.  Where
-// the two times were within a factor of 2.5, the choice by these estimates missed the faster one by 5 % or more
-// in 40 of 900 places, by at most 1.6 (strips); marches everywhere were slower in 500, up to 20 times: small
+// Estimates, from per-step times (events around 64 steps) of every family by marches or patches and by the general
+// kernels: 901 pairs of lattice and block width on one MI355X (boxes of 125 to 4 M sites; squares, open squares,
+// brick lattices and squares with next-nearest neighbours of 64 to 1.6 M sites, any shape down to strips of four columns;
+// rings; one hopping and one an entry; B = 1, 2, 4, 16), 378 of them on tuned handles too.  A launch costs a constant and a
+// time per iteration of a round of workgroups, less where few of a tile's lanes have work of their own, and its
+// traffic.  Boxes come out within 9 %, r.m.s., the others within 7 to 17 %.
+//
+// Marches are slower by 5 % or more in 601 of 4,505 places (454 of 1,890 against tuned kernels), up to 19 times: small
 // boxes, whose launch takes 14 us or more for three steps of 3.5 us (20^3, one vector: Hermitian step 4.65 us
 // against 3.56 general, MSD term 10.8 against 3.6, two chains 15.3 against 3.8; 60^3: 5.6 / 6.1, 13.3 / 10.9 and
 // 17.9 / 7.2), and strips, whose tiles own few of their cells (5 x 5 x 20,000, four vectors: 93 against
-// 25; squares of 4 x 200,000, four vectors: 42 against 33).
+// 25; squares of 4 x 200,000, four vectors: 42 against 33).  By these estimates the slower one is taken in 101 (61) places,
+// by 20 % or more in 48 (18).
 double plan_launch_us(const MarchLattice& M, int hop_mode, int family, int B, int cus, const MarchPlan& p) {
   auto ceil_div = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
   const bool one = family == MF_SYM || family == MF_EVO, entry = hop_mode != HOP_UNIFORM;
-  int zc = 0;
-  for (const MarchSeg& q : p.segs) zc = std::max(zc, (int)q.zc);
   const int64_t per_cu = ceil_div((int64_t)p.items * B, cus);
+  int zc = 0;
+  double rows = 0.0, fill = 0.0;   // elements; the tiles' share of a workgroup's lanes
+  for (const MarchSeg& q : p.segs) {
+    zc = std::max(zc, (int)q.zc);
+    const double r = (double)q.Lx * q.Ly * q.Lm * B;
+    fill += r * (M.pattern == MARCH_BOX ? q.tx * q.ty : q.ux) / p.lanes;
+    rows += r;
+  }
+  fill /= rows;
   if (p.patch) {
     if (M.pattern == MARCH_CHAIN) return 8.7 + (entry ? 9.0 : 7.0) * zc * per_cu;
     const double full = (one ? 4.5 : 6.6) * (entry ? 1.15 : 1.0) * (M.pattern == MARCH_NNN ? 1.5 : 1.0);
     return kPatchFixedUs + full * (p.T == 8 && p.lanes == 1024 ? 1.5 : 1.0) * zc * per_cu;
   }
-  const int64_t iters = ceil_div(zc + 2 * p.T, 3) * 3;
-  // fixed time of a launch, time of an iteration: SYM, PAIR, EVO, EVO2, MSD
-  static const double box[5][2] = {{3.0, 1.25}, {3.0, 5.8}, {3.0, 1.5}, {2.0, 3.5}, {2.0, 3.9}};
-  static const double flat[5][2] = {{14.0, 0.30}, {10.0, 0.80}, {8.0, 0.35}, {12.0, 0.70}, {12.0, 0.72}};
-  static const double bonds[5][2] = {{11.0, 0.42}, {9.0, 0.82}, {8.0, 0.48}, {10.0, 0.80}, {10.0, 0.85}};
-  if (M.pattern == MARCH_BOX) return box[family][0] + box[family][1] * iters * per_cu;
-  const double(&c)[2] = entry ? bonds[family] : flat[family];
-  const double waves = 0.5 * (per_cu + (double)p.items * B / cus) * p.lanes / 256.0;   // as in plan_march
-  const double rounds = (double)ceil_div(per_cu, 512 / p.lanes);
-  return c[0] + c[1] * iters * (std::max(waves, 0.75) + (p.T >= 8 ? 0.7 : 0.1) * rounds) * (p.lanes > 64 ? 1.05 : 1.0);
+  // constant; time of an iteration; bytes per us; share of the iteration that does not shrink with the fill
+  struct Cost { double fixed, iter, rate, base; };
+  static const Cost cost[3][kMarchFamilies] = {   // SYM, PAIR, EVO, EVO2, MSD
+      {{5.9, 1.05, 7.1e6, 0.80}, {14.9, 3.39, 4.3e6, 0.66}, {5.3, 1.22, 6.3e6, 0.78}, {5.8, 2.70, 5.8e6, 0.80}, {4.6, 3.52, 5.1e6, 0.74}},   // box
+      {{13.6, 0.34, 9.1e6, 0.89}, {6.4, 0.96, 8.1e6, 0.82}, {7.2, 0.28, 6.7e6, 1.0}, {9.3, 0.48, 6.2e6, 1.0}, {10.2, 0.51, 6.1e6, 1.0}},    // one hopping
+      {{7.4, 0.63, 12.0e6, 0.68}, {3.7, 1.13, 9.7e6, 0.64}, {6.4, 0.49, 7.5e6, 0.80}, {3.9, 1.15, 7.9e6, 0.50}, {4.4, 1.19, 8.0e6, 0.53}},  // one an entry
+  };
+  const Cost& c = cost[M.pattern == MARCH_BOX ? 0 : entry ? 2 : 1][family];
+  double w = (double)ceil_div(zc + 2 * p.T, 3) * 3;
+  double bytes = 16.0 * rows * (one ? 1 : 2) * (family == MF_SYM || family == MF_PAIR ? 4 : 6);   // two elements in and out a chain, and sums
+  if (M.pattern == MARCH_BOX) {
+    w *= per_cu;
+    bytes *= 1.24;   // (margins)
+  } else {
+    const double waves = 0.5 * (per_cu + (double)p.items * B / cus) * p.lanes / 256.0;   // as in plan_march
+    const double rounds = (double)ceil_div(per_cu, 512 / p.lanes);
+    w *= (std::max(waves, 0.75) + (p.T >= 8 ? 0.7 : 0.1) * rounds) * (p.lanes > 64 ? 1.05 : 1.0);
+    const double hop[4] = {0, 8, 16, 2};
+    bytes = 1.15 * bytes + hop[hop_mode] * rows * (M.pattern == MARCH_BRICK ? 3 : 4);
+  }
+  return std::hypot(c.fixed + c.iter * w * (c.base + (1.0 - c.base) * fill), bytes / c.rate);
 }
 
-// A step is a launch, at least, and 0.75 of that and its bytes at 5.2 TB/s (the measured steps lie within 15 %,
-// r.m.s.); the gathers of eight neighbours take longer than the bytes.
-double general_step_us(int family, int hop_mode, int64_t n, int64_t nnz, int B) {
-  static const double floor_us[5] = {3.7, 3.7, 2.9, 3.1, 3.3}, vec[5] = {48, 96, 80, 160, 160};
+// A step is a launch, at least, and 0.75 of that and its bytes at 5.2 TB/s (the measured steps lie within 15 %, r.m.s.);
+// with the row order and caps that the autotuner chooses 6.7, while the step's bytes fit the last-level cache; the
+// gathers of eight neighbours take longer than the bytes.
+double general_step_us(int family, int hop_mode, int64_t n, int64_t nnz, int B, bool tuned) {
+  static const double floor_us[kMarchFamilies] = {3.7, 3.7, 2.9, 3.1, 3.3}, vec[kMarchFamilies] = {48, 96, 80, 160, 160};
   const double key[4] = {4, 12, 20, 2};   // bytes of an entry: column and hopping, or a table index
   const double entry = key[hop_mode] + (family == MF_MSD && hop_mode != HOP_DICT ? 8.0 : 0.0);
   const double bytes = (double)n * (vec[family] * B + 8.0) + entry * (double)nnz;
   const double gather = nnz < 8 * n ? 1.0 : family == MF_SYM || family == MF_PAIR ? 1.4 : 1.25;
-  return gather * std::max(floor_us[family] + 0.2 * (B - 1), 0.75 * floor_us[family] + bytes / 5.2e6);
+  return gather * std::max(floor_us[family] + 0.2 * (B - 1),
+                           0.75 * floor_us[family] + bytes / (tuned && bytes < 380e6 ? 6.7e6 : 5.2e6));
 }
 
 double planar_us(int64_t n, int B) { return B == 1 ? 0.0 : 2.2 + 32.0 * (double)n * B / 5.5e6; }

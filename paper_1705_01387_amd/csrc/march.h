@@ -137,9 +137,9 @@ hipError_t launch_march(int pattern, int hop_mode, int family, int lanes, int pa
 bool plan_patch(const MarchLattice& M, const std::vector<int64_t>& seg_off, int family, int B, int max_items, int cus,
                 MarchPlan* out);
 // Estimated times (microseconds): a launch of the plan's T steps, a single step of a family by the general
-// kernels (nnz: stored entries), and the change of layout of a block of vectors.
+// kernels (nnz: stored entries; tuned: with the autotuner's row order and caps), and the change of layout of a block of vectors.
 double plan_launch_us(const MarchLattice& M, int hop_mode, int family, int B, int cus, const MarchPlan& p);
-double general_step_us(int family, int hop_mode, int64_t n, int64_t nnz, int B);
+double general_step_us(int family, int hop_mode, int64_t n, int64_t nnz, int B, bool tuned);
 double planar_us(int64_t n, int B);
 constexpr double kPatchFixedUs = 2.3;   // of a patch launch's time, what does not shrink with its steps
 // planar[c * n + r] = rows[r * B + c], and back
