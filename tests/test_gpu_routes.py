@@ -77,28 +77,58 @@ def test_few_steps(gpu):
 # Hermitian and evolution tiles of a box own 26 x 26 cells at most, the commutator's and the two chains' 28 x 28;
 # runs of one plane and of several.
 BOXES = {
-    "26x53x44": lambda: I.box(26, 53, 44, W=3.0, seed=6),
-    "28x57x40_shuffled": lambda: I.box(28, 57, 40, W=3.0, seed=7, slot_seed=8),
-    "57x53x21": lambda: I.box(57, 53, 21, W=3.0, seed=9),
-    "90x11x40": lambda: I.box(90, 11, 40, W=3.0, seed=10),
+    "26x53x44": (lambda: I.box(26, 53, 44, W=3.0, seed=6), 16),
+    "28x57x40_shuffled": (lambda: I.box(28, 57, 40, W=3.0, seed=7, slot_seed=8), 16),
+    "57x53x21": (lambda: I.box(57, 53, 21, W=3.0, seed=9), 16),
+    "90x11x40": (lambda: I.box(90, 11, 40, W=3.0, seed=10), 16),
+    "79x66x61": (lambda: I.box(79, 66, 61, W=3.0, seed=15), 4),
+    "105x99x98": (lambda: I.box(105, 99, 98, W=3.0, seed=16), 1),
 }
+
+
+def against_general(H, call):
+    """{name: tensor} of call with the marches and without."""
+    code = H.info.kernel_variant
+    on = call()
+    P.gpuqt_set_variant(H, code & ~MARCH)
+    off = call()
+    P.gpuqt_set_variant(H, code)
+    for k, ref in off.items():
+        assert ((on[k] - ref).abs().max() / ref.abs().max()).item() < TOL, k
 
 
 @pytest.mark.parametrize("name", list(BOXES))
 def test_box_marches(gpu, name):
-    """Boxes that march every family but the two chains, blocks of 16, against the general kernels."""
+    """Boxes that march every family but the two chains, against the general kernels."""
     print(f"case: box march {name}", flush=True)
-    m = BOXES[name]()
+    make, B = BOXES[name]
+    m = make()
     H = P.gpuqt_build_h_from_model(m)
-    d, c = vectors(m.n, 16, 11), vectors(m.n, 16, 12)
+    d, c = vectors(m.n, B, 11), vectors(m.n, B, 12)
     on = marched(H, d, 48)
     assert on["sym"] and on["evo"] and on["msd"], on
-    both = []
-    code = H.info.kernel_variant
-    for v in (code, code & ~MARCH):
-        P.gpuqt_set_variant(H, v)
-        both.append(dict(mu=P.gpuqt_moments(H, d, d, 50), odd=P.gpuqt_moments(H, d, d, 63),
-                         one=P.gpuqt_evolve(H, d, -1.9), chi=P.gpuqt_evolve(H, d, 1.9, chi=c, with_commutator=True)[1],
-                         zero=P.gpuqt_evolve(H, d, 1.9, with_commutator=True)[1], msd=P.gpuqt_msd(H, d, [1.0, 1.3], 40)))
-    for k, ref in both[1].items():
-        assert ((both[0][k] - ref).abs().max() / ref.abs().max()).item() < TOL, k
+    against_general(H, lambda: dict(
+        mu=P.gpuqt_moments(H, d, d, 50), odd=P.gpuqt_moments(H, d, d, 63), one=P.gpuqt_evolve(H, d, -1.9),
+        chi=P.gpuqt_evolve(H, d, 1.9, chi=c, with_commutator=True)[1],
+        zero=P.gpuqt_evolve(H, d, 1.9, with_commutator=True)[1], msd=P.gpuqt_msd(H, d, [1.0, 1.3], 40)))
+
+
+@pytest.mark.parametrize("name", list(BOXES))
+def test_box_vac_marches(gpu, name):
+    """A VAC series of few moments and long steps: there the marches of the two-vector evolution outweigh those of the
+    two chains, and both run; recorded rows and their tape's gradients as well."""
+    import torch
+    print(f"case: box VAC march {name}", flush=True)
+    make, B = BOXES[name]
+    m = make()
+    H = P.gpuqt_build_h_from_model(m)
+    d, dts, M = vectors(m.n, B, 13), [4.0, 0.5, 3.0], 11
+    assert launches(H, "moment_pair", lambda: P.gpuqt_vac(H, d, dts, M)) < 3 * (M // 2)
+    w = torch.from_numpy(np.random.default_rng(14).normal(size=(3, 1, B, M))).cuda()
+
+    def rows():
+        out, tape = P.gpuqt_vac_record(H, d, dts, M)
+        assert torch.equal(out, P.gpuqt_vac(H, d, dts, M))
+        return dict(rows=out, tape=P.gpuqt_vac_backward_tape(H, d, dts, w, tape)[0])
+
+    against_general(H, rows)
