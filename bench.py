@@ -329,7 +329,7 @@ def single_vector_steps(P, torch, H, n, dev, args, seed=4200):
         ms, nl = fam[f]
         avg = ms / 1e3 / nl
         b = family_bytes(H.info, 1, f)
-        out[name] = {"kernel": FAMILY_KERNEL[f], "B": 1, "launches": nl, "avg_us": avg * 1e6,
+        out[name] = {"kernel": kernel_name(H.info, 1, f), "B": 1, "launches": nl, "avg_us": avg * 1e6,
                      "bytes_per_launch": b, "GBs": b / avg / 1e9, "frac": b / avg / 1e9 / HBM_PEAK_GBS,
                      "variant": variant_text(H.info.kernel_variant, f),
                      "traffic": measured_traffic("cubic_b1" if f == "moment_sym" else "cubic_b1_plain", f, b,

@@ -216,7 +216,6 @@ struct Handle {
     A.hidx = d_hidx;
     A.htab = reinterpret_cast<const double2*>(d_htab);
     A.S_log2 = S_log2;
-    A.K = uniform_width;
     for (int j = 0; j < 8; ++j) A.slot[j] = lat.slot[j];
     A.dx = lat.dx;
     A.dxcol = d_dxcol;

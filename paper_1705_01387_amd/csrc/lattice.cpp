@@ -247,7 +247,6 @@ bool detect_lattice(const gpuqt_h_desc* d, const HostLayout& L, const int32_t bo
 bool plan_march(const MarchLattice& M, const std::vector<int64_t>& seg_off, int T, int B, int max_items, int cus,
                 const std::vector<int>& lane_choices, int max_tile_x, MarchPlan* out) {
   const int n_seg = (int)seg_off.size() - 1;
-  if (M.pattern == MARCH_CHAIN || M.pattern == MARCH_NNN) return false;
   const bool box = M.pattern == MARCH_BOX;
   double best = 0.0;
   const double idle = T >= 8 ? 0.7 : 0.1;
@@ -351,9 +350,10 @@ bool plan_march(const MarchLattice& M, const std::vector<int64_t>& seg_off, int 
 // 2.00 / 2.69 with four steps), else four, whose smaller margins mean fewer patches (512^2: 3.2 / 4.9
 // against 4.0 / 6.2; next-nearest neighbours 4.7 / 6.7 against 6.1 / 9.3).  Where the lattice has marches
 // they are the faster beyond two rounds (two rounds, 512^2: patches 3.2 / 4.9 and with sums 3.1 / 5.2, marches
-// 3.3 / 4.8 and 3.9 / 6.1; four, 512^2 and two vectors: 5.6 / 8.9 and 4.9 / 9.5 against 4.3 / 5.8 and 5.5 / 9.4);
-// next-nearest neighbours have none, and four steps a launch beat single ones at every size (1000^2: 14.4 /
-// 21 against 22 / 33, with sums 12.5 / 20 against 28 / 45).
+// 3.3 / 4.8 and 3.9 / 6.1; four, 512^2 and two vectors: 5.6 / 8.9 and 4.9 / 9.5 against 4.3 / 5.8 and 5.5 / 9.4).
+// Measured on squares with one hopping, which brick lattices and hoppings per entry follow: none of their patches
+// measured was slower than the general kernels.  Next-nearest neighbours have no marches (four steps a
+// launch against single ones, 1000^2: 14.4 / 21 against 22 / 33, with sums 12.5 / 20 against 28 / 45).
 bool plan_patch(const MarchLattice& M, const std::vector<int64_t>& seg_off, int family, int B, int max_items, int cus,
                 MarchPlan* out) {
   const int n_seg = (int)seg_off.size() - 1;

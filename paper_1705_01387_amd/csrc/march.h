@@ -80,7 +80,7 @@ struct MarchMat {
   const double* hop;            // per entry, real or complex
   const uint16_t* hidx;         // table index per entry
   const double2* htab;
-  int32_t S_log2, K;
+  int32_t S_log2;
   int32_t slot[8];
   double dx;                    // BOX
   const double* dxcol;          // two dimensions

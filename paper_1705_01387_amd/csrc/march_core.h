@@ -17,9 +17,9 @@
 // launch before and this one: square 2000^2, one vector, Hermitian step 47 -> 9.9 us (T = 8,
 // two waves a SIMD; T = 4 14.8, T = 6 11.3, T = 10 11.8 at one wave), two chains 91.5 -> 26.2
 // (T = 5); brick 2000 x 1000 with complex hoppings, Hermitian 21 -> 9.4 (T = 5), two chains
-// 34 -> 21 (T = 4); box 200^3, four vectors, Hermitian 277 -> 159 (T = 3; T = 2 232), MSD term
-// 945 -> 618 (T = 2): there the counted traffic, 1.22 and 1.24 of two elements read and two
-// written a chain, moves at 87 and 100 % of the copy rate.
+// 34 -> 21 (T = 4); box 200^3, four vectors, Hermitian 277 -> 160 (T = 3; T = 2 232), MSD term
+// 945 -> 684 (T = 2): there the counted traffic, 1.22 and 1.24 of two elements read and two
+// written a chain, moves at 86 and 90 % of the copy rate.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -42,9 +42,6 @@ constexpr bool has_dots(int fam) { return fam == MF_SYM || fam == MF_PAIR; }
 // index never leaves it.
 constexpr int kMaxTileX = 64;
 constexpr int margin_of(int pat) { return pat == MARCH_BOX ? kMaxTileX : 1; }
-constexpr size_t lds_bytes(int pat, int fam, int T, int lanes) {
-  return (size_t)2 * (two_chains(fam) ? 2 : 1) * T * (lanes + 2 * margin_of(pat)) * sizeof(double2);
-}
 
 // Sums over the wavefront of N values a lane holds (N a power of two, at most 64): while
 // more than one is left, a lane hands half of them to the lane `off` away and takes that
@@ -513,9 +510,9 @@ __global__ __launch_bounds__(LANES, PAT == MARCH_BOX ? 4 : FAM == MF_PAIR ? 1 : 
 
 // Steps per launch of each kernel: more of them mean fewer bytes per step, more
 // registers (12 per level and chain, and the hoppings of T rows) and wider margins.  The
-// counts are the fastest that keep two waves a SIMD (a box: 16 waves of one workgroup),
-// measured as above; the sums of a series are formed where the last three levels meet, so
-// T <= 3 there.
+// counts are the fastest that keep two waves a SIMD (a box: 16 waves of one workgroup; two chains with
+// their dots run at one), measured as above; the sums of a series are formed where the last three
+// levels meet, so T <= 3 there.
 static_assert(kMarchMaxSteps >= 8, "the most steps of steps_of");
 constexpr int steps_of(int pat, int hop, int fam) {
   const bool entry = hop != HOP_UNIFORM;
