@@ -33,8 +33,8 @@ Also on the line:
   copy_probe_GBs a full-grid 16-byte copy kernel over 2 x 1 GiB.
 
 Other workloads (--workload): honeycomb (2,000,000-orbital honeycomb with Peierls phases, one
-vector, DOS + VAC + MSD at M = 3000: its working set fits the 256 MB last-level cache, so
-the roofline is labelled "llc"); honeycomb-general (the same with every hopping stored per
+vector, DOS + VAC + MSD at M = 3000; a roofline whose launch fits the 256 MB last-level cache
+is labelled "llc", a march's 284 MB do not); honeycomb-general (the same with every hopping stored per
 entry, as an arbitrary hopping.in gives); batched (8 uneven square realisations x 16 vectors
 in one launch per step, eager vs graph-captured, and vs one vector at a time); small (square
 64 x 64: DOS + VAC + MSD, launch-bound, eager vs graph-captured); paper; train.
