@@ -13,7 +13,7 @@ CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libgpuqt.so")
 BUILD_DIR = os.path.join(ROOT, "_build")
 
-SOURCES = ["kernels.hip", "kernels_adjoint.hip", "kernels_adjoint_pair.hip", "kernels_adjoint_sym.hip", "api.cpp", "layout.cpp", "io.cpp", "tune.cpp", "noalloc.hip",
+SOURCES = ["kernels.hip", "kernels_kpm.hip", "kernels_adjoint.hip", "kernels_adjoint_pair.hip", "kernels_adjoint_sym.hip", "api.cpp", "layout.cpp", "io.cpp", "tune.cpp", "noalloc.hip",
            "lattice.cpp", "march.hip", "march_square_uniform.hip", "march_square_real.hip", "march_square_complex.hip", "march_square_dict.hip",
            "march_brick_uniform.hip", "march_brick_real.hip", "march_brick_complex.hip", "march_brick_dict.hip",
            "march_box_uniform.hip",

@@ -421,7 +421,7 @@ bool detect_box(const gpuqt_h_desc* d, int32_t box[3]);
 // Every segment s of layout L (rows seg_off[s] ..) a periodic Lx x Ly square in natural
 // order: row seg_off[s] + x + Lx y with exactly the four neighbours (x +- 1 mod Lx, y) and
 // (x, y +- 1 mod Ly) in any slot order, Lx, Ly >= 3, Lx Ly <= 2^24 (a segment of a block
-// of 16 vectors spans at most 4 GiB: the sheet kernel addresses it with 32-bit offsets).
+// of 16 vectors spans at most 4 GiB, which marches address with 32-bit offsets).
 // sheet = (Lx, Ly) per segment when all are, else false.
 bool detect_sheets(const gpuqt_h_desc* d, const std::vector<int64_t>& seg_off, std::vector<int32_t>* sheet);
 

@@ -497,193 +497,6 @@ __global__ __launch_bounds__(256) void k_sigma(int mode, int n_t, const double* 
   }
 }
 
-// KPM sum of Section 3.3, one (row r, energy) per wavefront and kKpmEnergies of them in turn:
-// s = sum_n 2 g_n c_n T_n(x), the damped coefficients of kKpmTile moments at a time in LDS (g_n and its
-// sincospi once a workgroup, not once an energy).  Lane l takes the moments l + 64 i of a tile: T_{n+64} = 2
-// T_64 T_n - T_{n-64} from T_n = cos(n acos x), so no chain is longer than 16 steps (a chain over
-// all moments costs a rounding error that grows with n, and at the band's edges with n^2).
-// Bound by latency: 1001 energies, 1000 moments, one row: 200 us with a thread per energy and one chain
-// over all moments, 7.8 us so.
-constexpr int kKpmTile = 1024, kKpmEnergies = 2, kKpmWaves = 4;
-
-__global__ __launch_bounds__(64 * kKpmWaves) void k_kpm(int R, int M, const double* __restrict__ C, int n_E,
-                                                        const double* __restrict__ E, double inv_dE,
-                                                        double pref_base, int jackson, double cot_pa,
-                                                        double* __restrict__ out) {
-  __shared__ double wc[kKpmTile];
-  const int r = blockIdx.y;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int e0 = (blockIdx.x * kKpmWaves + wave) * kKpmEnergies;
-  const double a = 1.0 / (M + 1);
-  const double* c = C + (int64_t)r * M;
-  double x[kKpmEnergies], th[kKpmEnergies], c64[kKpmEnergies], s[kKpmEnergies];
-#pragma unroll
-  for (int q = 0; q < kKpmEnergies; ++q) {
-    x[q] = e0 + q < n_E ? E[e0 + q] * inv_dE : 0.0;
-    th[q] = acos(x[q]);                      // (a NaN past the band; not used)
-    c64[q] = 2.0 * cos(64.0 * th[q]);
-    s[q] = 0.0;
-  }
-  for (int n0 = 0; n0 < M; n0 += kKpmTile) {
-    const int m = min(kKpmTile, M - n0);
-    __syncthreads();
-    for (int i = threadIdx.x; i < m; i += 64 * kKpmWaves) {
-      const int n = n0 + i;
-      double g = n == 0 ? 1.0 : 2.0;
-      if (jackson && n > 0) {
-        double sn, cs;
-        sincospi(n * a, &sn, &cs);
-        g *= (1.0 - n * a) * cs + a * sn * cot_pa;
-      }
-      wc[i] = g * c[n];
-    }
-    __syncthreads();
-    double t[kKpmEnergies], u[kKpmEnergies];   // T_n, T_{n-64}
-#pragma unroll
-    for (int q = 0; q < kKpmEnergies; ++q) {
-      t[q] = cos((n0 + lane) * th[q]);
-      u[q] = cos((n0 + lane - 64) * th[q]);
-    }
-    for (int i = lane; i < m; i += 64) {
-      const double w = wc[i];
-#pragma unroll
-      for (int q = 0; q < kKpmEnergies; ++q) {
-        s[q] = fma(w, t[q], s[q]);
-        const double v = fma(c64[q], t[q], -u[q]);
-        u[q] = t[q];
-        t[q] = v;
-      }
-    }
-  }
-#pragma unroll
-  for (int q = 0; q < kKpmEnergies; ++q) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) s[q] += __shfl_xor(s[q], off);
-    if (lane == 0 && e0 + q < n_E)
-      out[(int64_t)r * n_E + e0 + q] =
-          fabs(x[q]) < 1.0 ? pref_base / sqrt(1.0 - x[q] * x[q]) * s[q] : __builtin_nan("");
-  }
-}
-
-// The same sum for many rows and energies: one energy and RQ rows a thread, 2^lE energies and 256 >> lE such
-// groups of rows a workgroup, kKpmRowTile moments of its rows in LDS.  T_n(x) comes from T_{n+1} = 2 x T_n -
-// T_{n-1}, started again every kKpmChain moments, for all RQ rows at once, from the cosine and sine of one
-// rounded angle: a chain keeps its angle's error, where two angles' cosines make it grow near the band's edges
-// (1000 moments up to 0.95 of the band, r.m.s. against extended precision: 2.7e-14, with two cosines 4.2e-14,
-// k_kpm 2.1e-14; 200 moments 4.3e-15, 6.3e-15, 5.0e-15).
-constexpr int kKpmRowTile = 64, kKpmChain = 16, kKpmRowsMinE = 4;   // (at least 2^kKpmRowsMinE energies)
-
-template <int RQ>
-__global__ __launch_bounds__(256) void k_kpm_rows(int R, int M, const double* __restrict__ C, int n_E,
-                                                  const double* __restrict__ E, double inv_dE, double pref_base,
-                                                  int jackson, double cot_pa, int lE, double* __restrict__ out) {
-  constexpr int STRIDE = kKpmRowTile * RQ + 2;   // of a group of rows (+ 2: groups start in other banks)
-  extern __shared__ double wr[];                 // [256 >> lE][STRIDE]
-  const int e = (int)((blockIdx.x << lE) | (threadIdx.x & ((1u << lE) - 1))), g = threadIdx.x >> lE, G = 256 >> lE;
-  const int64_t row0 = (int64_t)blockIdx.y * G * RQ;
-  const double a = 1.0 / (M + 1), x = e < n_E ? E[e] * inv_dE : 0.0;
-  const double th = acos(x), sx = sqrt(1.0 - x * x);   // (NaN past the band; not used)
-  double s[RQ];
-#pragma unroll
-  for (int r = 0; r < RQ; ++r) s[r] = 0.0;
-  for (int n0 = 0; n0 < M; n0 += kKpmRowTile) {
-    const int i = threadIdx.x & (kKpmRowTile - 1), n = n0 + i;   // the moment this thread brings, of every row
-    double w = n == 0 ? 1.0 : 2.0;
-    if (jackson && n > 0) {
-      double sn, cs;
-      sincospi(n * a, &sn, &cs);
-      w *= (1.0 - n * a) * cs + a * sn * cot_pa;
-    }
-    __syncthreads();
-    for (int q = threadIdx.x / kKpmRowTile; q < G * RQ; q += 256 / kKpmRowTile)
-      wr[q / RQ * STRIDE + i * RQ + q % RQ] = n < M && row0 + q < R ? w * C[(row0 + q) * M + n] : 0.0;
-    __syncthreads();
-    const double* wg = wr + g * STRIDE;
-    for (int c = n0; c < min(M, n0 + kKpmRowTile); c += kKpmChain) {
-      double t, sn;   // T_c, T_{c-1} = cos(c th - th)
-      sincos(c * th, &sn, &t);
-      double u = fma(t, x, sn * sx);
-#pragma unroll
-      for (int k = 0; k < kKpmChain; ++k) {
-#pragma unroll
-        for (int r = 0; r < RQ; ++r) s[r] = fma(wg[(c - n0 + k) * RQ + r], t, s[r]);
-        const double v = fma(2.0 * x, t, -u);
-        u = t;
-        t = v;
-      }
-    }
-  }
-  if (e >= n_E) return;
-#pragma unroll
-  for (int r = 0; r < RQ; ++r) {
-    const int64_t row = row0 + g * RQ + r;
-    if (row < R)
-      out[row * n_E + e] = fabs(x) < 1.0 ? pref_base / sqrt(1.0 - x * x) * s[r] : __builtin_nan("");
-  }
-}
-
-// Transpose of k_kpm: out[r][n] = sum_e g[r][e] pref(E_e) w_n T_n(E~_e).  kKpmMoments moments of a row to 2^lS
-// threads, which share the energies; energies outside the band contribute nothing.  acos, the square root and two cosines once
-// for all of a group's moments.
-constexpr int kKpmMoments = 8;
-
-__global__ __launch_bounds__(256) void k_kpm_adjoint(int R, int M, const double* __restrict__ g, int n_E,
-                                                     const double* __restrict__ E, double inv_dE,
-                                                     double pref_base, int jackson, double cot_pa, int lS,
-                                                     double* __restrict__ out) {
-  __shared__ double sh[4][kKpmMoments];
-  const int share = 1 << lS, in_wave = min(share, 64), l = threadIdx.x & (share - 1);
-  const int groups = (M + kKpmMoments - 1) / kKpmMoments;   // of a row
-  const int64_t q = (int64_t)blockIdx.x * (256 >> lS) + (threadIdx.x >> lS), r = q / groups;
-  const int n0 = (int)(q - r * groups) * kKpmMoments;
-  double s[kKpmMoments];
-#pragma unroll
-  for (int i = 0; i < kKpmMoments; ++i) s[i] = 0.0;
-  for (int e = r < R ? l : n_E; e < n_E; e += share) {
-    const double x = E[e] * inv_dE;
-    if (!(fabs(x) < 1.0)) continue;
-    const double th = acos(x);
-    const double f = g[r * n_E + e] * pref_base / sqrt(1.0 - x * x);
-    double t = cos(n0 * th), u = cos((n0 - 1) * th);
-#pragma unroll
-    for (int i = 0; i < kKpmMoments; ++i) {
-      s[i] = fma(f, t, s[i]);
-      const double v = fma(2.0 * x, t, -u);
-      u = t;
-      t = v;
-    }
-  }
-  for (int off = in_wave >> 1; off >= 1; off >>= 1)
-#pragma unroll
-    for (int i = 0; i < kKpmMoments; ++i) s[i] += __shfl_xor(s[i], off);
-  if (share > 64) {   // the group's wavefronts in order
-    if ((threadIdx.x & 63) == 0)
-#pragma unroll
-      for (int i = 0; i < kKpmMoments; ++i) sh[threadIdx.x >> 6][i] = s[i];
-    __syncthreads();
-    const int w0 = (threadIdx.x >> lS) * (share >> 6);
-#pragma unroll
-    for (int i = 0; i < kKpmMoments; ++i) {
-      s[i] = 0.0;
-      for (int w = 0; w < share >> 6; ++w) s[i] += sh[w0 + w][i];
-    }
-  }
-  if (r >= R || l >= 64) return;
-  const double a = 1.0 / (M + 1);
-#pragma unroll
-  for (int i = 0; i < kKpmMoments; ++i) {   // moment n0 + i from lane i of the group, or one after another
-    const int n = n0 + i;
-    if ((i & (in_wave - 1)) != l || n >= M) continue;
-    double wn = n == 0 ? 1.0 : 2.0;
-    if (jackson && n > 0) {
-      double sn, cs;
-      sincospi(n * a, &sn, &cs);
-      wn *= (1.0 - n * a) * cs + a * sn * cot_pa;
-    }
-    out[r * M + n] = wn * s[i];
-  }
-}
-
 // Bandwidth probe: one 16-byte element per thread over a grid that covers the
 // whole buffer (every element's load is in flight at once, as far as the chip
 // holds them; no loop-carried address arithmetic).
@@ -806,50 +619,6 @@ hipError_t launch_moment_step_sym(const DevMat& A, int hop_mode, int B, const St
     k_moment_step_sym<decltype(Bc)::value, decltype(Hc)::value, decltype(Kc)::value,
                       decltype(NTc)::value><<<dim3(A.G), kBlock, 0, s>>>(A, io, part_a, part_b, part_c);
   });
-}
-
-hipError_t launch_kpm(int R, int M, const double* C, int n_E, const double* E, double inv_dE,
-                      double pref_base, int jackson, double* out, hipStream_t s) {
-  if (R <= 0 || n_E <= 0) return hipSuccess;
-  const double a = 1.0 / (M + 1);
-  const double cot_pa = cos(M_PI * a) / sin(M_PI * a);
-  // Estimated times beyond a launch's 7 us: k_kpm 0.5 ns + 0.55 ps a moment for each (row, energy), eight energies a
-  // workgroup; k_kpm_rows 0.07 us a moment, the latency of its tiles.  284 sizes measured, 1 to 4096 rows, 8 to
-  // 4000 moments, 1 to 1001 energies: the slower one is taken by 18 % once (256 rows, 1000 moments, 256 energies,
-  // 69 us against 59), else by less.  k_kpm alone took 2313 us for 4096 rows, 8 moments and 1001 energies, where
-  // k_kpm_rows takes 21; one row and 1000 moments take 7.8 and 39.
-  const double rows_of_8 = 8.0 * R * ((n_E + 7) / 8);
-  if (rows_of_8 * (0.5e-3 + 5.5e-7 * M) > 0.07 * M) {
-    int lE = kKpmRowsMinE;
-    while (lE < 8 && (1 << lE) < n_E) ++lE;
-    const int rq = R >= 4 ? 4 : 1, G = 256 >> lE;
-    const dim3 grid((n_E + (1 << lE) - 1) >> lE, (R + G * rq - 1) / (G * rq));
-    const size_t lds = (size_t)G * (kKpmRowTile * rq + 2) * sizeof(double);
-    auto* k = rq == 4 ? k_kpm_rows<4> : k_kpm_rows<1>;
-    k<<<grid, 256, lds, s>>>(R, M, C, n_E, E, inv_dE, pref_base, jackson, cot_pa, lE, out);
-    return hipGetLastError();
-  }
-  constexpr int per = kKpmWaves * kKpmEnergies;
-  k_kpm<<<dim3((n_E + per - 1) / per, R), 64 * kKpmWaves, 0, s>>>(R, M, C, n_E, E, inv_dE, pref_base, jackson, cot_pa,
-                                                   out);
-  return hipGetLastError();
-}
-
-hipError_t launch_kpm_adjoint(int R, int M, const double* g, int n_E, const double* E, double inv_dE,
-                              double pref_base, int jackson, double* out, hipStream_t s) {
-  if (R <= 0 || M <= 0) return hipSuccess;
-  const double a = 1.0 / (M + 1);
-  const double cot_pa = cos(M_PI * a) / sin(M_PI * a);
-  // threads sharing a group's energies: as many as there are energies, until the groups fill the chip (2^18
-  // threads), and above 2^16 threads no fewer than four energies each.  Within 15 % of the best of 1 to 256 threads at the
-  // 284 sizes of launch_kpm; 256 threads always took 2730 us for 4096 rows, 1000 moments and one energy, one takes 26.
-  const int64_t groups = (int64_t)R * ((M + kKpmMoments - 1) / kKpmMoments);
-  int lS = 8;
-  while (lS > 0 && ((groups << lS) > (1 << 18) || (1 << lS) > n_E || ((groups << lS) > (1 << 16) && (4 << lS) > n_E))) --lS;
-  const int per = 256 >> lS;   // groups a workgroup
-  k_kpm_adjoint<<<dim3((unsigned)((groups + per - 1) / per)), 256, 0, s>>>(R, M, g, n_E, E, inv_dE, pref_base, jackson,
-                                                                           cot_pa, lS, out);
-  return hipGetLastError();
 }
 
 hipError_t launch_transport(const TransportIO& io, hipStream_t s) {
